@@ -1,19 +1,26 @@
 // Differentiable rollout: forward with checkpoints and backward by recomputation.
 //
-// Forward: a group of kGroup lanes per agent runs T steps of the configured model
-// (computed alike by the group's lanes, which share the nearest-edge search) and after
-// each step the
-// smooth reward  r = -|g'| - softplus(s),  g' = R(-yaw)(g - p),  s = signed distance (in
-// the ego frame, positive on the right of the segment direction, i.e. off-road) to the
-// nearest road-edge segment within the observation radius (s = -R when there is none).
-// The reward is an instance of the configurable agent/road-distance rewards of Sec. 3.2
-// "Rewards".  The state before every ckpt_every-th step is saved.
+// Forward: a row of 16 lanes per agent takes 16 steps of the configured model at a time, a
+// lane per step: what a step needs from the steps before it is a running sum, everything
+// else (trigonometry, nearest edge, reward) is independent and formed by all lanes at once.
+// After each step the smooth reward is  r = -|g'| - softplus(s),  g' = R(-yaw)(g - p),
+// s = signed distance (in the ego frame, positive on the right of the segment direction,
+// i.e. off-road) to the nearest road-edge segment within the observation radius (s = -R when
+// there is none).  The reward is an instance of the configurable agent/road-distance
+// rewards of Sec. 3.2 "Rewards".  The state before every ckpt_every-th step is saved.
 //
-// Backward: per segment of ckpt_every steps, last segment first, the forward is recomputed
-// from its checkpoint into LDS (states and nearest-segment choices), then the adjoint of
-// (x, y, yaw, v) is carried backwards through the reward and the dynamics, producing
-// dJ/d(accel, steer) for every step.  Segment choice, side and clip activity are held
-// constant; the result does not depend on ckpt_every.
+// Backward: per block of steps, last block first, the forward is recomputed from its
+// checkpoint, a lane per step; each lane forms the reward's derivative and the coefficients
+// of the adjoint's recursion at its step, the recursion over (x, y, yaw, v) runs backwards
+// with them, and each lane turns the adjoint at its step into dJ/d(accel, steer).  Segment
+// choice, side and clip activity are held constant; the result does not depend on
+// ckpt_every.
+//
+// Both are bound by vector instructions (per agent-step, 4096 worlds x 64 agents, 6000 road
+// points, T = 91, checkpoints every 10 steps: forward 33, backward 50).  With 8 lanes per
+// agent that repeated the dynamics and the reward and shared one nearest-edge search per
+// step they took 176 and 185, and the time was 9.45 + 11.4 ms against 1.54 + 2.16 ms now;
+// 512 x 32 agents, T = 20: 182 + 190 against 27 + 31 us.
 //
 // Observation (optional): the forward can log the state after every step, from which
 // k_rollout_obs forms the continuous observation of each agent (speed, goal in its frame;
@@ -25,111 +32,385 @@
 
 namespace gdk {
 
-constexpr int kRollThreads = 64;                // threads per workgroup
-constexpr int kGroup = 8;                       // lanes per agent (half a DPP row)
-constexpr int kRollAgents = kRollThreads / kGroup;
+constexpr int kRollThreads = 256;               // threads per workgroup
+constexpr int kRow = 16;                        // lanes per agent: one DPP row, a lane per step
+constexpr int kRollAgents = kRollThreads / kRow;
 constexpr int kMaxCkpt = 32;
+constexpr int kEdgeList = 64;                   // candidate segments of a block of steps, per agent
+constexpr int kEdgeStride = kEdgeList + 1;      // (odd: the rows of a wave read other LDS banks)
 
 struct EdgeChoice {
     int q;          // cell-sorted position of the segment in the world's edge arrays, -1 = none
     float side;     // +1 off-road (right of the segment direction), -1 on-road
 };
 
-// Lane groups: 8 lanes (half a DPP row) work on one agent.  Minimum over the group of
-// (distance bits, world-local index) with the cell-sorted position carried along, by DPP
-// moves inside each half row (every lane ends with the group minimum).  8 lanes measured
-// faster than 16 (forward 1.37 -> 1.59 G agent-steps/s on 512 x 32 agents, 1.78 -> 2.23 G
-// on 4096 x 64) and than 4.
-__device__ __forceinline__ void group_min(unsigned &hi, unsigned &lo, int &q) {
-#define GD_ROR_STEP(ctrl)                                                                   \
-    {                                                                                      \
-        const unsigned h2 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)hi, ctrl, 0xf, 0xf, false); \
-        const unsigned l2 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)lo, ctrl, 0xf, 0xf, false); \
-        const int q2 = __builtin_amdgcn_update_dpp(0, q, ctrl, 0xf, 0xf, false);           \
-        const bool less = h2 < hi || (h2 == hi && l2 < lo);                                \
-        hi = less ? h2 : hi;                                                               \
-        lo = less ? l2 : lo;                                                               \
-        q = less ? q2 : q;                                                                 \
+// ---- rows of 16 lanes
+// value of lane K of the row, on all of its lanes
+template <int K>
+__device__ __forceinline__ float row_bcast(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + K, 0xf, 0xf, true));  // row_newbcast
+}
+// value of the lane before (lane 0: `first`)
+__device__ __forceinline__ float row_before(float v, float first) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(first), __float_as_int(v), 0x111, 0xf, 0xf, false));  // row_shr:1
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+// minimum over the row, on all of its lanes (row rotations)
+__device__ __forceinline__ float row_min(float v) {
+    v = fminf(v, dpp_f<0x128>(v));
+    v = fminf(v, dpp_f<0x124>(v));
+    v = fminf(v, dpp_f<0x122>(v));
+    return fminf(v, dpp_f<0x121>(v));
+}
+// ballot of the row's 16 lanes
+__device__ __forceinline__ unsigned row_ballot(bool p) {
+    return (unsigned)(__ballot(p) >> (threadIdx.x & 48)) & 0xffffu;
+}
+// f(0), f(1), ... f(15) with constant arguments, in groups of four of which those at or
+// beyond the (wave-uniform) count n are left out
+template <int K>
+struct StepIndex {
+    static constexpr int k = K;
+};
+template <int K0, typename F>
+__device__ __forceinline__ void four_up(F &&f) {
+    f(StepIndex<K0>{});
+    f(StepIndex<K0 + 1>{});
+    f(StepIndex<K0 + 2>{});
+    f(StepIndex<K0 + 3>{});
+}
+template <typename F>
+__device__ __forceinline__ void each_step(int n, F &&f) {
+    four_up<0>(f);
+    if (n <= 4) return;
+    four_up<4>(f);
+    if (n <= 8) return;
+    four_up<8>(f);
+    if (n <= 12) return;
+    four_up<12>(f);
+}
+template <int K0, typename F>
+__device__ __forceinline__ void four_down(F &&f) {
+    f(StepIndex<K0 + 3>{});
+    f(StepIndex<K0 + 2>{});
+    f(StepIndex<K0 + 1>{});
+    f(StepIndex<K0>{});
+}
+template <typename F>
+__device__ __forceinline__ void each_step_down(int n, F &&f) {
+    if (n > 12) four_down<12>(f);
+    if (n > 8) four_down<8>(f);
+    if (n > 4) four_down<4>(f);
+    four_down<0>(f);
+}
+
+// world of agent i: the largest w with agent_off[w] <= i, by a 16-way search of the row
+__device__ __forceinline__ int world_of_row(const int *agent_off, int W, int i, int sub) {
+    int lo = 0, len = W;
+    while (len > 1) {
+        const int st = (len + kRow - 1) / kRow;
+        const int o = sub * st;
+        const bool le = o < len && agent_off[lo + o] <= i;
+        const int c = max(__popc(row_ballot(le)), 1) - 1;
+        lo += c * st;
+        len = min(st, len - c * st);
     }
-    GD_ROR_STEP(0x141)  // row_half_mirror: lane i of 8 against lane 7 - i
-    GD_ROR_STEP(0xB1)   // quad_perm [1, 0, 3, 2]
-    GD_ROR_STEP(0x4E)   // quad_perm [2, 3, 0, 1]
-#undef GD_ROR_STEP
+    return lo;
 }
 
-// Sum over the 8 lanes of a group (every lane ends with the same total, summed in the same
-// order on every lane).
-__device__ __forceinline__ float group_sum(float v) {
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, false));  // row_half_mirror
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, false));   // quad_perm [1,0,3,2]
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, false));   // quad_perm [2,3,0,1]
-    return v;
+// ---- a block of up to 16 steps of one agent, a lane per step
+struct AgentState {  // the state a block starts from, the same on all lanes of the row
+    float x, y, yaw, v, sn, cs;  // sn, cs: sine and cosine of yaw
+};
+struct StepState {   // this lane's step: the state before (0) and after (1) it
+    float x0, y0, yaw0, v0, sn0, cs0;
+    float x1, y1, yaw1, v1, sn1, cs1;
+    float ts, cb, sb, sp, cp;  // bicycle: tan(steer), slip angle, direction of motion
+    float vb;                  // bicycle: clipped midpoint speed; simplified model: distance
+};
+
+// The n steps of a block from state c.  What a step needs from the steps before it is a sum
+// (speed, heading and position in turn), so the only serial part is one or a few additions
+// per step, taken on all lanes of the row with the step's increment broadcast from its lane;
+// tangents, sines and divisions are formed once per lane.  Every operation is rounded as in a
+// step-by-step evaluation.  Bicycle model (App. B): slip angle beta = atan(tan(steer) / 2)
+// through cos beta = 1 / sqrt(1 + z^2), sin beta = z cos beta (z = tan(steer) / 2), the
+// direction of motion by angle addition.
+template <bool DELTA>
+__device__ __forceinline__ void run_block(const AgentState &c, float2 u, int n, int sub, float L, float dt,
+                                          float vmax, StepState &o) {
+#pragma clang fp contract(off)
+    const float acc = u.x, h = 0.5f * acc;
+    float ix, iy, iw;  // increments of the lane's step
+    // speed before the step
+    float v = c.v;
+    each_step(n, [&](auto kc) {
+        constexpr int k = decltype(kc)::k;
+        float w = __builtin_fmaf(row_bcast<k>(acc), dt, v);
+        if (!DELTA) w = fminf(fmaxf(w, -vmax), vmax);
+        v = sub > k ? w : v;
+    });
+    o.v0 = v;
+    o.v1 = __builtin_fmaf(acc, dt, v);
+    if (DELTA) {
+        o.vb = __builtin_fmaf(v, dt, h * dt * dt);
+        iw = u.y * o.vb;
+    } else {
+        o.v1 = fminf(fmaxf(o.v1, -vmax), vmax);
+        o.vb = fminf(fmaxf(__builtin_fmaf(h, dt, v), -vmax), vmax);
+        o.ts = tanf(u.y);
+        const float z = 0.5f * o.ts;
+        o.cb = __builtin_amdgcn_rsqf(__builtin_fmaf(z, z, 1.0f));
+        o.sb = z * o.cb;
+        iw = o.vb * o.cb * o.ts / L * dt;
+    }
+    // heading before the step
+    float yaw = c.yaw;
+    each_step(n, [&](auto kc) {
+        constexpr int k = decltype(kc)::k;
+        const float w = yaw + row_bcast<k>(iw);
+        yaw = sub > k ? w : yaw;
+    });
+    o.yaw0 = yaw;
+    o.yaw1 = yaw + iw;
+    sincosf(o.yaw1, &o.sn1, &o.cs1);
+    o.sn0 = row_before(o.sn1, c.sn);  // the step before ends with this step's heading
+    o.cs0 = row_before(o.cs1, c.cs);
+    if (DELTA) {
+        ix = o.vb * o.cs0;
+        iy = o.vb * o.sn0;
+    } else {
+        o.sp = __builtin_fmaf(o.cs0, o.sb, o.sn0 * o.cb);
+        o.cp = __builtin_fmaf(o.cs0, o.cb, -(o.sn0 * o.sb));
+        ix = o.vb * o.cp * dt;
+        iy = o.vb * o.sp * dt;
+    }
+    // position before the step
+    float x = c.x, y = c.y;
+    each_step(n, [&](auto kc) {
+        constexpr int k = decltype(kc)::k;
+        const float wx = x + row_bcast<k>(ix), wy = y + row_bcast<k>(iy);
+        x = sub > k ? wx : x;
+        y = sub > k ? wy : y;
+    });
+    o.x0 = x;
+    o.y0 = y;
+    o.x1 = x + ix;
+    o.y1 = y + iy;
 }
 
-// nearest road-edge segment to (px, py) within R (ties -> lowest world-local index), by
-// rings of grid cells around the point's cell, searched by the lanes of a group (`sub`
-// = lane within the group; each cell's segments are spread over them).  Segments are keyed by the cell of their
-// first point, so a segment at distance d has its key within d + max_seg.  A key in a cell
-// r rings out is at least (r - 1) * cs away, so before ring r is searched every unseen
-// segment is at least (r - 1) * cs - max_seg away, and the search stops once that exceeds
-// the best distance found (or the radius).
-__device__ EdgeChoice nearest_edge_group(const WorldGrid &g, const int *ecs, const float4 *es,
-                                     const int *eid, float px, float py, float R, int sub) {
-    EdgeChoice ch{-1, -1.0f};
-    if (g.n_edge == 0 || !(px == px) || !(py == py)) return ch;
-    const float fx = floorf((px - g.ox) * g.inv_cs), fy = floorf((py - g.oy) * g.inv_cs);
-    const int cx = (int)fminf(fmaxf(fx, -1.0e6f), 1.0e6f);
-    const int cy = (int)fminf(fmaxf(fy, -1.0e6f), 1.0e6f);
-    const int rmax = (int)ceilf((R + g.max_seg) * g.inv_cs) + 1;
-    // segments are ranked by their binary32 squared distance (the square root, monotone,
-    // is taken once per ring and for the winner only)
-    unsigned bhi = 0x7f800000u, blo = 0xffffffffu;  // (+inf, no index)
-    int bq = -1;
-    for (int r = 0; r <= rmax; r++) {
-        group_min(bhi, blo, bq);
-        const float best = sqrtf(__uint_as_float(bhi));
-        if (best <= R && best + g.max_seg + 1e-3f * g.cs < (float)(r - 1) * g.cs) break;
-        const int y0 = max(cy - r, 0), y1 = min(cy + r, g.ny - 1);
-        for (int yy = y0; yy <= y1; yy++) {
-            const bool edge_row = (yy == cy - r) || (yy == cy + r);
-            const int xa = cx - r, xb = cx + r;
-            for (int side = 0; side < (edge_row ? 1 : 2); side++) {
-                int x0, x1;
-                if (edge_row) {
-                    x0 = max(xa, 0);
-                    x1 = min(xb, g.nx - 1);
-                } else {
-                    x0 = x1 = side == 0 ? xa : xb;
-                    if (x0 < 0 || x0 >= g.nx) continue;
-                }
-                if (x0 > x1) continue;
-                const int q0 = ecs[yy * g.nx + x0], q1 = ecs[yy * g.nx + x1 + 1];
-                for (int q = q0 + sub; q < q1; q += kGroup) {
-                    const float4 e = es[q];
-                    const float ex = e.z - e.x, ey = e.w - e.y;
-                    const float ax = e.x - px, ay = e.y - py;
-                    const float ee = ex * ex + ey * ey;
-                    // closest point with the hardware reciprocal (1 ulp; ties closer than
-                    // the 1e-4 m band are decided alike by the forward and its recompute)
-                    float u = ee > 0.0f ? -(ax * ex + ay * ey) * __builtin_amdgcn_rcpf(ee) : 0.0f;
-                    u = fminf(fmaxf(u, 0.0f), 1.0f);
-                    const float qx = ax + u * ex, qy = ay + u * ey;
-                    const float d2 = qx * qx + qy * qy;
-                    const unsigned dh = __float_as_uint(d2), k = (unsigned)eid[q];
-                    if (dh < bhi || (dh == bhi && k < blo)) {
-                        bhi = dh;
-                        blo = k;
-                        bq = q;
-                    }
-                }
-            }
+// the state after a block of 16 steps
+__device__ __forceinline__ AgentState after_block(const StepState &o) {
+    return {row_bcast<15>(o.x1), row_bcast<15>(o.y1), row_bcast<15>(o.yaw1),
+            row_bcast<15>(o.v1), row_bcast<15>(o.sn1), row_bcast<15>(o.cs1)};
+}
+
+// ---- nearest road-edge segment
+struct EdgeGrid {  // a world's edge segments
+    WorldGrid g;
+    const int *ecs;
+    const float4 *es;
+    const int *eid;
+};
+// the last block's nearest segment q (-1: none yet) at distance d of the point (x, y) of the
+// path next to the coming block
+struct EdgeBound {
+    float x, y, d;
+    int q;
+};
+
+// Visits, 16 at a time, every segment that can lie within r of (cx, cy): f(q, ok) with the
+// segment's cell-sorted position (ok = false: padding).  Segments are keyed by the cell of
+// their first point, so the square of cells is widened by the longest segment.
+template <typename F>
+__device__ __forceinline__ void scan_edges(const EdgeGrid &e, float cx, float cy, float r, int sub, F &&f) {
+    const WorldGrid &g = e.g;
+    const float rr = r + g.max_seg + 1e-3f * g.cs;
+    const int x0 = cell_coord(cx - rr, g.ox, g.inv_cs, g.nx), x1 = cell_coord(cx + rr, g.ox, g.inv_cs, g.nx);
+    const int y0 = cell_coord(cy - rr, g.oy, g.inv_cs, g.ny), y1 = cell_coord(cy + rr, g.oy, g.inv_cs, g.ny);
+    for (int yb = y0; yb <= y1; yb += kRow) {
+        // a lane per grid row: its range of segments
+        const int yy = min(yb + sub, y1);
+        const int q0 = e.ecs[yy * g.nx + x0], q1 = e.ecs[yy * g.nx + x1 + 1];
+        const int m = min(kRow, y1 - yb + 1);
+        for (int k = 0; k < m; k++) {
+            const int b1 = __shfl(q1, k, kRow);
+            for (int q = __shfl(q0, k, kRow); q < b1; q += kRow) f(q + sub, q + sub < b1);
         }
     }
-    group_min(bhi, blo, bq);
-    if (!(sqrtf(__uint_as_float(bhi)) <= R) || bq < 0) return ch;
+}
+
+// squared distance of (px, py) to the segment from (x0, y0) along (ex, ey); ir = 1 / |e|^2 (0
+// for a point)
+__device__ __forceinline__ float seg_d2(float x0, float y0, float ex, float ey, float ir, float px, float py) {
+    const float ax = x0 - px, ay = y0 - py;
+    const float u = fminf(fmaxf(-(ax * ex + ay * ey) * ir, 0.0f), 1.0f);
+    const float qx = ax + u * ex, qy = ay + u * ey;
+    return qx * qx + qy * qy;
+}
+
+// 1 / |e|^2 (the hardware reciprocal: 1 ulp; ties closer than the 1e-4 m band are decided
+// alike by the forward and its recompute), 0 for a segment without length
+__device__ __forceinline__ float seg_inv(float ex, float ey) {
+    const float ee = ex * ex + ey * ey;
+    return ee > 0.0f ? __builtin_amdgcn_rcpf(ee) : 0.0f;
+}
+
+// The candidate list of one row in LDS.
+struct EdgeList {
+    float4 *seg;  // x0, y0, ex, ey
+    float2 *inv;  // 1 / |e|^2, position (bits)
+    float *dc;    // distance from the centre of the row's points
+};
+
+// Nearest road-edge segment within R of each lane's point (px, py), by the smallest binary32
+// squared distance, ties to the lowest world-local index; `valid`: the lane has a point.
+// The row's points lie on one agent's path, rho from their centre c at most.  With D a
+// bound on the distance of c to its nearest segment, every point's nearest segment lies
+// within D + 2 rho of c:
+//   1. D from the segments stored around the last block's nearest one, or, without one,
+//      from widening squares of cells;
+//   2. the row collects the segments within D + 2 rho in LDS, a lane per segment;
+//   3. every lane takes its distance b to each fourth of them: its nearest one lies within
+//      b, so within max(b + |p - c|) of c for all lanes; the list shrinks to those;
+//   4. every lane takes its minimum over what is left, read by all lanes at once.
+// A full list is taken in parts.  Bound by vector instructions: step 4 over the whole list
+// of step 2 took about 65 instead of 20 segments per block and half of the kernel's time.
+__device__ __forceinline__ EdgeChoice nearest_edges(const EdgeGrid &e, const EdgeList &ls, float px, float py,
+                                                    bool valid, float R, int sub, EdgeBound &bd,
+                                                    bool last_lane) {
+    EdgeChoice ch{-1, -1.0f};
+    const WorldGrid &g = e.g;
+    valid = valid && fabsf(px) < INFINITY && fabsf(py) < INFINITY;
+    const float lox = row_min(valid ? px : INFINITY), hix = -row_min(valid ? -px : INFINITY);
+    const float loy = row_min(valid ? py : INFINITY), hiy = -row_min(valid ? -py : INFINITY);
+    float best = INFINITY;
+    int bq = -1;
+    if (g.n_edge > 0 && lox <= hix) {
+        const float cx = 0.5f * lox + 0.5f * hix, cy = 0.5f * loy + 0.5f * hiy;
+        const float wx = hix - lox, wy = hiy - loy;
+        // (slack for the rounding of distances between coordinates of this size)
+        const float marg = 1e-2f + 1e-3f * g.cs + 2e-6f * (fabsf(cx) + fabsf(cy));
+        const float rho = 0.5f * __builtin_amdgcn_sqrtf(wx * wx + wy * wy) + marg;
+        const float far = R + rho;  // nothing beyond it is within R of a point
+        auto centre_d2 = [&](int q, bool ok) {
+            const float4 s = e.es[ok ? q : 0];
+            const float ex = s.z - s.x, ey = s.w - s.y;
+            const float d2 = seg_d2(s.x, s.y, ex, ey, seg_inv(ex, ey), cx, cy);
+            return ok ? d2 : INFINITY;
+        };
+        float D;
+        if (bd.q >= 0) {
+            const int q = bd.q - kRow / 2 + sub;
+            const float d = __builtin_amdgcn_sqrtf(row_min(centre_d2(q, q >= 0 && q < g.n_edge)));
+            const float hx = cx - bd.x, hy = cy - bd.y;
+            D = fminf(d, bd.d + __builtin_amdgcn_sqrtf(hx * hx + hy * hy)) + marg;
+        } else {
+            for (float r = 0.5f * g.cs;; r *= 3.0f) {
+                r = fminf(r, far);
+                float d2 = INFINITY;
+                scan_edges(e, cx, cy, r, sub, [&](int q, bool ok) { d2 = fminf(d2, centre_d2(q, ok)); });
+                D = __builtin_amdgcn_sqrtf(row_min(d2)) + marg;
+                if (D <= r || !(r < far)) break;
+            }
+        }
+        const float rf = fminf(D + 2.0f * rho, far) + marg;
+        const float pcx = px - cx, pcy = py - cy;
+        const float pc = __builtin_amdgcn_sqrtf(pcx * pcx + pcy * pcy);
+        int cnt = 0;
+        auto sync = [] {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        };
+        auto distance2 = [&](int k, int &q) {
+            const float4 s = ls.seg[k];
+            const float2 t = ls.inv[k];
+            q = __float_as_int(t.y);
+            return seg_d2(s.x, s.y, s.z, s.w, t.x, px, py);
+        };
+        // the segments of the list pad to a multiple of four with some that are never nearer
+        auto pad = [&](int m) {
+            const int padded = (m + 3) & ~3;
+            if (m + sub < padded) {
+                ls.seg[m + sub] = make_float4(NAN, NAN, 0.f, 0.f);
+                ls.inv[m + sub] = make_float2(0.f, 0.f);
+            }
+            sync();
+            return padded;
+        };
+        auto take = [&]() {
+            sync();
+            float b2 = best;
+            for (int k = 0; k < cnt; k += 4) {
+                int q;
+                b2 = fminf(b2, distance2(k, q));
+            }
+            const float reach = valid ? __builtin_amdgcn_sqrtf(b2) + pc : 0.0f;
+            const float keep = -row_min(-reach) + marg;
+            int m = 0;
+            for (int k0 = 0; k0 < cnt; k0 += kRow) {
+                const int k = min(k0 + sub, cnt - 1);
+                const float4 s = ls.seg[k];
+                const float2 t = ls.inv[k];
+                const bool in = k0 + sub < cnt && ls.dc[k] <= keep;
+                const unsigned bits = row_ballot(in);
+                sync();
+                if (in) {
+                    const int pos = m + __popc(bits & ((1u << sub) - 1u));
+                    ls.seg[pos] = s;
+                    ls.inv[pos] = t;
+                }
+                m += __popc(bits);
+                sync();
+            }
+            const int padded = pad(m);
+            for (int k0 = 0; k0 < padded; k0 += 2) {
+#pragma unroll
+                for (int k = k0; k < k0 + 2; k++) {
+                    int q;
+                    const float d2 = distance2(k, q);
+                    bool less = d2 < best;
+                    // (exact ties are rare: the indices are read for them only)
+                    if (d2 == best && bq >= 0) less = e.eid[q] < e.eid[bq];
+                    best = less ? d2 : best;
+                    bq = less ? q : bq;
+                }
+            }
+            sync();
+            cnt = 0;
+        };
+        scan_edges(e, cx, cy, rf, sub, [&](int q, bool ok) {
+            const float4 s = e.es[ok ? q : 0];
+            const float ex = s.z - s.x, ey = s.w - s.y;
+            const float ir = seg_inv(ex, ey);
+            const float d = __builtin_amdgcn_sqrtf(seg_d2(s.x, s.y, ex, ey, ir, cx, cy));
+            const bool in = ok && d <= rf;
+            const unsigned bits = row_ballot(in);
+            if (cnt + kRow > kEdgeList) take();
+            if (in) {
+                const int pos = cnt + __popc(bits & ((1u << sub) - 1u));
+                ls.seg[pos] = make_float4(s.x, s.y, ex, ey);
+                ls.inv[pos] = make_float2(ir, __int_as_float(q));
+                ls.dc[pos] = d;
+            }
+            cnt += __popc(bits);
+        });
+        take();
+    }
+    // the bound for the next block: this block's point next to it
+    const float d = sqrtf(best);
+    const int qk = valid ? bq : -1;
+    bd.x = last_lane ? row_bcast<15>(px) : row_bcast<0>(px);
+    bd.y = last_lane ? row_bcast<15>(py) : row_bcast<0>(py);
+    bd.d = last_lane ? row_bcast<15>(d) : row_bcast<0>(d);
+    bd.q = __float_as_int(last_lane ? row_bcast<15>(__int_as_float(qk)) : row_bcast<0>(__int_as_float(qk)));
+    if (!valid || bq < 0 || !(d <= R)) return ch;
     ch.q = bq;
-    const float4 e = es[bq];
-    const float cr = (e.z - e.x) * (py - e.y) - (e.w - e.y) * (px - e.x);
+    const float4 s = e.es[bq];
+    const float cr = (s.z - s.x) * (py - s.y) - (s.w - s.y) * (px - s.x);
     ch.side = cr < 0.0f ? 1.0f : -1.0f;
     return ch;
 }
@@ -138,38 +419,10 @@ __device__ __forceinline__ float softplusf(float z) { return fmaxf(z, 0.0f) + lo
 // (the hardware reciprocal: 1 ulp, far inside the gradient tolerance)
 __device__ __forceinline__ float sigmoidf(float z) { return __builtin_amdgcn_rcpf(1.0f + expf(-z)); }
 
-// slip angle beta = atan(tan(steer) / 2) through its cosine and sine, cos beta =
-// 1 / sqrt(1 + z^2), sin beta = z cos beta (z = tan(steer) / 2), and the direction of
-// motion by angle addition: one tangent and one sincos per step instead of an arctangent,
-// a cosine and a sincos (the forward and the backward's recompute share this function)
-__device__ __forceinline__ void slip(float steer, float yaw, float &ts, float &cb, float &sb,
-                                     float &sp, float &cp) {
-    ts = tanf(steer);
-    const float z = 0.5f * ts;
-    cb = __builtin_amdgcn_rsqf(1.0f + z * z);
-    sb = z * cb;
-    float sy, cy;
-    sincosf(yaw, &sy, &cy);
-    sp = sy * cb + cy * sb;
-    cp = cy * cb - sy * sb;
-}
-
-__device__ __forceinline__ void bicycle_r(float &x, float &y, float &yaw, float &v, float L,
-                                          float acc, float steer, float dt, float vmax) {
-    float vb = fminf(fmaxf(v + 0.5f * acc * dt, -vmax), vmax);
-    float ts, cb, sb, sp, cp;
-    slip(steer, yaw, ts, cb, sb, sp, cp);
-    x = x + vb * cp * dt;
-    y = y + vb * sp * dt;
-    yaw = yaw + vb * cb * ts / L * dt;
-    v = fminf(fmaxf(v + acc * dt, -vmax), vmax);
-}
-
-// smooth reward at (x, y, yaw) for a fixed segment choice, computed through the ego frame
-__device__ __forceinline__ float smooth_reward(float x, float y, float yaw, float gx, float gy,
+// smooth reward at (x, y) and the heading's sine and cosine for a fixed segment choice,
+// computed through the ego frame
+__device__ __forceinline__ float smooth_reward(float x, float y, float st, float ct, float gx, float gy,
                                                const float4 *es, const EdgeChoice &ch, float R) {
-    float st, ct;
-    sincosf(yaw, &st, &ct);
     const float dxg = gx - x, dyg = gy - y;
     const float gpx = ct * dxg + st * dyg, gpy = -st * dxg + ct * dyg;
     const float ng = sqrtf(gpx * gpx + gpy * gpy);
@@ -200,46 +453,61 @@ __device__ __forceinline__ void world_of(const int *agent_off, int W, int i, int
     w = lo;
 }
 
+// The workgroup of tile number b: consecutive tiles (agents of one world, neighbours in the
+// rows of actions and rewards) go to one XCD and share its L2.  Workgroups are handed to the
+// 8 XCDs in turn.
+__device__ __forceinline__ int xcd_tile(int b, int nb) {
+    const int per = nb / 8, rest = nb % 8, x = b % 8, k = b / 8;
+    return x * per + min(x, rest) + k;
+}
+
+template <bool DELTA>
 __global__ __launch_bounds__(kRollThreads) void k_rollout_fwd(SimArgs a, const float2 *__restrict__ act,
                                                               int T, int C, float *__restrict__ rewards,
                                                               float *__restrict__ ckpt,
                                                               float *__restrict__ slog) {
-    // kGroup lanes per agent: the nearest-edge search is spread over them, the rest of
-    // the step is computed by all of them alike and written by the first
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = gid / kGroup, sub = gid % kGroup;
+    __shared__ float4 s_seg[kRollAgents * kEdgeStride];
+    __shared__ float2 s_inv[kRollAgents * kEdgeStride];
+    __shared__ float s_dc[kRollAgents * kEdgeStride];
+    const int row = threadIdx.x / kRow, sub = threadIdx.x % kRow;
+    const int i = xcd_tile(blockIdx.x, gridDim.x) * kRollAgents + row;
     if (i >= a.A) return;
-    int w;
-    world_of(a.agent_off, a.W, i, w);
-    const WorldGrid g = a.grid[w];
-    const int r0 = a.road_off[w];
-    const int *ecs = a.ecell_start + (size_t)w * kCellStride;
-    const float4 *es = a.eseg + r0;
-    const int *eid = a.eseg_id + r0;
-    float x = a.x[i], y = a.y[i], yaw = a.yaw[i], v = a.v[i];
-    const float L = a.len[i], gx = a.gx[i], gy = a.gy[i];
+    const EdgeList ls{s_seg + row * kEdgeStride, s_inv + row * kEdgeStride, s_dc + row * kEdgeStride};
     const size_t A = (size_t)a.A;
-    for (int t = 0; t < T; t++) {
-        if (t % C == 0 && sub == 0) {
+    const float2 none = make_float2(0.f, 0.f);
+    float2 next = sub < T ? act[(size_t)sub * A + i] : none;
+    AgentState c{a.x[i], a.y[i], a.yaw[i], a.v[i], 0.f, 0.f};
+    const float L = a.len[i], gx = a.gx[i], gy = a.gy[i];
+    const int w = world_of_row(a.agent_off, a.W, i, sub);
+    const int r0 = a.road_off[w];
+    const EdgeGrid e{a.grid[w], a.ecell_start + (size_t)w * kCellStride, a.eseg + r0, a.eseg_id + r0};
+    sincosf(c.yaw, &c.sn, &c.cs);
+    EdgeBound bd{0.f, 0.f, 0.f, -1};
+    for (int t0 = 0; t0 < T; t0 += kRow) {
+        const int n = min(kRow, T - t0), t = t0 + sub;
+        const bool on = sub < n;
+        const float2 u = next;
+        next = t + kRow < T ? act[(size_t)(t + kRow) * A + i] : none;
+        StepState o;
+        run_block<DELTA>(c, u, n, sub, L, a.dt, a.vmax, o);
+        c = after_block(o);
+        if (on && t % C == 0) {
             float *ck = ckpt + (size_t)(t / C) * 4 * A;
-            ck[i] = x;
-            ck[A + i] = y;
-            ck[2 * A + i] = yaw;
-            ck[3 * A + i] = v;
+            ck[i] = o.x0;
+            ck[A + i] = o.y0;
+            ck[2 * A + i] = o.yaw0;
+            ck[3 * A + i] = o.v0;
         }
-        const float2 u = act[(size_t)t * A + i];
-        if (a.dyn == GD_DYN_DELTA) delta_model(x, y, yaw, v, u.x, u.y, a.dt);
-        else bicycle_r(x, y, yaw, v, L, u.x, u.y, a.dt, a.vmax);
-        const EdgeChoice ch = nearest_edge_group(g, ecs, es, eid, x, y, a.R_obs, sub);
-        const float rw = smooth_reward(x, y, yaw, gx, gy, es, ch, a.R_obs);
-        if (sub == 0) {
+        const EdgeChoice ch = nearest_edges(e, ls, o.x1, o.y1, on, a.R_obs, sub, bd, true);
+        const float rw = smooth_reward(o.x1, o.y1, o.sn1, o.cs1, gx, gy, e.es, ch, a.R_obs);
+        if (on) {
             rewards[(size_t)t * A + i] = rw;
             if (slog) {
                 float *sl = slog + (size_t)t * 4 * A;
-                sl[i] = x;
-                sl[A + i] = y;
-                sl[2 * A + i] = yaw;
-                sl[3 * A + i] = v;
+                sl[i] = o.x1;
+                sl[A + i] = o.y1;
+                sl[2 * A + i] = o.yaw1;
+                sl[3 * A + i] = o.v1;
             }
         }
     }
@@ -293,6 +561,7 @@ __global__ __launch_bounds__(kObsThreads) void k_rollout_obs(SimArgs a, const fl
     }
 }
 
+template <bool DELTA, bool OBS>
 __global__ __launch_bounds__(kRollThreads) void k_rollout_bwd(SimArgs a, const float2 *__restrict__ act,
                                                               const float *__restrict__ ckpt, int T, int C,
                                                               const float *__restrict__ grad_r,
@@ -300,204 +569,210 @@ __global__ __launch_bounds__(kRollThreads) void k_rollout_bwd(SimArgs a, const f
                                                               const float *__restrict__ slog,
                                                               float2 *__restrict__ grad_a,
                                                               float *__restrict__ grad_s0) {
-    // per thread: states before steps c0..c0+C (C+1 entries) and the segment choice of the
-    // reward after each of the C steps
-    // (kGroup lanes per agent as in the forward kernel; the per-agent LDS records are
-    // written by the group's first lane and read by all of them)
-    __shared__ float4 s_state[kRollAgents * (kMaxCkpt + 1)];
-    __shared__ int s_q[kRollAgents * kMaxCkpt];
-    __shared__ float s_side[kRollAgents * kMaxCkpt];
-    const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = gid / kGroup, sub = gid % kGroup;
+    __shared__ float4 s_seg[kRollAgents * kEdgeStride];
+    __shared__ float2 s_inv[kRollAgents * kEdgeStride];
+    __shared__ float s_dc[kRollAgents * kEdgeStride];
+    const int row = threadIdx.x / kRow, sub = threadIdx.x % kRow;
+    const int i = xcd_tile(blockIdx.x, gridDim.x) * kRollAgents + row;
     if (i >= a.A) return;
-    const int la = threadIdx.x / kGroup;
-    float4 *st = s_state + la * (kMaxCkpt + 1);
-    int *sq = s_q + la * kMaxCkpt;
-    float *ss = s_side + la * kMaxCkpt;
-    int w;
-    world_of(a.agent_off, a.W, i, w);
-    const WorldGrid g = a.grid[w];
-    const int r0 = a.road_off[w];
-    const int *ecs = a.ecell_start + (size_t)w * kCellStride;
-    const float4 *es = a.eseg + r0;
-    const int *eid = a.eseg_id + r0;
+    const EdgeList ls{s_seg + row * kEdgeStride, s_inv + row * kEdgeStride, s_dc + row * kEdgeStride};
+    const size_t A = (size_t)a.A;
     const float L = a.len[i], gxa = a.gx[i], gya = a.gy[i];
     const float iL = 1.0f / L;  // once per agent: the adjoint's divisions by L become products
     const float dt = a.dt, vmax = a.vmax;
-    const size_t A = (size_t)a.A;
-    const int a0 = a.agent_off[w], n = a.agent_off[w + 1] - a0, l = i - a0;
+    const int w = world_of_row(a.agent_off, a.W, i, sub);
+    const int r0 = a.road_off[w];
+    const EdgeGrid e{a.grid[w], a.ecell_start + (size_t)w * kCellStride, a.eseg + r0, a.eseg_id + r0};
+    const int a0 = a.agent_off[w], nw = a.agent_off[w + 1] - a0, l = i - a0;
     const int P = a.P, F = 3 + 4 * P;
     float lx = 0.f, ly = 0.f, lth = 0.f, lv = 0.f;  // adjoint of the state after the current step
-    const int nseg = (T + C - 1) / C;
-    for (int sgi = nseg - 1; sgi >= 0; sgi--) {
-        const int c0 = sgi * C;
-        const int c1 = min(T, c0 + C);
-        // recompute the segment forward
-        const float *ck = ckpt + (size_t)sgi * 4 * A;
-        float x = ck[i], y = ck[A + i], yaw = ck[2 * A + i], v = ck[3 * A + i];
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (sub == 0) st[0] = make_float4(x, y, yaw, v);
-        for (int t = c0; t < c1; t++) {
-            const float2 u = act[(size_t)t * A + i];
-            if (a.dyn == GD_DYN_DELTA) delta_model(x, y, yaw, v, u.x, u.y, dt);
-            else bicycle_r(x, y, yaw, v, L, u.x, u.y, dt, vmax);
-            const EdgeChoice ch = nearest_edge_group(g, ecs, es, eid, x, y, a.R_obs, sub);
-            if (sub == 0) {
-                st[t - c0 + 1] = make_float4(x, y, yaw, v);
-                sq[t - c0] = ch.q;
-                ss[t - c0] = ch.side;
+    EdgeBound bd{0.f, 0.f, 0.f, -1};
+    // blocks of whole checkpoint segments, as many as fit 16 steps (or 16 steps of a longer
+    // segment), last block first
+    const int B = C <= kRow ? kRow / C * C : C;
+    for (int c0 = (T - 1) / B * B; c0 >= 0; c0 -= B) {
+        const int c1 = min(T, c0 + B);
+        const float *ck = ckpt + (size_t)(c0 / C) * 4 * A;
+        for (int t0 = c0 + (c1 - 1 - c0) / kRow * kRow; t0 >= c0; t0 -= kRow) {
+            const int n = min(kRow, c1 - t0), t = t0 + sub;
+            const bool on = sub < n;
+            const float gr = on ? grad_r[(size_t)t * A + i] : 0.0f;
+            // states of the block, from the checkpoint (through the steps before the block)
+            AgentState c{ck[i], ck[A + i], ck[2 * A + i], ck[3 * A + i], 0.f, 0.f};
+            sincosf(c.yaw, &c.sn, &c.cs);
+            StepState o;
+            float2 u;
+            for (int tb = c0;; tb += kRow) {
+                u = tb + sub < c1 ? act[(size_t)(tb + sub) * A + i] : make_float2(0.f, 0.f);
+                run_block<DELTA>(c, u, tb < t0 ? kRow : n, sub, L, dt, vmax, o);
+                if (tb == t0) break;
+                c = after_block(o);
             }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        // reverse
-        for (int t = c1 - 1; t >= c0; t--) {
-            const float gr = grad_r[(size_t)t * A + i];
-            const float4 s1 = st[t - c0 + 1];
-            float sn, cs;
-            sincosf(s1.z, &sn, &cs);
-            if (grad_obs) {
-                // observation terms of step t, from the state log (the states the
-                // observation was formed from, so that the partner masks agree with it)
+            const EdgeChoice ch = nearest_edges(e, ls, o.x1, o.y1, on, a.R_obs, sub, bd, false);
+            // gradient of the step's reward (and observation) with respect to the state after
+            // the step
+            float gx = 0.f, gy = 0.f, gth = 0.f, gv = 0.f;
+            const float sn = o.sn1, cs = o.cs1;
+            if (OBS && on) {
+                // observation terms, from the state log (the states the observation was
+                // formed from, so that the partner masks agree with it)
                 const float *S = slog + (size_t)t * 4 * A;
                 const float *go = grad_obs + ((size_t)t * A + i) * F;
                 const float xi = S[i], yi = S[A + i];
                 float oth, octh;
                 sincosf(S[2 * A + i], &oth, &octh);
-                float dx_ = 0.f, dy_ = 0.f, dth_ = 0.f, dv_ = 0.f;
-                if (sub == 0) {
-                    // own speed and goal in the own frame, g' = R(-yaw)(g - p)
-                    dv_ += go[0];
+                // own speed and goal in the own frame, g' = R(-yaw)(g - p)
+                gv += go[0];
+                {
                     const float dxg = gxa - xi, dyg = gya - yi;
                     const float gpx = octh * dxg + oth * dyg, gpy = -oth * dxg + octh * dyg;
-                    dx_ += -octh * go[1] + oth * go[2];
-                    dy_ += -oth * go[1] - octh * go[2];
-                    dth_ += gpy * go[1] - gpx * go[2];
+                    gx += -octh * go[1] + oth * go[2];
+                    gy += -oth * go[1] - octh * go[2];
+                    gth += gpy * go[1] - gpx * go[2];
                 }
                 // own partner slots: f = R(-yaw_i)(p_j - p_i), wrap(yaw_j - yaw_i)
-                for (int sl = sub; sl < P; sl += kGroup) {
-                    const int j = sl < l ? sl : sl + 1;
-                    if (j >= n) continue;
-                    const int jj = a0 + j;
+                for (int sl = 0; sl < min(P, nw - 1); sl++) {
+                    const int jj = a0 + (sl < l ? sl : sl + 1);
                     const float xj = S[jj], yj = S[A + jj];
                     if (!(key32(xi, yi, xj, yj) <= a.R2_obs)) continue;
                     const float dx = xj - xi, dy = yj - yi;
                     const float fx = octh * dx + oth * dy, fy = -oth * dx + octh * dy;
-                    const float bx = go[3 + 4 * sl], by = go[4 + 4 * sl], bd = go[5 + 4 * sl];
-                    dx_ -= octh * bx - oth * by;
-                    dy_ -= oth * bx + octh * by;
-                    dth_ += bx * fy - by * fx - bd;
+                    const float bx = go[3 + 4 * sl], by = go[4 + 4 * sl], bdh = go[5 + 4 * sl];
+                    gx -= octh * bx - oth * by;
+                    gy -= oth * bx + octh * by;
+                    gth += bx * fy - by * fx - bdh;
                 }
                 // the slot of agent i in every other agent's observation
-                for (int m = sub; m < n; m += kGroup) {
-                    if (m == l) continue;
+                for (int m = 0; m < nw; m++) {
                     const int sl = l < m ? l : l - 1;
-                    if (sl >= P) continue;
+                    if (m == l || sl >= P) continue;
                     const int mm = a0 + m;
                     const float xm = S[mm], ym = S[A + mm];
                     if (!(key32(xm, ym, xi, yi) <= a.R2_obs)) continue;
                     float sm, cm;
                     sincosf(S[2 * A + mm], &sm, &cm);
                     const float *gm = grad_obs + ((size_t)t * A + mm) * F + 3 + 4 * sl;
-                    dx_ += cm * gm[0] - sm * gm[1];
-                    dy_ += sm * gm[0] + cm * gm[1];
-                    dth_ += gm[2];
-                    dv_ += gm[3];
+                    gx += cm * gm[0] - sm * gm[1];
+                    gy += sm * gm[0] + cm * gm[1];
+                    gth += gm[2];
+                    gv += gm[3];
                 }
-                lx += group_sum(dx_);
-                ly += group_sum(dy_);
-                lth += group_sum(dth_);
-                lv += group_sum(dv_);
             }
             // goal term: r = -|g'|
             {
-                const float dxg = gxa - s1.x, dyg = gya - s1.y;
+                const float dxg = gxa - o.x1, dyg = gya - o.y1;
                 const float gpx = cs * dxg + sn * dyg, gpy = -sn * dxg + cs * dyg;
                 const float ng = sqrtf(gpx * gpx + gpy * gpy);
                 if (ng > 0.0f) {
                     const float ing = __builtin_amdgcn_rcpf(ng);
                     const float bgx = -gpx * ing * gr, bgy = -gpy * ing * gr;
-                    lx += -cs * bgx + sn * bgy;
-                    ly += -sn * bgx - cs * bgy;
-                    lth += gpy * bgx - gpx * bgy;
+                    gx += -cs * bgx + sn * bgy;
+                    gy += -sn * bgx - cs * bgy;
+                    gth += gpy * bgx - gpx * bgy;
                 }
             }
             // off-road term: r = -softplus(side * |q'|), q' = a' + u e' in the ego frame
-            const int q = sq[t - c0];
-            if (q >= 0) {
-                const float side = ss[t - c0];
-                const float4 e = es[q];
-                const float ax = e.x - s1.x, ay = e.y - s1.y, bx = e.z - s1.x, by = e.w - s1.y;
+            if (ch.q >= 0) {
+                const float4 s = e.es[ch.q];
+                const float ax = s.x - o.x1, ay = s.y - o.y1, bx = s.z - o.x1, by = s.w - o.y1;
                 const float apx = cs * ax + sn * ay, apy = -sn * ax + cs * ay;
                 const float bpx = cs * bx + sn * by, bpy = -sn * bx + cs * by;
                 const float ex = bpx - apx, ey = bpy - apy;
                 const float ee = ex * ex + ey * ey;
                 const float iee = __builtin_amdgcn_rcpf(ee);
-                float u = ee > 0.0f ? -(apx * ex + apy * ey) * iee : 0.0f;
-                const bool cl = u <= 0.0f || u >= 1.0f;
-                u = fminf(fmaxf(u, 0.0f), 1.0f);
-                const float qx = apx + u * ex, qy = apy + u * ey;
+                float uu = ee > 0.0f ? -(apx * ex + apy * ey) * iee : 0.0f;
+                const bool cl = uu <= 0.0f || uu >= 1.0f;
+                uu = fminf(fmaxf(uu, 0.0f), 1.0f);
+                const float qx = apx + uu * ex, qy = apy + uu * ey;
                 const float d = sqrtf(qx * qx + qy * qy);
-                const float sdist = side * d;
+                const float sdist = ch.side * d;
                 const float sbar = -sigmoidf(sdist) * gr;
-                const float dbar = side * sbar;
+                const float dbar = ch.side * sbar;
                 float bqx = 0.f, bqy = 0.f;
                 if (d > 0.0f) {
                     const float id = __builtin_amdgcn_rcpf(d);
                     bqx = dbar * qx * id;
                     bqy = dbar * qy * id;
                 }
-                float bapx = bqx, bapy = bqy, bex = u * bqx, bey = u * bqy;
+                float bapx = bqx, bapy = bqy, bex = uu * bqx, bey = uu * bqy;
                 if (!cl && ee > 0.0f) {
                     const float ubar = bqx * ex + bqy * ey;
                     bapx += ubar * (-ex * iee);
                     bapy += ubar * (-ey * iee);
-                    bex += ubar * (-apx * iee - 2.0f * u * ex * iee);
-                    bey += ubar * (-apy * iee - 2.0f * u * ey * iee);
+                    bex += ubar * (-apx * iee - 2.0f * uu * ex * iee);
+                    bey += ubar * (-apy * iee - 2.0f * uu * ey * iee);
                 }
                 const float bbpx = bex, bbpy = bey;
                 bapx -= bex;
                 bapy -= bey;
                 const float bax = cs * bapx - sn * bapy, bay = sn * bapx + cs * bapy;
                 const float bbx = cs * bbpx - sn * bbpy, bby = sn * bbpx + cs * bbpy;
-                lx += -(bax + bbx);
-                ly += -(bay + bby);
-                lth += bapx * apy - bapy * apx + bbpx * bpy - bbpy * bpx;
+                gx += -(bax + bbx);
+                gy += -(bay + bby);
+                gth += bapx * apy - bapy * apx + bbpx * bpy - bbpy * bpx;
             }
-            // dynamics s_t -> s_{t+1}
-            const float4 s0 = st[t - c0];
-            const float2 u = act[(size_t)t * A + i];
-            if (a.dyn == GD_DYN_DELTA) {
+            // dynamics s_t -> s_{t+1}: coefficients of the adjoint's recursion
+            //   lth <- lth + m1 lx + m2 ly,  lv <- n1 lx + n2 ly + n3 lth + n4 lv
+            float m1 = 0.f, m2 = 0.f, n1 = 0.f, n2 = 0.f, n3 = 0.f, n4 = 1.f;
+            float c1f = 0.f, c2f = 0.f;
+            if (DELTA) {
                 // d = v dt + a dt^2/2; x += d cos(yaw); y += d sin(yaw); yaw += s d; v += a dt
-                const float d = s0.w * dt + 0.5f * u.x * dt * dt;
-                float sn0, cs0;
-                sincosf(s0.z, &sn0, &cs0);
-                const float bd = lx * cs0 + ly * sn0 + lth * u.y;
-                if (sub == 0) grad_a[(size_t)t * A + i] = make_float2(lv * dt + bd * 0.5f * dt * dt, lth * d);
-                lth = lth + d * (ly * cs0 - lx * sn0);
-                lv = lv + bd * dt;
-                continue;
+                m1 = -o.vb * o.sn0;
+                m2 = o.vb * o.cs0;
+                n1 = o.cs0 * dt;
+                n2 = o.sn0 * dt;
+                n3 = u.y * dt;
+            } else {
+                const float vb_raw = o.v0 + 0.5f * u.x * dt, vn_raw = o.v0 + u.x * dt;
+                c1f = (vb_raw > -vmax && vb_raw < vmax) ? 1.0f : 0.0f;
+                c2f = (vn_raw > -vmax && vn_raw < vmax) ? 1.0f : 0.0f;
+                m1 = -o.vb * o.sp * dt;
+                m2 = o.vb * o.cp * dt;
+                n1 = c1f * (o.cp * dt);
+                n2 = c1f * (o.sp * dt);
+                n3 = c1f * (o.cb * o.ts * iL * dt);
+                n4 = c2f;
             }
-            const float vb_raw = s0.w + 0.5f * u.x * dt;
-            const float vb = fminf(fmaxf(vb_raw, -vmax), vmax);
-            const float c1f = (vb_raw > -vmax && vb_raw < vmax) ? 1.0f : 0.0f;
-            const float vn_raw = s0.w + u.x * dt;
-            const float c2f = (vn_raw > -vmax && vn_raw < vmax) ? 1.0f : 0.0f;
-            float tdl, cb, sbt, sp, cp;
-            slip(u.y, s0.z, tdl, cb, sbt, sp, cp);
-            const float sec2 = 1.0f + tdl * tdl;
-            const float dbeta = 0.5f * sec2 * __builtin_amdgcn_rcpf(1.0f + 0.25f * tdl * tdl);
-            const float bvb = lx * cp * dt + ly * sp * dt + lth * cb * tdl * iL * dt;
-            const float bphi = -lx * vb * sp * dt + ly * vb * cp * dt;
-            const float bth = lth + bphi;
-            const float bbeta = bphi - lth * vb * sbt * tdl * iL * dt;
-            const float bdl = lth * vb * cb * sec2 * iL * dt + bbeta * dbeta;
-            const float bv = bvb * c1f + lv * c2f;
-            const float ba = bvb * c1f * 0.5f * dt + lv * c2f * dt;
-            if (sub == 0) grad_a[(size_t)t * A + i] = make_float2(ba, bdl);
-            lth = bth;
-            lv = bv;
+            if (!on) {
+                gx = gy = gth = gv = 0.f;
+                m1 = m2 = n1 = n2 = n3 = 0.f;
+                n4 = 1.f;
+            }
+            // the recursion, last step first, on all lanes of the row; a lane keeps the adjoint
+            // of the state after its step
+            float kx = 0.f, ky = 0.f, kth = 0.f, kv = 0.f;
+            each_step_down(n, [&](auto kc) {
+                constexpr int k = decltype(kc)::k;
+                lx += row_bcast<k>(gx);
+                ly += row_bcast<k>(gy);
+                lth += row_bcast<k>(gth);
+                if (OBS) lv += row_bcast<k>(gv);
+                const bool me = sub == k;
+                kx = me ? lx : kx;
+                ky = me ? ly : ky;
+                kth = me ? lth : kth;
+                kv = me ? lv : kv;
+                const float v = row_bcast<k>(n4) * lv;
+                lv = row_bcast<k>(n1) * lx + v;
+                lv = row_bcast<k>(n2) * ly + lv;
+                lv = row_bcast<k>(n3) * lth + lv;
+                lth = row_bcast<k>(m1) * lx + lth;
+                lth = row_bcast<k>(m2) * ly + lth;
+            });
+            // gradient of the step's action
+            float2 ga;
+            if (DELTA) {
+                const float bdist = kx * o.cs0 + ky * o.sn0 + kth * u.y;
+                ga = make_float2(kv * dt + bdist * 0.5f * dt * dt, kth * o.vb);
+            } else {
+                const float sec2 = 1.0f + o.ts * o.ts;
+                const float dbeta = 0.5f * sec2 * __builtin_amdgcn_rcpf(1.0f + 0.25f * o.ts * o.ts);
+                const float bvb = kx * o.cp * dt + ky * o.sp * dt + kth * o.cb * o.ts * iL * dt;
+                const float bphi = -kx * o.vb * o.sp * dt + ky * o.vb * o.cp * dt;
+                const float bbeta = bphi - kth * o.vb * o.sb * o.ts * iL * dt;
+                ga = make_float2(bvb * c1f * 0.5f * dt + kv * c2f * dt, kth * o.vb * o.cb * sec2 * iL * dt + bbeta * dbeta);
+            }
+            if (on) grad_a[(size_t)t * A + i] = ga;
         }
     }
     if (grad_s0 && sub == 0) {
@@ -580,12 +855,14 @@ hipError_t launch_invert_actions_impl(const float *states, int T, int A, float d
     return hipGetLastError();
 }
 
+// workgroups of the rollout kernels: 16 agents each
+static unsigned roll_blocks(int A) { return (unsigned)(((long long)A + kRollAgents - 1) / kRollAgents); }
+
 hipError_t launch_rollout_fwd_impl(const SimArgs &a, const float2 *actions, int T, int C,
                                    float *rewards, float *ckpt, float *states, hipStream_t s) {
     if (C < 1 || C > kMaxCkpt) return hipErrorInvalidValue;
-    const int blocks = (int)(((long long)a.A * kGroup + kRollThreads - 1) / kRollThreads);
-    hipLaunchKernelGGL(k_rollout_fwd, dim3(blocks), dim3(kRollThreads), 0, s, a, actions, T, C, rewards, ckpt,
-                       states);
+    auto k = a.dyn == GD_DYN_DELTA ? k_rollout_fwd<true> : k_rollout_fwd<false>;
+    hipLaunchKernelGGL(k, dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a, actions, T, C, rewards, ckpt, states);
     return hipGetLastError();
 }
 
@@ -602,9 +879,11 @@ hipError_t launch_rollout_bwd_impl(const SimArgs &a, const float2 *actions, cons
                                    const float *states, float2 *grad_actions, float *grad_state0,
                                    hipStream_t s) {
     if (C < 1 || C > kMaxCkpt) return hipErrorInvalidValue;
-    const int blocks = (int)(((long long)a.A * kGroup + kRollThreads - 1) / kRollThreads);
-    hipLaunchKernelGGL(k_rollout_bwd, dim3(blocks), dim3(kRollThreads), 0, s, a, actions, ckpt, T, C,
-                       grad_rewards, grad_obs, states, grad_actions, grad_state0);
+    const bool delta = a.dyn == GD_DYN_DELTA;
+    auto k = grad_obs ? (delta ? k_rollout_bwd<true, true> : k_rollout_bwd<false, true>)
+                      : (delta ? k_rollout_bwd<true, false> : k_rollout_bwd<false, false>);
+    hipLaunchKernelGGL(k, dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a, actions, ckpt, T, C, grad_rewards,
+                       grad_obs, states, grad_actions, grad_state0);
     return hipGetLastError();
 }
 
