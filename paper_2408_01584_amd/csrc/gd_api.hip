@@ -19,11 +19,12 @@ namespace gdk {
 hipError_t launch_lidar_impl(const SimArgs &a, const LidarCtl &lc, hipStream_t s);
 hipError_t launch_rollout_fwd_impl(const SimArgs &a, const float2 *actions, int T, int C,
                                    float *rewards, float *ckpt, float *states, hipStream_t s);
-hipError_t launch_rollout_obs_impl(const SimArgs &a, const float *states, int T, float *obs, hipStream_t s);
+hipError_t launch_rollout_obs_impl(const SimArgs &a, const float *states, int T, int max_agents, float *obs,
+                                   hipStream_t s);
 hipError_t launch_rollout_bwd_impl(const SimArgs &a, const float2 *actions, const float *ckpt,
                                    int T, int C, const float *grad_rewards, const float *grad_obs,
-                                   const float *states, float2 *grad_actions, float *grad_state0,
-                                   hipStream_t s);
+                                   const float *states, int max_agents, float2 *grad_actions,
+                                   float *grad_state0, hipStream_t s);
 hipError_t launch_invert_actions_impl(const float *states, int T, int A, float dt, float *actions,
                                       hipStream_t s);
 constexpr int kMaxInvertSteps = 65535 * 16;  // launch chunks of 16 steps on grid axis y
@@ -35,7 +36,7 @@ bool lidar_kernel_node(const SimArgs *a, const LidarCtl *lc, hipKernelNodeParams
 
 static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
-Layout make_layout(int W, long long A, long long R) {
+Layout make_layout(int W, long long A, long long R, int partners) {
     Layout L{};
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -55,6 +56,8 @@ Layout make_layout(int W, long long A, long long R) {
     L.pbase = take(sizeof(long long) * (size_t)W);
     L.err = take(256);
     L.order = take(sizeof(int) * (size_t)W);
+    L.obs_grad = take(partners >= 0 ? sizeof(float4) * (size_t)A * obs_grad_steps(A) : 0);
+    L.carry = take(partners >= 0 ? sizeof(float4) * (size_t)A : 0);
     L.total = off;
     return L;
 }
@@ -364,7 +367,7 @@ gd_status gd_workspace_size(const gd_config *cfg, const int32_t *h_agent_off,
     if (st != GD_OK) return st;
     if (!bytes) return fail(GD_E_ARG, "bytes is NULL");
     const int W = cfg->num_worlds;
-    *bytes = make_layout(W, h_agent_off[W], h_road_off[W]).total;
+    *bytes = make_layout(W, h_agent_off[W], h_road_off[W], cfg->partners).total;
     return GD_OK;
 }
 
@@ -393,7 +396,7 @@ gd_status gd_create(const gd_config *cfg, const int32_t *h_agent_off, const int3
     if (cfg->lidar_rays > 0 && A > 0 && (!b->lidar || !b->lidar_hit))
         return fail(GD_E_ARG, "lidar buffers are NULL");
     if (((uintptr_t)b->workspace) & 255) return fail(GD_E_ARG, "workspace must be 256-byte aligned");
-    Layout L = make_layout(W, A, R);
+    Layout L = make_layout(W, A, R, cfg->partners);
     if (b->workspace_bytes < L.total)
         return fail(GD_E_SIZE, "workspace too small: %zu bytes, need %zu", b->workspace_bytes, L.total);
     int max_road = 0, max_agents = 0;
@@ -492,6 +495,8 @@ gd_status gd_create(const gd_config *cfg, const int32_t *h_agent_off, const int3
     a.kth = (float *)(ws + L.kth);
     a.pbase = (long long *)(ws + L.pbase);
     a.err = (unsigned *)(ws + L.err);
+    a.obs_grad = (float4 *)(ws + L.obs_grad);
+    a.carry = (float4 *)(ws + L.carry);
     sim->ctl.order = (const int *)(ws + L.order);
     sim->ctl.agent_cap = (std::max(max_agents, 1) + 3) / 4 * 4;  // as in launch_shape
 
@@ -633,7 +638,7 @@ gd_status gd_rollout_fwd(gd_sim *sim, const float *actions, int32_t T, int32_t c
     TIMED(sim, s, GD_PHASE_ROLLOUT_FWD,
           launch_rollout_fwd_impl(sim->args, (const float2 *)actions, T, ckpt_every, rewards, ckpt, states, s),
           "rollout forward launch");
-    if (obs) HIP_TRY(launch_rollout_obs_impl(sim->args, states, T, obs, s), "rollout observation launch");
+    if (obs) HIP_TRY(launch_rollout_obs_impl(sim->args, states, T, sim->max_agents, obs, s), "rollout observation launch");
     return GD_OK;
 }
 
@@ -651,7 +656,8 @@ gd_status gd_rollout_bwd(gd_sim *sim, const float *actions, const float *ckpt, i
     hipStream_t s = (hipStream_t)stream;
     TIMED(sim, s, GD_PHASE_ROLLOUT_BWD,
           launch_rollout_bwd_impl(sim->args, (const float2 *)actions, ckpt, T, ckpt_every, grad_rewards,
-                                  grad_obs, grad_obs ? states : nullptr, (float2 *)grad_actions, grad_state0, s),
+                                  grad_obs, grad_obs ? states : nullptr, sim->max_agents, (float2 *)grad_actions,
+                                  grad_state0, s),
           "rollout backward launch");
     return GD_OK;
 }

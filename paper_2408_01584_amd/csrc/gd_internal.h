@@ -68,6 +68,8 @@ struct SimArgs {
                        // observation, R^2 when it had fewer than K in the radius
     long long *pbase;  // [W] first partner slot of each world
     unsigned *err;     // device error word
+    float4 *obs_grad;  // [obs_grad_steps(A), A] rollout backward: the observation's gradient
+    float4 *carry;     // [A] rollout backward: adjoint between parts
 };
 
 enum StepMode { kModeStep = 0, kModeObs = 1, kModeReset = 2 };
@@ -104,9 +106,17 @@ size_t lidar_lds_bytes(int N, const LidarCtl &lc);
 // Workspace layout (byte offsets, each 256-aligned).
 struct Layout {
     size_t grid, cell_start, pt_xy, pt_aux, ecell_start, eseg, eseg_id, snap, kth, pbase, err, order,
-        total;
+        obs_grad, carry, total;
 };
-Layout make_layout(int W, long long A, long long R);
+// partners: the configured slots (a rollout's observation needs a fixed number)
+Layout make_layout(int W, long long A, long long R, int partners);
+
+// Steps of a rollout whose observation gradient (16 B per agent and step) the workspace holds:
+// 64 MB of it, at least 32 steps (the longest backward block) and at most 128.
+__host__ __device__ inline int obs_grad_steps(long long A) {
+    const long long s = A > 0 ? ((64ll << 20) / 16) / A : 128;
+    return s < 32 ? 32 : s > 128 ? 128 : (int)s;
+}
 
 // Workspace of the polyline decimation: areas (f32), then predecessor and successor links
 // (i32) of every point, each region 256-byte aligned; part 3 is the total.

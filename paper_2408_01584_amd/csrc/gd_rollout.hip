@@ -28,6 +28,8 @@
 // Fig. 1, Sec. 3.2 "Sensor modalities").  Partners couple the agents of a world, so the
 // backward reads the other agents' states from that log: at each step an agent's adjoint
 // gathers the terms of its own observation and of every observation it appears in.
+#include <algorithm>
+
 #include "gd_internal.h"
 
 namespace gdk {
@@ -443,16 +445,6 @@ __device__ __forceinline__ float smooth_reward(float x, float y, float st, float
     return -ng - softplusf(s);
 }
 
-__device__ __forceinline__ void world_of(const int *agent_off, int W, int i, int &w) {
-    int lo = 0, hi = W - 1;  // largest w with agent_off[w] <= i
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (agent_off[mid] <= i) lo = mid;
-        else hi = mid - 1;
-    }
-    w = lo;
-}
-
 // The workgroup of tile number b: consecutive tiles (agents of one world, neighbours in the
 // rows of actions and rewards) go to one XCD and share its L2.  Workgroups are handed to the
 // 8 XCDs in turn.
@@ -461,8 +453,9 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
     return x * per + min(x, rest) + k;
 }
 
+// (four waves per SIMD: 128 registers; one more register costs a quarter of the waves)
 template <bool DELTA>
-__global__ __launch_bounds__(kRollThreads) void k_rollout_fwd(SimArgs a, const float2 *__restrict__ act,
+__global__ __launch_bounds__(kRollThreads, 4) void k_rollout_fwd(SimArgs a, const float2 *__restrict__ act,
                                                               int T, int C, float *__restrict__ rewards,
                                                               float *__restrict__ ckpt,
                                                               float *__restrict__ slog) {
@@ -513,60 +506,210 @@ __global__ __launch_bounds__(kRollThreads) void k_rollout_fwd(SimArgs a, const f
     }
 }
 
+// Four floats of an observation row (a partner slot; rows start at any multiple of 4 bytes).
+struct __attribute__((packed, aligned(4))) Slot4 {
+    float x, y, z, w;
+};
+
+constexpr int kObsThreads = 256;
+
 // Observation of the rollout from its state log slog [T, 4, A] (the state after each
 // step): obs [T, A, 3 + 4P] = (speed, goal x', goal y') then, per partner slot s (the
 // s-th other agent of the world in index order), (x', y', wrap(yaw_j - yaw), v_j) when
-// the partner lies within the radius (binary32 key, inclusive), zeros otherwise.  One wave
-// per (step, agent), a lane per feature.
-constexpr int kObsThreads = 256;
-__global__ __launch_bounds__(kObsThreads) void k_rollout_obs(SimArgs a, const float *__restrict__ slog,
-                                                             int T, float *__restrict__ obs) {
-    const long long item = (long long)blockIdx.x * (kObsThreads / kWave) + threadIdx.x / kWave;
-    const int lane = threadIdx.x & (kWave - 1);
+// the partner lies within the radius (binary32 key, inclusive), zeros otherwise.
+// Bound by its writes.  One workgroup per world and `steps` of the rollout's steps, whose
+// states are staged in LDS with their sines and cosines; then `lpr` lanes (a power of two)
+// per agent, a partner slot per lane, 16 bytes stored at a time.  A wave per agent-step with a
+// lane per feature looked up the world and took a sine and cosine for each agent-step:
+// 512 x 32 agents, T = 20 (166 MB): 192 us against 30 us now (5.6 TB/s).
+__global__ __launch_bounds__(kObsThreads) void k_rollout_obs(SimArgs a, const float *__restrict__ slog, int tb,
+                                                             int T, int steps, int lpr, float *__restrict__ obs) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int w = blockIdx.x;
+    const int a0 = a.agent_off[w], n = a.agent_off[w + 1] - a0;
+    const int t0 = tb + (int)blockIdx.y * steps, m = min(steps, T - t0);
+    float4 *pose = reinterpret_cast<float4 *>(smem);  // x, y, yaw, speed of the steps' agents
     const size_t A = (size_t)a.A;
-    if (item >= (long long)T * (long long)A) return;
-    const int t = (int)(item / (long long)A), i = (int)(item % (long long)A);
-    int w;
-    world_of(a.agent_off, a.W, i, w);
-    const int a0 = a.agent_off[w], n = a.agent_off[w + 1] - a0, l = i - a0;
-    const int P = a.P, F = 3 + 4 * P;
-    const float *S = slog + (size_t)t * 4 * A;
-    const float x = S[i], y = S[A + i], yaw = S[2 * A + i];
-    float sn, cs;
-    sincosf(yaw, &sn, &cs);
-    float *o = obs + ((size_t)t * A + i) * F;
-    for (int f = lane; f < F; f += kWave) {
-        float val = 0.0f;
-        if (f == 0) {
-            val = S[3 * A + i];
-        } else if (f < 3) {
-            const float dxg = a.gx[i] - x, dyg = a.gy[i] - y;
-            val = f == 1 ? cs * dxg + sn * dyg : -sn * dxg + cs * dyg;
-        } else {
-            const int sl = (f - 3) >> 2, k = (f - 3) & 3;
-            const int j = sl < l ? sl : sl + 1;
-            if (j < n) {
-                const int jj = a0 + j;
-                const float xj = S[jj], yj = S[A + jj];
-                if (key32(x, y, xj, yj) <= a.R2_obs) {
-                    const float dx = xj - x, dy = yj - y;
-                    val = k == 0 ? cs * dx + sn * dy
-                        : k == 1 ? -sn * dx + cs * dy
-                        : k == 2 ? wrap_pi(S[2 * A + jj] - yaw)
-                                 : S[3 * A + jj];
-                }
+    const int P = a.P;
+    const size_t F = 3 + 4 * (size_t)P;
+    float2 *turn = reinterpret_cast<float2 *>(pose + (size_t)m * n);  // sine, cosine
+    for (int k = threadIdx.x; k < m * n; k += kObsThreads) {
+        const int tl = k / n, i = k - tl * n;
+        const float *S = slog + (size_t)(t0 + tl) * 4 * A + a0 + i;
+        const float x = S[0], y = S[A], yaw = S[2 * A], v = S[3 * A];
+        const float gx = a.gx[a0 + i], gy = a.gy[a0 + i];
+        float sn, cs;
+        sincosf(yaw, &sn, &cs);
+        pose[k] = make_float4(x, y, yaw, v);
+        turn[k] = make_float2(sn, cs);
+        const float dxg = gx - x, dyg = gy - y;
+        float *o = obs + ((size_t)(t0 + tl) * A + a0 + i) * F;
+        o[0] = v;
+        o[1] = cs * dxg + sn * dyg;
+        o[2] = -sn * dxg + cs * dyg;
+    }
+    __syncthreads();
+    const int sub = threadIdx.x & (lpr - 1), per = kObsThreads / lpr;
+    for (int tl = 0; tl < m; tl++) {
+        for (int i = threadIdx.x / lpr; i < n; i += per) {
+            const float4 p = pose[tl * n + i];
+            const float sn = turn[tl * n + i].x, cs = turn[tl * n + i].y;
+            Slot4 *o = reinterpret_cast<Slot4 *>(obs + ((size_t)(t0 + tl) * A + a0 + i) * F + 3);
+            for (int sl = sub; sl < P; sl += lpr) {
+                const int j = sl < i ? sl : sl + 1;
+                const float4 q = pose[tl * n + min(j, n - 1)];
+                const bool in = j < n && key32(p.x, p.y, q.x, q.y) <= a.R2_obs;
+                const float dx = q.x - p.x, dy = q.y - p.y;
+                const float fx = cs * dx + sn * dy, fy = -sn * dx + cs * dy, h = wrap_pi(q.z - p.z);
+                o[sl] = in ? Slot4{fx, fy, h, q.w} : Slot4{0.f, 0.f, 0.f, 0.f};
             }
         }
-        o[f] = val;
     }
 }
 
+// Gradient of the observation terms with respect to the states after the steps: og [steps, A]
+// (x, y, yaw, speed) for steps t0 .. t0 + gridDim.y, from grad_obs and the state log (the
+// states the observation was formed from, so that the partner masks agree with it).
+// Partners couple the agents: the slot of agent j in observer m's row, f = R(-yaw_m)(p_j -
+// p_m), wrap(yaw_j - yaw_m), v_j, gives terms to both.  One workgroup per world and step: a
+// wave takes an observer (a few of them in small worlds) with a lane per agent j, so that
+// grad_obs is read in rows, only where the partner is within the radius; the terms of j stay
+// in its lane over all observers, those of m are summed over the row's lanes; both in a
+// fixed order.  Bound by the latency of those reads.  Gathered by each agent's lanes inside
+// the backward kernel instead, row and column read per agent and step, the backward took
+// 390 us against 40 + 37 us now (512 x 32 agents, T = 20).
+struct ObsGradLds {
+    float4 *pose;  // x, y, sine, cosine of each agent
+    float4 *mine;  // terms of each agent from its own row (x, y, yaw)
+    float4 *part;  // per wave: terms of each agent from the others' rows
+};
+
+// sum over groups of `cols` lanes (a power of two, at least 8), on all of their lanes
+__device__ __forceinline__ float group_sum(float v, int cols) {
+    v += dpp_f<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+    v += dpp_f<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+    v += dpp_f<0x141>(v);  // row_half_mirror
+    if (cols > 8) v += dpp_f<0x140>(v);  // row_mirror
+    if (cols > 16) v += __shfl_xor(v, 16, kWave);
+    if (cols > 32) v += __shfl_xor(v, 32, kWave);
+    return v;
+}
+
+__global__ __launch_bounds__(kObsThreads) void k_rollout_obs_grad(SimArgs a, const float *__restrict__ slog, int t0,
+                                                                  int cols, const float *__restrict__ grad_obs,
+                                                                  float4 *__restrict__ og) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int w = blockIdx.x, t = t0 + blockIdx.y;
+    const int a0 = a.agent_off[w], n = a.agent_off[w + 1] - a0;
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave, waves = blockDim.x / kWave;
+    const ObsGradLds s{reinterpret_cast<float4 *>(smem), reinterpret_cast<float4 *>(smem) + n,
+                       reinterpret_cast<float4 *>(smem) + 2 * n};
+    const size_t A = (size_t)a.A;
+    const int P = a.P;
+    const size_t F = 3 + 4 * (size_t)P;
+    const float *S = slog + (size_t)t * 4 * A + a0;
+    const float *G = grad_obs + ((size_t)t * A + a0) * F;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        float sn, cs;
+        sincosf(S[2 * A + i], &sn, &cs);
+        s.pose[i] = make_float4(S[i], S[A + i], sn, cs);
+        s.mine[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    __syncthreads();
+    const int rows = kWave / cols;  // observers of a wave at a time
+    const int col = lane & (cols - 1), row = lane / cols;
+    for (int j0 = 0; j0 < n; j0 += cols) {
+        const int j = j0 + col;
+        const float4 pj = s.pose[min(j, n - 1)];
+        float cx = 0.f, cy = 0.f, ch = 0.f, cv = 0.f;
+        // four observers' rows in flight together
+        constexpr int U = 4;
+        for (int m0 = wid * rows; m0 < n; m0 += U * waves * rows) {
+            Slot4 g[U];
+            float4 pm[U];
+            bool in[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int m = m0 + u * waves * rows + row;
+                pm[u] = s.pose[min(m, n - 1)];
+                const int sl = j < m ? j : j - 1;
+                in[u] = j < n && m < n && j != m && sl < P && key32(pm[u].x, pm[u].y, pj.x, pj.y) <= a.R2_obs;
+                g[u] = Slot4{0.f, 0.f, 0.f, 0.f};
+                if (in[u]) g[u] = *reinterpret_cast<const Slot4 *>(G + (size_t)m * F + 3 + 4 * (size_t)sl);
+            }
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int m = m0 + u * waves * rows + row;
+                if (__ballot(in[u]) == 0ull) continue;
+                float rx = 0.f, ry = 0.f, rh = 0.f;
+                if (in[u]) {
+                    const float sn = pm[u].z, cs = pm[u].w;
+                    const float dx = pj.x - pm[u].x, dy = pj.y - pm[u].y;
+                    const float fx = cs * dx + sn * dy, fy = -sn * dx + cs * dy;
+                    const float wx = cs * g[u].x - sn * g[u].y, wy = sn * g[u].x + cs * g[u].y;
+                    cx += wx;
+                    cy += wy;
+                    ch += g[u].z;
+                    cv += g[u].w;
+                    rx = -wx;
+                    ry = -wy;
+                    rh = g[u].x * fy - g[u].y * fx - g[u].z;
+                }
+                rx = group_sum(rx, cols);
+                ry = group_sum(ry, cols);
+                rh = group_sum(rh, cols);
+                if (col == 0 && m < n) {
+                    float4 q = s.mine[m];  // (observer m is always taken by this wave)
+                    q.x += rx;
+                    q.y += ry;
+                    q.z += rh;
+                    s.mine[m] = q;
+                }
+            }
+        }
+        for (int d = cols; d < kWave; d <<= 1) {
+            cx += __shfl_xor(cx, d, kWave);
+            cy += __shfl_xor(cy, d, kWave);
+            ch += __shfl_xor(ch, d, kWave);
+            cv += __shfl_xor(cv, d, kWave);
+        }
+        if (row == 0 && j < n) s.part[wid * n + j] = make_float4(cx, cy, ch, cv);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const float *go = G + (size_t)i * F;
+        const float4 p = s.pose[i];
+        const float dxg = a.gx[a0 + i] - p.x, dyg = a.gy[a0 + i] - p.y;
+        const float gpx = p.w * dxg + p.z * dyg, gpy = -p.z * dxg + p.w * dyg;
+        // own speed, goal in the own frame g' = R(-yaw)(g - p), own slots
+        float4 q = s.mine[i];
+        q.x += -p.w * go[1] + p.z * go[2];
+        q.y += -p.z * go[1] - p.w * go[2];
+        q.z += gpy * go[1] - gpx * go[2];
+        q.w = go[0];
+        for (int k = 0; k < waves; k++) {
+            const float4 c = s.part[k * n + i];
+            q.x += c.x;
+            q.y += c.y;
+            q.z += c.z;
+            q.w += c.w;
+        }
+        og[(size_t)blockIdx.y * A + a0 + i] = q;
+    }
+}
+
+// Steps [Ts, Te) of the backward (all of them unless the observation's gradient og, of these
+// steps, comes in parts: then the adjoint of the state before the part is kept in `carry`).
+// steps of a backward block: whole checkpoint segments, as many as fit 16 steps, or one longer
+__host__ __device__ inline int roll_block(int C) { return C <= kRow ? kRow / C * C : C; }
+
 template <bool DELTA, bool OBS>
-__global__ __launch_bounds__(kRollThreads) void k_rollout_bwd(SimArgs a, const float2 *__restrict__ act,
+__global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, const float2 *__restrict__ act,
                                                               const float *__restrict__ ckpt, int T, int C,
+                                                              int Ts, int Te,
                                                               const float *__restrict__ grad_r,
-                                                              const float *__restrict__ grad_obs,
-                                                              const float *__restrict__ slog,
+                                                              const float4 *__restrict__ og,
+                                                              float4 *__restrict__ carry,
                                                               float2 *__restrict__ grad_a,
                                                               float *__restrict__ grad_s0) {
     __shared__ float4 s_seg[kRollAgents * kEdgeStride];
@@ -583,20 +726,26 @@ __global__ __launch_bounds__(kRollThreads) void k_rollout_bwd(SimArgs a, const f
     const int w = world_of_row(a.agent_off, a.W, i, sub);
     const int r0 = a.road_off[w];
     const EdgeGrid e{a.grid[w], a.ecell_start + (size_t)w * kCellStride, a.eseg + r0, a.eseg_id + r0};
-    const int a0 = a.agent_off[w], nw = a.agent_off[w + 1] - a0, l = i - a0;
-    const int P = a.P, F = 3 + 4 * P;
     float lx = 0.f, ly = 0.f, lth = 0.f, lv = 0.f;  // adjoint of the state after the current step
+    if (OBS && Te < T) {
+        const float4 q = carry[i];
+        lx = q.x;
+        ly = q.y;
+        lth = q.z;
+        lv = q.w;
+    }
     EdgeBound bd{0.f, 0.f, 0.f, -1};
-    // blocks of whole checkpoint segments, as many as fit 16 steps (or 16 steps of a longer
-    // segment), last block first
-    const int B = C <= kRow ? kRow / C * C : C;
-    for (int c0 = (T - 1) / B * B; c0 >= 0; c0 -= B) {
-        const int c1 = min(T, c0 + B);
+    // blocks of whole checkpoint segments (a longer segment 16 steps at a time), last first
+    const int B = roll_block(C);
+    for (int c0 = (Te - 1) / B * B; c0 >= Ts; c0 -= B) {
+        const int c1 = min(Te, c0 + B);
         const float *ck = ckpt + (size_t)(c0 / C) * 4 * A;
         for (int t0 = c0 + (c1 - 1 - c0) / kRow * kRow; t0 >= c0; t0 -= kRow) {
             const int n = min(kRow, c1 - t0), t = t0 + sub;
             const bool on = sub < n;
             const float gr = on ? grad_r[(size_t)t * A + i] : 0.0f;
+            float4 og_t = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (OBS && on) og_t = og[(size_t)(t - Ts) * A + i];
             // states of the block, from the checkpoint (through the steps before the block)
             AgentState c{ck[i], ck[A + i], ck[2 * A + i], ck[3 * A + i], 0.f, 0.f};
             sincosf(c.yaw, &c.sn, &c.cs);
@@ -611,53 +760,8 @@ __global__ __launch_bounds__(kRollThreads) void k_rollout_bwd(SimArgs a, const f
             const EdgeChoice ch = nearest_edges(e, ls, o.x1, o.y1, on, a.R_obs, sub, bd, false);
             // gradient of the step's reward (and observation) with respect to the state after
             // the step
-            float gx = 0.f, gy = 0.f, gth = 0.f, gv = 0.f;
+            float gx = og_t.x, gy = og_t.y, gth = og_t.z, gv = og_t.w;
             const float sn = o.sn1, cs = o.cs1;
-            if (OBS && on) {
-                // observation terms, from the state log (the states the observation was
-                // formed from, so that the partner masks agree with it)
-                const float *S = slog + (size_t)t * 4 * A;
-                const float *go = grad_obs + ((size_t)t * A + i) * F;
-                const float xi = S[i], yi = S[A + i];
-                float oth, octh;
-                sincosf(S[2 * A + i], &oth, &octh);
-                // own speed and goal in the own frame, g' = R(-yaw)(g - p)
-                gv += go[0];
-                {
-                    const float dxg = gxa - xi, dyg = gya - yi;
-                    const float gpx = octh * dxg + oth * dyg, gpy = -oth * dxg + octh * dyg;
-                    gx += -octh * go[1] + oth * go[2];
-                    gy += -oth * go[1] - octh * go[2];
-                    gth += gpy * go[1] - gpx * go[2];
-                }
-                // own partner slots: f = R(-yaw_i)(p_j - p_i), wrap(yaw_j - yaw_i)
-                for (int sl = 0; sl < min(P, nw - 1); sl++) {
-                    const int jj = a0 + (sl < l ? sl : sl + 1);
-                    const float xj = S[jj], yj = S[A + jj];
-                    if (!(key32(xi, yi, xj, yj) <= a.R2_obs)) continue;
-                    const float dx = xj - xi, dy = yj - yi;
-                    const float fx = octh * dx + oth * dy, fy = -oth * dx + octh * dy;
-                    const float bx = go[3 + 4 * sl], by = go[4 + 4 * sl], bdh = go[5 + 4 * sl];
-                    gx -= octh * bx - oth * by;
-                    gy -= oth * bx + octh * by;
-                    gth += bx * fy - by * fx - bdh;
-                }
-                // the slot of agent i in every other agent's observation
-                for (int m = 0; m < nw; m++) {
-                    const int sl = l < m ? l : l - 1;
-                    if (m == l || sl >= P) continue;
-                    const int mm = a0 + m;
-                    const float xm = S[mm], ym = S[A + mm];
-                    if (!(key32(xm, ym, xi, yi) <= a.R2_obs)) continue;
-                    float sm, cm;
-                    sincosf(S[2 * A + mm], &sm, &cm);
-                    const float *gm = grad_obs + ((size_t)t * A + mm) * F + 3 + 4 * sl;
-                    gx += cm * gm[0] - sm * gm[1];
-                    gy += sm * gm[0] + cm * gm[1];
-                    gth += gm[2];
-                    gv += gm[3];
-                }
-            }
             // goal term: r = -|g'|
             {
                 const float dxg = gxa - o.x1, dyg = gya - o.y1;
@@ -775,6 +879,10 @@ __global__ __launch_bounds__(kRollThreads) void k_rollout_bwd(SimArgs a, const f
             if (on) grad_a[(size_t)t * A + i] = ga;
         }
     }
+    if (OBS && Ts > 0) {
+        if (sub == 0) carry[i] = make_float4(lx, ly, lth, lv);
+        return;
+    }
     if (grad_s0 && sub == 0) {
         grad_s0[i] = lx;
         grad_s0[A + i] = ly;
@@ -866,25 +974,69 @@ hipError_t launch_rollout_fwd_impl(const SimArgs &a, const float2 *actions, int 
     return hipGetLastError();
 }
 
-hipError_t launch_rollout_obs_impl(const SimArgs &a, const float *states, int T, float *obs, hipStream_t s) {
-    const long long items = (long long)T * a.A;
-    const long long blocks = (items + kObsThreads / kWave - 1) / (kObsThreads / kWave);
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_rollout_obs, dim3((unsigned)blocks), dim3(kObsThreads), 0, s, a, states, T, obs);
-    return hipGetLastError();
+// lanes per agent of k_rollout_obs: the power of two that leaves the fewest lanes without a slot
+static int obs_lanes(int P) {
+    int best = kWave;
+    for (int l = kWave / 2; l >= 8; l /= 2)
+        if ((P + l - 1) / l * l < (P + best - 1) / best * best) best = l;
+    return best;
+}
+
+hipError_t launch_rollout_obs_impl(const SimArgs &a, const float *states, int T, int max_agents, float *obs,
+                                   hipStream_t s) {
+    // about 4096 slots per workgroup, 16 per thread; at least one step, states within 48 KB
+    const long long slots = (long long)std::max(max_agents, 1) * std::max(a.P, 1);
+    const int steps = (int)std::max(1ll, std::min({4096 / slots, (long long)T, 2048ll / std::max(max_agents, 1)}));
+    const size_t lds = (size_t)steps * max_agents * (sizeof(float4) + sizeof(float2));
+    const long long most = 65535ll * steps;  // (grid axis y)
+    for (long long t0 = 0; t0 < T; t0 += most) {
+        const int m = (int)std::min((long long)T - t0, most);
+        hipLaunchKernelGGL(k_rollout_obs, dim3(a.W, (m + steps - 1) / steps), dim3(kObsThreads), lds, s, a, states,
+                           (int)t0, T, steps, obs_lanes(a.P), obs);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+template <bool DELTA>
+static hipError_t launch_bwd(const SimArgs &a, const float2 *actions, const float *ckpt, int T, int C,
+                             const float *grad_rewards, const float *grad_obs, const float *states, int max_agents,
+                             float2 *grad_actions, float *grad_state0, hipStream_t s) {
+    if (!grad_obs) {
+        hipLaunchKernelGGL((k_rollout_bwd<DELTA, false>), dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a, actions,
+                           ckpt, T, C, 0, T, grad_rewards, nullptr, nullptr, grad_actions, grad_state0);
+        return hipGetLastError();
+    }
+    // the observation's gradient in parts of as many whole blocks as the workspace holds
+    const int B = roll_block(C), part = std::max(1, obs_grad_steps(a.A) / B) * B;
+    int cols = 8;  // columns of a wave: as many as agents, a power of two
+    while (cols < kWave && cols < max_agents) cols *= 2;
+    const int rows = kWave / cols;
+    // four observers per wave and pass, up to four waves, within 64 KB of LDS
+    const int fit = std::max(1, 64 * 1024 / (int)sizeof(float4) / std::max(max_agents, 1) - 2);
+    const int waves = std::min({kObsThreads / kWave, fit, std::max(1, (max_agents + 4 * rows - 1) / (4 * rows))});
+    const size_t lds = (size_t)max_agents * sizeof(float4) * (2 + waves);
+    for (int Ts = (T - 1) / part * part; Ts >= 0; Ts -= part) {
+        const int Te = std::min(T, Ts + part);
+        hipLaunchKernelGGL(k_rollout_obs_grad, dim3(a.W, Te - Ts), dim3(waves * kWave), lds, s, a, states, Ts, cols,
+                           grad_obs, a.obs_grad);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_rollout_bwd<DELTA, true>), dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a, actions,
+                           ckpt, T, C, Ts, Te, grad_rewards, a.obs_grad, a.carry, grad_actions, grad_state0);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_rollout_bwd_impl(const SimArgs &a, const float2 *actions, const float *ckpt, int T,
                                    int C, const float *grad_rewards, const float *grad_obs,
-                                   const float *states, float2 *grad_actions, float *grad_state0,
+                                   const float *states, int max_agents, float2 *grad_actions, float *grad_state0,
                                    hipStream_t s) {
     if (C < 1 || C > kMaxCkpt) return hipErrorInvalidValue;
-    const bool delta = a.dyn == GD_DYN_DELTA;
-    auto k = grad_obs ? (delta ? k_rollout_bwd<true, true> : k_rollout_bwd<false, true>)
-                      : (delta ? k_rollout_bwd<true, false> : k_rollout_bwd<false, false>);
-    hipLaunchKernelGGL(k, dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a, actions, ckpt, T, C, grad_rewards,
-                       grad_obs, states, grad_actions, grad_state0);
-    return hipGetLastError();
+    auto f = a.dyn == GD_DYN_DELTA ? launch_bwd<true> : launch_bwd<false>;
+    return f(a, actions, ckpt, T, C, grad_rewards, grad_obs, states, max_agents, grad_actions, grad_state0, s);
 }
 
 }  // namespace gdk
