@@ -315,7 +315,7 @@ gd_status gd_invert_actions(gd_sim *sim, const float *states, int32_t T, float *
  * caller gathers the kept points (types and end-of-polyline marks are unchanged, as end
  * points survive) and builds the simulator on them.  workspace: device, 256-byte aligned,
  * at least gd_decimate_workspace_size(n_points) bytes, used for polylines of more than
- * 4096 points.  Asynchronous on `stream`; the library allocates nothing. */
+ * 6144 points.  Asynchronous on `stream`; the library allocates nothing. */
 gd_status gd_decimate_workspace_size(int32_t n_points, size_t *bytes);
 gd_status gd_decimate(const int32_t *poly_off, int32_t n_poly, int32_t n_points, const float *x,
                       const float *y, float min_area, uint8_t *keep, float *dir, void *workspace,

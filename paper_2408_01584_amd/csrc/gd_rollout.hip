@@ -26,8 +26,7 @@
 // k_rollout_obs forms the continuous observation of each agent (speed, goal in its frame;
 // per partner slot the partner's position in its frame, heading difference, speed --
 // Fig. 1, Sec. 3.2 "Sensor modalities").  Partners couple the agents of a world, so the
-// backward reads the other agents' states from that log: at each step an agent's adjoint
-// gathers the terms of its own observation and of every observation it appears in.
+// observation's gradient is formed from that log in a kernel of its own, world by world.
 #include <algorithm>
 
 #include "gd_internal.h"
