@@ -121,8 +121,8 @@ typedef struct {
     float collision_penalty;   /* reward -= penalty when the agent collided */
     float cell_size;           /* road grid cell (m); 0 = library default (15 m) */
     int32_t obs_waves;         /* launch shape of the step kernel: waves per workgroup
-                                  (1, 2, 4, 8, 12, 16; 0 = the shape with the most
-                                  resident waves per compute unit that fits the LDS) */
+                                  (1, 2, 4, 8, 12, 16; 0 = the shape with the lowest
+                                  predicted step time that fits the LDS) */
     int32_t obs_bins;          /* distance bins of the top-K selection (64, 128, 256,
                                   512, 1024; 0 = default) */
     int32_t obs_cands;         /* candidate-list entries per wave of the top-K selection
@@ -132,7 +132,7 @@ typedef struct {
                                   GD_ROAD_LDS (staged in LDS for the whole step; needs
                                   16 B per point of the largest world), GD_ROAD_GLOBAL
                                   (from the workspace through the caches) or GD_ROAD_AUTO
-                                  (staged when that keeps as many resident waves) */
+                                  (whichever is predicted to be faster) */
     int32_t dynamics;          /* GD_DYN_BICYCLE or GD_DYN_DELTA */
     float lidar_fov;           /* 0: LIDAR rays around the full circle; in [1e-4, 2 pi]:
                                   a view cone of this width (rad) turned by the per-agent

@@ -952,19 +952,15 @@ static bool node_one(const SimArgs *a, const StepCtl *c, int waves, hipKernelNod
     return true;
 }
 
-// Waves per compute unit that the registers of this instantiation allow (4 SIMDs, at
-// most 8 waves each, 512 VGPRs per lane per SIMD in granules of 8); 20 when the runtime
-// does not report the count.
+// Waves per compute unit that the registers (vector and scalar) of this instantiation allow;
+// 20 when the runtime does not say.
 template <int NB, int RM>
-static int vgpr_waves_per_cu() {
+static int reg_waves_per_cu() {
     static int cached = 0;
     if (!cached) {
-        hipFuncAttributes at{};
-        int w = 20;
-        if (hipFuncGetAttributes(&at, (const void *)k_step<NB, RM>) == hipSuccess && at.numRegs > 0) {
-            const int regs = (at.numRegs + 7) / 8 * 8;
-            w = 4 * std::min(8, 512 / regs);
-        }
+        int w = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&w, (const void *)k_step<NB, RM>, kWave, 0) != hipSuccess || w < 1)
+            w = 20;
         cached = w;
     }
     return cached;
@@ -973,9 +969,9 @@ static int vgpr_waves_per_cu() {
 template <int NB>
 static int waves_nb(int rm) {
     switch (rm) {
-        case kRoadLds: return vgpr_waves_per_cu<NB, kRoadLds>();
-        case kRoadGlobal16: return vgpr_waves_per_cu<NB, kRoadGlobal16>();
-        default: return vgpr_waves_per_cu<NB, kRoadGlobal32>();
+        case kRoadLds: return reg_waves_per_cu<NB, kRoadLds>();
+        case kRoadGlobal16: return reg_waves_per_cu<NB, kRoadGlobal16>();
+        default: return reg_waves_per_cu<NB, kRoadGlobal32>();
     }
 }
 

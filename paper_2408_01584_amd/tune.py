@@ -23,9 +23,9 @@ CACHE = os.environ.get("GD_TUNE_CACHE", os.path.join(os.path.dirname(os.path.abs
 DEFAULT_SPACE = [
     dict(obs_waves=w, obs_bins=b, obs_cands=c, cell_size=cs, obs_road=rd)
     for rd in (1, 2)  # GD_ROAD_LDS, GD_ROAD_GLOBAL
-    for w in (16, 12, 8)
-    for c in (512, 768)
-    for b in (256, 512, 1024)
+    for w in (16, 12, 8, 4)
+    for c in (256, 512)
+    for b in (128, 256, 512)
     for cs in (10.0, 15.0)
 ]
 
