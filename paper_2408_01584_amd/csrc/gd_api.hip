@@ -597,6 +597,9 @@ gd_status gd_create(const gd_config *cfg, const int32_t *h_agent_off, const int3
         sim->lctl.cell_cap4 = sim->ctl.cell_cap4;
         sim->lctl.waves = kLidarMaxWaves;
         sim->lctl.edge_cap = 0;
+        // few worlds: several workgroups each, until there are three per compute unit or a
+        // wave has one agent
+        sim->lctl.parts = std::max(1, std::min(3 * kComputeUnits / W, (max_agents + kLidarMaxWaves - 1) / kLidarMaxWaves));
         if (cfg->lidar_rays > 0) {
             const size_t glob = lidar_lds_bytes(cfg->lidar_rays, sim->lctl);
             LidarCtl staged = sim->lctl;

@@ -92,7 +92,7 @@ struct StepCtl {
     int cand_cap;              // candidate list entries per wave
 };
 
-// Launch control of the LIDAR kernel (one workgroup per world).
+// Launch control of the LIDAR kernel (`parts` workgroups per world).
 constexpr int kLidarMaxWaves = 8;
 struct LidarCtl {
     const int *order;  // [W] world of each workgroup, NULL = identity
@@ -100,6 +100,7 @@ struct LidarCtl {
     int edge_cap;      // edge segments per world staged in LDS (0 = read from global)
     int cell_cap4;     // LDS slots for a world's edge-grid cell starts
     int waves;         // waves per workgroup (1..kLidarMaxWaves)
+    int parts;         // workgroups per world
 };
 size_t lidar_lds_bytes(int N, const LidarCtl &lc);
 

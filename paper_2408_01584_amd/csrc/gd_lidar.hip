@@ -8,113 +8,105 @@
 // (range, 0).  Everything below works in the frame of the ray fan (the heading, turned by
 // the head angle for a cone), in which the ray directions are the same for all agents.
 //
-// One workgroup per world.  The world's agents (position, heading, half extents, flags)
-// are staged in LDS first, and its edge segments with their grid rows too when that does
-// not cost resident workgroups (the host decides; otherwise they are read through the
-// caches).  Then one wave per agent, lanes
-// over the candidate segments: edge segments keyed in the grid rows that meet the disc of
-// radius range + longest segment, then the four sides of every other visible agent within
-// range.  Each candidate is moved into the ego frame; those whose closest point lies
-// within range are compacted into a per-wave list, and the list is processed with one
-// candidate per lane: the arc it subtends (widened by 1 mrad) gives the few rays it can
-// meet, and each of those rays is intersected exactly; a per-ray 64-bit LDS minimum over
-// (distance bits, type) keeps the nearest hit (ties: road edge first).
+// A workgroup per world (several for a batch of few worlds, each with a part of its agents).
+// The world's agents (position, heading, half extents, flags) are staged in LDS first, and
+// its edge segments with their grid rows too when that does not cost resident workgroups
+// (the host decides; otherwise they are read through the caches).  Then one wave per agent,
+// lanes over the candidate segments: edge segments keyed in the grid rows that meet the disc
+// of radius range + longest segment, then the four sides of every other visible agent
+// within range.  Each candidate is moved into the frame of the fan; the arc it subtends
+// (widened by 1 mrad) gives the run of rays it can meet.  Most candidates lie between two
+// rays (four of five road edges with 30 rays): only those with a ray go to a per-wave list.
+// The list is then turned into (candidate, ray) tasks, so that each lane intersects one ray
+// exactly; a per-ray 64-bit LDS minimum over (distance bits, type) keeps the nearest hit
+// (ties: road edge first).
+//
+// Bound by vector instructions.  With the arcs taken after the list, for every candidate within range,
+// and each candidate's rays taken by its lane one after the other, an agent took 904 vector
+// instructions with a ring of 30 rays and 1468 with a cone of 120 rays over 2.1 rad, 732 and
+// 1202 now: 390 -> 347 us for 4096 x 64 agents and 49 -> 39 us for 500 x 24.
 #include "gd_internal.h"
 
 namespace gdk {
 
-// Angle of (x, y) in [-pi, pi] within 2e-5 rad.  It only selects which rays a candidate
-// is tested against, a range widened by 1 mrad on each side, so it leaves the hits
-// unchanged.  atan(a) on [0, 1] is
-// a * P(a^2) with P a degree-4 least-squares fit on Chebyshev nodes (max error 1.2e-5).
-__device__ __forceinline__ float ray_angle(float y, float x) {
-    const float ax = fabsf(x), ay = fabsf(y);
-    const float mx = fmaxf(ax, ay), mn = fminf(ax, ay);
-    const float t = mx > 0.0f ? mn * __builtin_amdgcn_rcpf(mx) : 0.0f;
-    const float s = t * t;
-    float r = ((((0.020931812f * s - 0.0854083076f) * s + 0.18041268f) * s - 0.330405563f) * s +
-               0.999878764f) * t;
-    if (ay > ax) r = 1.57079633f - r;
-    if (x < 0.0f) r = 3.14159265f - r;
-    return y < 0.0f ? -r : r;
+// Angle of (x, y) in [-pi, pi] within 2e-5 rad, ri = 1 / |(x, y)|.  It only selects which rays
+// a candidate is tested against, a run widened by 1 mrad on each side, so it leaves the hits
+// unchanged.  With u = (|y| - |x|) ri = sqrt(2) sin(angle of (|x|, |y|) - pi/4), the angle is
+// pi/4 + asin(u / sqrt(2)), the arcsine as u P(u^2) with P a degree-3 fit on [0, 1] (max error
+// 1.9e-5), then the quadrant.
+__device__ __forceinline__ float ray_angle(float y, float x, float ri) {
+    const float u = (fabsf(y) - fabsf(x)) * ri;
+    const float s = u * u;
+    float r = fmaf(fmaf(fmaf(fmaf(0.0104458375f, s, 0.00711097206f), s, 0.0608780789f), s, 0.70694428f), u, 0.785398163f);
+    r = x < 0.0f ? 3.14159265f - r : r;
+    return copysignf(r, y);
 }
 
-// Rays of the fan whose angle lies in [a0, a1] widened by 1 mrad on each side (far above
-// the angle error; widening only adds rays that the exact test then rejects).  Ring: ray k
-// at k / inv_step, indices taken modulo N.  Cone: ray k at (k + 1/2) / inv_step - half,
-// indices clamped to [0, N).
+// Run of rays of the fan that the segment a-b can meet (endpoints in the frame of the fan,
+// agent at the origin, ria and rib their inverse distances): first ray k0 and count n, the
+// arc widened by 1 mrad on each side (far above the angle error; widening only adds rays
+// that the exact test then rejects).  Ring: ray k at k / inv_step, indices modulo N.  Cone: ray k
+// at (k + 1/2) / inv_step - half.
 template <bool CONE>
-__device__ __forceinline__ void fan_rays(float a0, float a1, int N, float inv_step, float half, int &k0,
-                                         int &k1) {
-    if (!CONE) {
-        k0 = (int)ceilf((a0 - 1e-3f) * inv_step);
-        k1 = (int)floorf((a1 + 1e-3f) * inv_step);
-        return;
-    }
-    k0 = (int)fmaxf(ceilf((a0 - 1e-3f + half) * inv_step - 0.5f), 0.0f);
-    k1 = (int)fminf(floorf((a1 + 1e-3f + half) * inv_step - 0.5f), (float)(N - 1));
-}
-
-template <bool CONE>
-__device__ __forceinline__ void lidar_candidate(float ax, float ay, float bx, float by,
-                                                unsigned type, int N, float inv_step, float half,
-                                                float range, const float2 *dirs,
-                                                unsigned long long *best) {
-    // a, b: segment endpoints in the frame of the ray fan (agent at the origin)
-    const float pa = ray_angle(ay, ax), pb = ray_angle(by, bx);
+__device__ __forceinline__ int arc_rays(float ax, float ay, float ria, float bx, float by, float rib, int N,
+                                        float inv_step, float half, int &k0) {
+    constexpr float kPi = 3.14159265f, kTwoPi = 6.283185307179586f, kWide = 1e-3f;
+    const float pa = ray_angle(ay, ax, ria), pb = ray_angle(by, bx, rib);
     float lo = pa, span = pb - pa;
-    const float two_pi = 6.283185307179586f;
-    if (span > 3.14159265f) span -= two_pi;
-    if (span < -3.14159265f) span += two_pi;
-    if (span < 0.0f) {
-        lo = pb;
-        span = -span;
+    span = span > kPi ? span - kTwoPi : span;
+    span = span < -kPi ? span + kTwoPi : span;
+    lo = span < 0.0f ? pb : lo;
+    span = fabsf(span);
+    // an arc within 0.01 rad of pi (the segment passes next to the origin, where the rounded
+    // angles could pick the complementary arc) takes every ray
+    const bool all = !(span <= 3.13159265f);
+    if (!CONE) {
+        // lo >= -pi, so k0 >= -N / 2 - 1: one correction makes it a ray
+        const int f = (int)ceilf((lo - kWide) * inv_step);
+        const int n = (int)floorf((lo + span + kWide) * inv_step) - f + 1;
+        k0 = all || n >= N ? 0 : f < 0 ? f + N : f;
+        return all ? N : min(n, N);
     }
-    // the rays inside the arc [lo, lo + span]; an arc within 0.01 rad of pi (the segment
-    // passes next to the origin, where the rounded angles could pick the complementary
-    // arc) takes every ray.  A cone's rays lie in (-pi, pi), so the part of a (widened)
-    // arc beyond +-pi is looked up again one turn lower or higher.
-    int k0, k1, k2 = 0, k3 = -1;
-    fan_rays<CONE>(lo, lo + span, N, inv_step, half, k0, k1);
-    if (span > 3.13159265f || (!CONE && k1 - k0 >= N - 1)) {
-        k0 = 0;
-        k1 = N - 1;
-    } else if (CONE && lo + span + 1e-3f > 3.14159265f) {
-        fan_rays<CONE>(lo - two_pi, lo + span - two_pi, N, inv_step, half, k2, k3);
-    } else if (CONE && lo - 1e-3f < -3.14159265f) {
-        fan_rays<CONE>(lo + two_pi, lo + span + two_pi, N, inv_step, half, k2, k3);
-    }
-    const float ex = bx - ax, ey = by - ay;
-    const float nt = ax * ey - ay * ex;  // t = nt / den along the ray
-    const int n01 = k1 >= k0 ? k1 - k0 + 1 : 0;
-    const int nall = CONE ? n01 + (k3 >= k2 ? k3 - k2 + 1 : 0) : n01;
-    for (int m = 0; m < nall; m++) {
-        int k;
-        if (CONE) {
-            k = m < n01 ? k0 + m : k2 + (m - n01);  // in [0, N) already
+    // a cone's rays lie in (-pi, pi): the part of a (widened) arc beyond +-pi is looked up
+    // again one turn lower or higher; an arc with rays on both sides takes every ray
+    auto run = [&](float a0, float a1, int &f) {
+        f = (int)fmaxf(ceilf((a0 - kWide + half) * inv_step - 0.5f), 0.0f);
+        return max((int)fminf(floorf((a1 + kWide + half) * inv_step - 0.5f), (float)(N - 1)) - f + 1, 0);
+    };
+    int n = run(lo, lo + span, k0);
+    const float turn = lo + span + kWide > kPi ? -kTwoPi : lo - kWide < -kPi ? kTwoPi : 0.0f;
+    if (turn != 0.0f) {
+        int f;
+        const int m = run(lo + turn, lo + span + turn, f);
+        k0 = n == 0 ? f : k0;
+        if (n != 0 && m != 0) {
+            k0 = 0;
+            n = N;
         } else {
-            // k0 >= -N/2 - 1 and k0 + m <= N + 1 (arcs are at most a turn), so one
-            // correction each way replaces the modulo (an integer division on the GPU)
-            k = k0 + m;
-            k = k < 0 ? k + N : k;
-            k = k >= N ? k - N : k;
+            n += m;
         }
-        const float2 d = dirs[k];
-        // ray t*d against a + s*e: t = nt / den, s = ns / den; the range tests are taken
-        // on the numerators (signs and magnitudes), the division only for a hit
-        const float den = d.x * ey - d.y * ex;
-        const float ns = ax * d.y - ay * d.x;
-        const float sg = den < 0.0f ? -1.0f : 1.0f;
-        const float snt = sg * nt, sns = sg * ns, aden = sg * den;
-        if (aden > 0.0f && snt > 0.0f && snt <= range * aden && sns >= 0.0f && sns <= aden) {
-            // hit distance with the hardware reciprocal (1 ulp; about 2 ulp with the
-            // product, far inside the distance tolerance)
-            const float t = nt * __builtin_amdgcn_rcpf(den);
-            if (t > 0.0f && t <= range) {
-                const unsigned long long key = ((unsigned long long)__float_as_uint(t) << 32) | type;
-                atomicMin(&best[k], key);
-            }
-        }
+    }
+    k0 = all ? 0 : k0;
+    return all ? N : n;
+}
+
+// One ray (direction d) against the segment a-b: hit distance and type into the ray's minimum.
+// ray t*d against a + s*e: t = nt / den, s = ns / den; the range tests are taken on the
+// numerators (signs and magnitudes), the division only for a hit
+__device__ __forceinline__ void cast_ray(const float4 &v, unsigned type, float2 d, float range,
+                                         unsigned long long *best) {
+    const float ax = v.x, ay = v.y;
+    const float ex = v.z - ax, ey = v.w - ay;
+    const float nt = ax * ey - ay * ex;  // t = nt / den along the ray
+    const float den = d.x * ey - d.y * ex;
+    const float ns = ax * d.y - ay * d.x;
+    const float sg = den < 0.0f ? -1.0f : 1.0f;
+    const float snt = sg * nt, sns = sg * ns, aden = sg * den;
+    if (aden > 0.0f && snt > 0.0f && snt <= range * aden && sns >= 0.0f && sns <= aden) {
+        // hit distance with the hardware reciprocal (1 ulp; about 2 ulp with the product,
+        // far inside the distance tolerance)
+        const float t = nt * __builtin_amdgcn_rcpf(den);
+        if (t > 0.0f && t <= range) atomicMin(best, ((unsigned long long)__float_as_uint(t) << 32) | type);
     }
 }
 
@@ -122,24 +114,13 @@ __device__ __forceinline__ float lidar_uniform(float v) {
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
-constexpr int kLidarList = 256;  // candidate list entries per wave
-
-// a segment (ego frame, agent at the origin) can hold a hit within `range` only if its
-// closest point lies within it; the 1 mm of slack covers the rounding of this test
-__device__ __forceinline__ bool seg_in_range(float ax, float ay, float bx, float by, float r2) {
-    const float ex = bx - ax, ey = by - ay;
-    const float ee = ex * ex + ey * ey;
-    // (the hardware reciprocal: its 1-ulp error moves the closest point by far less than
-    // the 1 mm of slack)
-    float t = ee > 0.0f ? -(ax * ex + ay * ey) * __builtin_amdgcn_rcpf(ee) : 0.0f;
-    t = fminf(fmaxf(t, 0.0f), 1.0f);
-    const float cx = ax + t * ex, cy = ay + t * ey;
-    return cx * cx + cy * cy <= r2;
-}
+constexpr int kLidarList = 128;   // candidate list entries per wave
+constexpr int kLidarTake = 4;     // rays a candidate turns into tasks at a time
+constexpr int kLidarTasks = 64 * kLidarTake;
 
 // LDS layout of one workgroup (byte offsets, 16-aligned regions)
 struct LidarLds {
-    size_t dirs, best, list, ltype, nearl, agents, edges, ecells, total;
+    size_t dirs, best, list, runs, tasks, nearl, agents, edges, ecells, total;
 };
 
 __host__ __device__ inline LidarLds lidar_layout(int N, int waves, int agent_cap, int edge_cap,
@@ -149,8 +130,9 @@ __host__ __device__ inline LidarLds lidar_layout(int N, int waves, int agent_cap
     L.dirs = 0;
     L.best = up((size_t)N * 8);
     L.list = L.best + up((size_t)waves * N * 8);
-    L.ltype = L.list + (size_t)waves * kLidarList * 16;
-    L.nearl = L.ltype + up((size_t)waves * kLidarList);
+    L.runs = L.list + (size_t)waves * kLidarList * 16;
+    L.tasks = L.runs + (size_t)waves * kLidarList * 4;
+    L.nearl = L.tasks + (size_t)waves * kLidarTasks * 4;
     L.agents = L.nearl + up((size_t)waves * agent_cap * 2);
     // x, y, cos, sin, half length, half width, half diagonal, flags
     L.edges = L.agents + up((size_t)agent_cap * 4 * 8);
@@ -170,7 +152,8 @@ __global__ __launch_bounds__(kLidarMaxWaves * kWave) void k_lidar(SimArgs a, Lid
     const int lane = threadIdx.x & (kWave - 1);
     unsigned long long *best = reinterpret_cast<unsigned long long *>(smem + L.best) + (size_t)wid * N;
     float4 *lst = reinterpret_cast<float4 *>(smem + L.list) + (size_t)wid * kLidarList;
-    unsigned char *ltype = smem + L.ltype + (size_t)wid * kLidarList;
+    unsigned *runs = reinterpret_cast<unsigned *>(smem + L.runs) + (size_t)wid * kLidarList;  // k0, count, type
+    unsigned *tasks = reinterpret_cast<unsigned *>(smem + L.tasks) + (size_t)wid * kLidarTasks;
     unsigned short *nearl = reinterpret_cast<unsigned short *>(smem + L.nearl) + (size_t)wid * lc.agent_cap;
     const int ac = lc.agent_cap;
     float *sx = reinterpret_cast<float *>(smem + L.agents);
@@ -180,7 +163,8 @@ __global__ __launch_bounds__(kLidarMaxWaves * kWave) void k_lidar(SimArgs a, Lid
     float4 *sedge = reinterpret_cast<float4 *>(smem + L.edges);
     int *secells = reinterpret_cast<int *>(smem + L.ecells);
 
-    const int w = lc.order ? lc.order[blockIdx.x] : (int)blockIdx.x;
+    const int slot = (int)blockIdx.x / lc.parts, part = (int)blockIdx.x % lc.parts;
+    const int w = lc.order ? lc.order[slot] : slot;
     const int a0 = a.agent_off[w];
     const int n = a.agent_off[w + 1] - a0;
     const int r0 = a.road_off[w];
@@ -225,8 +209,8 @@ __global__ __launch_bounds__(kLidarMaxWaves * kWave) void k_lidar(SimArgs a, Lid
 
     const int *ecs = staged ? secells : a.ecell_start + (size_t)w * kCellStride;
     const float4 *es = staged ? sedge : a.eseg + r0;
-    const float reach = range + g.max_seg + 1e-3f * g.cs + 1e-3f;
-    for (int l = wid; l < n; l += nwaves) {
+    const float reach = range + g.max_seg + 1e-3f * g.cs + 1e-3f;  // of the edge segments
+    for (int l = part * nwaves + wid; l < n; l += lc.parts * nwaves) {
         const int ai = a0 + l;
         float *out = a.lidar + (size_t)ai * N;
         int *hit = a.lidar_hit + (size_t)ai * N;
@@ -252,33 +236,53 @@ __global__ __launch_bounds__(kLidarMaxWaves * kWave) void k_lidar(SimArgs a, Lid
         for (int k = lane; k < N; k += kWave) best[k] = ~0ull;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        // Candidates in the ego frame that pass an exact range test are appended to a
-        // per-wave list (ballot compaction); the list is cast in full waves whenever it
-        // fills, and at the end, so that the angle and ray work runs on dense lanes.
-        const float r2c = (range + 1e-3f) * (range + 1e-3f);
         int nl = 0;
-        auto flush = [&]() {
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            for (int e = lane; e < nl; e += kWave) {
-                const float4 v = lst[e];
-                lidar_candidate<CONE>(v.x, v.y, v.z, v.w, ltype[e], N, inv_step, half, range, dirs, best);
-            }
-            nl = 0;
+        auto sync = [] {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         };
-        auto push = [&](bool keep, float ax, float ay, float bx, float by, unsigned type) {
+        // the listed candidates' rays, kLidarTake per candidate and pass, one task per lane
+        auto flush = [&]() {
+            sync();
+            for (int e0 = 0; e0 < nl; e0 += kWave) {
+                const int e = e0 + lane;
+                const unsigned run = e < nl ? runs[e] : 0u;
+                int k = run & 0x7ff, left = (run >> 11) & 0x7ff;
+                while (__ballot(left > 0) != 0ull) {
+                    const int c = min(left, kLidarTake);
+                    const int end = wave_incl_scan(c);
+                    const int total = __builtin_amdgcn_readlane(end, kWave - 1);
+                    for (int m = 0; m < c; m++) {
+                        tasks[end - c + m] = ((unsigned)e << 11) | (unsigned)k;
+                        k = k + 1 == N ? 0 : k + 1;
+                    }
+                    left -= c;
+                    sync();
+                    for (int t = lane; t < total; t += kWave) {
+                        const unsigned task = tasks[t];
+                        const int te = task >> 11, tk = task & 0x7ff;
+                        cast_ray(lst[te], runs[te] >> 22, dirs[tk], range, &best[tk]);
+                    }
+                    sync();
+                }
+            }
+            nl = 0;
+        };
+        auto push = [&](bool ok, float ax, float ay, float bx, float by, unsigned type, float near2) {
+            const float a2 = fmaxf(ax * ax + ay * ay, 1e-30f), b2 = fmaxf(bx * bx + by * by, 1e-30f);
+            int k0, cnt = arc_rays<CONE>(ax, ay, __builtin_amdgcn_rsqf(a2), bx, by, __builtin_amdgcn_rsqf(b2), N,
+                                         inv_step, half, k0);
+            const bool keep = ok && cnt > 0 && fminf(a2, b2) <= near2;
             const unsigned long long bal = __ballot(keep);
-            const int cnt = __popcll(bal);
-            if (nl + cnt > kLidarList) flush();
+            const int add = __popcll(bal);
+            if (nl + add > kLidarList) flush();
             if (keep) {
                 const int pos = nl + __builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32),
                                                                __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
                 lst[pos] = make_float4(ax, ay, bx, by);
-                ltype[pos] = (unsigned char)type;
+                runs[pos] = (unsigned)k0 | ((unsigned)cnt << 11) | (type << 22);
             }
-            nl += cnt;
+            nl += add;
         };
         // road-edge segments keyed in the rows that meet the disc of radius `reach`: one
         // lane per row computes the row's range of cell-sorted segments, and the ranges
@@ -313,7 +317,8 @@ __global__ __launch_bounds__(kLidarMaxWaves * kWave) void k_lidar(SimArgs a, Lid
                 const float dx0 = e.x - px, dy0 = e.y - py, dx1 = e.z - px, dy1 = e.w - py;
                 const float ax = cs * dx0 + sn * dy0, ay = -sn * dx0 + cs * dy0;
                 const float bx = cs * dx1 + sn * dy1, by = -sn * dx1 + cs * dy1;
-                push(ok && seg_in_range(ax, ay, bx, by, r2c), ax, ay, bx, by, 1u);
+                // (an edge segment with a hit has an end within `reach` of the agent)
+                push(ok, ax, ay, bx, by, 1u, reach * reach);
             }
         }
         // sides of the other visible agents' boxes: the agents near enough are compacted
@@ -351,7 +356,7 @@ __global__ __launch_bounds__(kLidarMaxWaves * kWave) void k_lidar(SimArgs a, Lid
             const float ux1 = dxj + cj * ax1 - sj * ay1, uy1 = dyj + sj * ax1 + cj * ay1;
             const float ax = cs * ux0 + sn * uy0, ay = -sn * ux0 + cs * uy0;
             const float bx = cs * ux1 + sn * uy1, by = -sn * ux1 + cs * uy1;
-            push(ok && seg_in_range(ax, ay, bx, by, r2c), ax, ay, bx, by, 2u);
+            push(ok, ax, ay, bx, by, 2u, INFINITY);
         }
         flush();
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -391,8 +396,8 @@ hipError_t launch_lidar_impl(const SimArgs &a, const LidarCtl &lc, hipStream_t s
     const size_t lds = lidar_lds_bytes(a.N, lc);
     hipError_t e = lidar_prepare(a, lds);
     if (e != hipSuccess) return e;
-    if (a.lidar_fov > 0.0f) hipLaunchKernelGGL(k_lidar<true>, dim3(a.W), dim3(lc.waves * kWave), lds, s, a, lc);
-    else hipLaunchKernelGGL(k_lidar<false>, dim3(a.W), dim3(lc.waves * kWave), lds, s, a, lc);
+    if (a.lidar_fov > 0.0f) hipLaunchKernelGGL(k_lidar<true>, dim3(a.W * lc.parts), dim3(lc.waves * kWave), lds, s, a, lc);
+    else hipLaunchKernelGGL(k_lidar<false>, dim3(a.W * lc.parts), dim3(lc.waves * kWave), lds, s, a, lc);
     return hipGetLastError();
 }
 
@@ -400,7 +405,7 @@ bool lidar_kernel_node(const SimArgs *a, const LidarCtl *lc, hipKernelNodeParams
     const size_t lds = lidar_lds_bytes(a->N, *lc);
     if (lidar_prepare(*a, lds) != hipSuccess) return false;
     p.func = const_cast<void *>(lidar_kernel(*a));
-    p.gridDim = dim3(a->W);
+    p.gridDim = dim3(a->W * lc->parts);
     p.blockDim = dim3(lc->waves * kWave);
     p.sharedMemBytes = (unsigned)lds;
     args[0] = (void *)a;
