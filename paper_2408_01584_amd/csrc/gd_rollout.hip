@@ -17,9 +17,9 @@
 // ckpt_every.
 //
 // Both are bound by vector instructions (per agent-step, 4096 worlds x 64 agents, 6000 road
-// points, T = 91, checkpoints every 10 steps: forward 33, backward 50).  With 8 lanes per
+// points, T = 91, checkpoints every 10 steps: forward 33, backward 41).  With 8 lanes per
 // agent that repeated the dynamics and the reward and shared one nearest-edge search per
-// step they took 176 and 185, and the time was 9.45 + 11.4 ms against 1.54 + 2.16 ms now;
+// step they took 176 and 185, and the time was 9.45 + 11.4 ms against 1.54 + 1.88 ms now;
 // 512 x 32 agents, T = 20: 182 + 190 against 27 + 31 us.
 //
 // Observation (optional): the forward can log the state after every step, from which
@@ -203,10 +203,13 @@ __device__ __forceinline__ void run_block(const AgentState &c, float2 u, int n, 
     o.y1 = y + iy;
 }
 
-// the state after a block of 16 steps
-__device__ __forceinline__ AgentState after_block(const StepState &o) {
-    return {row_bcast<15>(o.x1), row_bcast<15>(o.y1), row_bcast<15>(o.yaw1),
-            row_bcast<15>(o.v1), row_bcast<15>(o.sn1), row_bcast<15>(o.cs1)};
+// the state after the n steps of a block
+__device__ __forceinline__ AgentState after_block(const StepState &o, int n) {
+    if (n == kRow)
+        return {row_bcast<15>(o.x1), row_bcast<15>(o.y1), row_bcast<15>(o.yaw1),
+                row_bcast<15>(o.v1), row_bcast<15>(o.sn1), row_bcast<15>(o.cs1)};
+    return {__shfl(o.x1, n - 1, kRow), __shfl(o.y1, n - 1, kRow), __shfl(o.yaw1, n - 1, kRow),
+            __shfl(o.v1, n - 1, kRow), __shfl(o.sn1, n - 1, kRow), __shfl(o.cs1, n - 1, kRow)};
 }
 
 // ---- nearest road-edge segment
@@ -482,7 +485,7 @@ __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_fwd(SimArgs a, cons
         next = t + kRow < T ? act[(size_t)(t + kRow) * A + i] : none;
         StepState o;
         run_block<DELTA>(c, u, n, sub, L, a.dt, a.vmax, o);
-        c = after_block(o);
+        if (n == kRow) c = after_block(o, kRow);
         if (on && t % C == 0) {
             float *ck = ckpt + (size_t)(t / C) * 4 * A;
             ck[i] = o.x0;
@@ -699,13 +702,20 @@ __global__ __launch_bounds__(kObsThreads) void k_rollout_obs_grad(SimArgs a, con
 
 // Steps [Ts, Te) of the backward (all of them unless the observation's gradient og, of these
 // steps, comes in parts: then the adjoint of the state before the part is kept in `carry`).
-// steps of a backward block: whole checkpoint segments, as many as fit 16 steps, or one longer
-__host__ __device__ inline int roll_block(int C) { return C <= kRow ? kRow / C * C : C; }
+// Steps of a backward block (at most 16, a lane each).  A block starts from the checkpoint
+// before it: whole checkpoint segments need no steps in between, but leave lanes idle (six of
+// 16 with checkpoints every 10 steps); blocks of 16 take up to C - 1 steps to their start
+// first.  Of 91 steps, blocks of 16 make 6 instead of 10 (4096 x 64 agents: 2.16 -> 1.88 ms);
+// of 20, both make 2, and the steps in between are saved.
+__host__ inline int roll_block(int T, int C) {
+    const int whole = C <= kRow ? kRow / C * C : kRow;
+    return (T + kRow - 1) / kRow < (T + whole - 1) / whole ? kRow : whole;
+}
 
 template <bool DELTA, bool OBS>
 __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, const float2 *__restrict__ act,
                                                               const float *__restrict__ ckpt, int T, int C,
-                                                              int Ts, int Te,
+                                                              int B, int Ts, int Te,
                                                               const float *__restrict__ grad_r,
                                                               const float4 *__restrict__ og,
                                                               float4 *__restrict__ carry,
@@ -734,149 +744,148 @@ __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, cons
         lv = q.w;
     }
     EdgeBound bd{0.f, 0.f, 0.f, -1};
-    // blocks of whole checkpoint segments (a longer segment 16 steps at a time), last first
-    const int B = roll_block(C);
-    for (int c0 = (Te - 1) / B * B; c0 >= Ts; c0 -= B) {
-        const int c1 = min(Te, c0 + B);
-        const float *ck = ckpt + (size_t)(c0 / C) * 4 * A;
-        for (int t0 = c0 + (c1 - 1 - c0) / kRow * kRow; t0 >= c0; t0 -= kRow) {
-            const int n = min(kRow, c1 - t0), t = t0 + sub;
-            const bool on = sub < n;
-            const float gr = on ? grad_r[(size_t)t * A + i] : 0.0f;
-            float4 og_t = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (OBS && on) og_t = og[(size_t)(t - Ts) * A + i];
-            // states of the block, from the checkpoint (through the steps before the block)
-            AgentState c{ck[i], ck[A + i], ck[2 * A + i], ck[3 * A + i], 0.f, 0.f};
-            sincosf(c.yaw, &c.sn, &c.cs);
-            StepState o;
-            float2 u;
-            for (int tb = c0;; tb += kRow) {
-                u = tb + sub < c1 ? act[(size_t)(tb + sub) * A + i] : make_float2(0.f, 0.f);
-                run_block<DELTA>(c, u, tb < t0 ? kRow : n, sub, L, dt, vmax, o);
-                if (tb == t0) break;
-                c = after_block(o);
-            }
-            const EdgeChoice ch = nearest_edges(e, ls, o.x1, o.y1, on, a.R_obs, sub, bd, false);
-            // gradient of the step's reward (and observation) with respect to the state after
-            // the step
-            float gx = og_t.x, gy = og_t.y, gth = og_t.z, gv = og_t.w;
-            const float sn = o.sn1, cs = o.cs1;
-            // goal term: r = -|g'|
-            {
-                const float dxg = gxa - o.x1, dyg = gya - o.y1;
-                const float gpx = cs * dxg + sn * dyg, gpy = -sn * dxg + cs * dyg;
-                const float ng = sqrtf(gpx * gpx + gpy * gpy);
-                if (ng > 0.0f) {
-                    const float ing = __builtin_amdgcn_rcpf(ng);
-                    const float bgx = -gpx * ing * gr, bgy = -gpy * ing * gr;
-                    gx += -cs * bgx + sn * bgy;
-                    gy += -sn * bgx - cs * bgy;
-                    gth += gpy * bgx - gpx * bgy;
-                }
-            }
-            // off-road term: r = -softplus(side * |q'|), q' = a' + u e' in the ego frame
-            if (ch.q >= 0) {
-                const float4 s = e.es[ch.q];
-                const float ax = s.x - o.x1, ay = s.y - o.y1, bx = s.z - o.x1, by = s.w - o.y1;
-                const float apx = cs * ax + sn * ay, apy = -sn * ax + cs * ay;
-                const float bpx = cs * bx + sn * by, bpy = -sn * bx + cs * by;
-                const float ex = bpx - apx, ey = bpy - apy;
-                const float ee = ex * ex + ey * ey;
-                const float iee = __builtin_amdgcn_rcpf(ee);
-                float uu = ee > 0.0f ? -(apx * ex + apy * ey) * iee : 0.0f;
-                const bool cl = uu <= 0.0f || uu >= 1.0f;
-                uu = fminf(fmaxf(uu, 0.0f), 1.0f);
-                const float qx = apx + uu * ex, qy = apy + uu * ey;
-                const float d = sqrtf(qx * qx + qy * qy);
-                const float sdist = ch.side * d;
-                const float sbar = -sigmoidf(sdist) * gr;
-                const float dbar = ch.side * sbar;
-                float bqx = 0.f, bqy = 0.f;
-                if (d > 0.0f) {
-                    const float id = __builtin_amdgcn_rcpf(d);
-                    bqx = dbar * qx * id;
-                    bqy = dbar * qy * id;
-                }
-                float bapx = bqx, bapy = bqy, bex = uu * bqx, bey = uu * bqy;
-                if (!cl && ee > 0.0f) {
-                    const float ubar = bqx * ex + bqy * ey;
-                    bapx += ubar * (-ex * iee);
-                    bapy += ubar * (-ey * iee);
-                    bex += ubar * (-apx * iee - 2.0f * uu * ex * iee);
-                    bey += ubar * (-apy * iee - 2.0f * uu * ey * iee);
-                }
-                const float bbpx = bex, bbpy = bey;
-                bapx -= bex;
-                bapy -= bey;
-                const float bax = cs * bapx - sn * bapy, bay = sn * bapx + cs * bapy;
-                const float bbx = cs * bbpx - sn * bbpy, bby = sn * bbpx + cs * bbpy;
-                gx += -(bax + bbx);
-                gy += -(bay + bby);
-                gth += bapx * apy - bapy * apx + bbpx * bpy - bbpy * bpx;
-            }
-            // dynamics s_t -> s_{t+1}: coefficients of the adjoint's recursion
-            //   lth <- lth + m1 lx + m2 ly,  lv <- n1 lx + n2 ly + n3 lth + n4 lv
-            float m1 = 0.f, m2 = 0.f, n1 = 0.f, n2 = 0.f, n3 = 0.f, n4 = 1.f;
-            float c1f = 0.f, c2f = 0.f;
-            if (DELTA) {
-                // d = v dt + a dt^2/2; x += d cos(yaw); y += d sin(yaw); yaw += s d; v += a dt
-                m1 = -o.vb * o.sn0;
-                m2 = o.vb * o.cs0;
-                n1 = o.cs0 * dt;
-                n2 = o.sn0 * dt;
-                n3 = u.y * dt;
-            } else {
-                const float vb_raw = o.v0 + 0.5f * u.x * dt, vn_raw = o.v0 + u.x * dt;
-                c1f = (vb_raw > -vmax && vb_raw < vmax) ? 1.0f : 0.0f;
-                c2f = (vn_raw > -vmax && vn_raw < vmax) ? 1.0f : 0.0f;
-                m1 = -o.vb * o.sp * dt;
-                m2 = o.vb * o.cp * dt;
-                n1 = c1f * (o.cp * dt);
-                n2 = c1f * (o.sp * dt);
-                n3 = c1f * (o.cb * o.ts * iL * dt);
-                n4 = c2f;
-            }
-            if (!on) {
-                gx = gy = gth = gv = 0.f;
-                m1 = m2 = n1 = n2 = n3 = 0.f;
-                n4 = 1.f;
-            }
-            // the recursion, last step first, on all lanes of the row; a lane keeps the adjoint
-            // of the state after its step
-            float kx = 0.f, ky = 0.f, kth = 0.f, kv = 0.f;
-            each_step_down(n, [&](auto kc) {
-                constexpr int k = decltype(kc)::k;
-                lx += row_bcast<k>(gx);
-                ly += row_bcast<k>(gy);
-                lth += row_bcast<k>(gth);
-                if (OBS) lv += row_bcast<k>(gv);
-                const bool me = sub == k;
-                kx = me ? lx : kx;
-                ky = me ? ly : ky;
-                kth = me ? lth : kth;
-                kv = me ? lv : kv;
-                const float v = row_bcast<k>(n4) * lv;
-                lv = row_bcast<k>(n1) * lx + v;
-                lv = row_bcast<k>(n2) * ly + lv;
-                lv = row_bcast<k>(n3) * lth + lv;
-                lth = row_bcast<k>(m1) * lx + lth;
-                lth = row_bcast<k>(m2) * ly + lth;
-            });
-            // gradient of the step's action
-            float2 ga;
-            if (DELTA) {
-                const float bdist = kx * o.cs0 + ky * o.sn0 + kth * u.y;
-                ga = make_float2(kv * dt + bdist * 0.5f * dt * dt, kth * o.vb);
-            } else {
-                const float sec2 = 1.0f + o.ts * o.ts;
-                const float dbeta = 0.5f * sec2 * __builtin_amdgcn_rcpf(1.0f + 0.25f * o.ts * o.ts);
-                const float bvb = kx * o.cp * dt + ky * o.sp * dt + kth * o.cb * o.ts * iL * dt;
-                const float bphi = -kx * o.vb * o.sp * dt + ky * o.vb * o.cp * dt;
-                const float bbeta = bphi - kth * o.vb * o.sb * o.ts * iL * dt;
-                ga = make_float2(bvb * c1f * 0.5f * dt + kv * c2f * dt, kth * o.vb * o.cb * sec2 * iL * dt + bbeta * dbeta);
-            }
-            if (on) grad_a[(size_t)t * A + i] = ga;
+    // blocks of B steps, last one first
+    for (int t0 = (Te - 1) / B * B; t0 >= Ts; t0 -= B) {
+        const int n = min(B, Te - t0), t = t0 + sub;
+        const bool on = sub < n;
+        const float gr = on ? grad_r[(size_t)t * A + i] : 0.0f;
+        float4 og_t = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (OBS && on) og_t = og[(size_t)(t - Ts) * A + i];
+        // states of the block, from the checkpoint before it
+        const float *ck = ckpt + (size_t)(t0 / C) * 4 * A;
+        AgentState c{ck[i], ck[A + i], ck[2 * A + i], ck[3 * A + i], 0.f, 0.f};
+        sincosf(c.yaw, &c.sn, &c.cs);
+        StepState o;
+        float2 u;
+        for (int tb = t0 / C * C;;) {
+            const bool own = tb == t0;
+            const int m = own ? n : min(kRow, t0 - tb);
+            u = sub < m ? act[(size_t)(tb + sub) * A + i] : make_float2(0.f, 0.f);
+            run_block<DELTA>(c, u, m, sub, L, dt, vmax, o);
+            if (own) break;
+            c = after_block(o, m);
+            tb += m;
         }
+        const EdgeChoice ch = nearest_edges(e, ls, o.x1, o.y1, on, a.R_obs, sub, bd, false);
+        // gradient of the step's reward (and observation) with respect to the state after
+        // the step
+        float gx = og_t.x, gy = og_t.y, gth = og_t.z, gv = og_t.w;
+        const float sn = o.sn1, cs = o.cs1;
+        // goal term: r = -|g'|
+        {
+            const float dxg = gxa - o.x1, dyg = gya - o.y1;
+            const float gpx = cs * dxg + sn * dyg, gpy = -sn * dxg + cs * dyg;
+            const float ng = sqrtf(gpx * gpx + gpy * gpy);
+            if (ng > 0.0f) {
+                const float ing = __builtin_amdgcn_rcpf(ng);
+                const float bgx = -gpx * ing * gr, bgy = -gpy * ing * gr;
+                gx += -cs * bgx + sn * bgy;
+                gy += -sn * bgx - cs * bgy;
+                gth += gpy * bgx - gpx * bgy;
+            }
+        }
+        // off-road term: r = -softplus(side * |q'|), q' = a' + u e' in the ego frame
+        if (ch.q >= 0) {
+            const float4 s = e.es[ch.q];
+            const float ax = s.x - o.x1, ay = s.y - o.y1, bx = s.z - o.x1, by = s.w - o.y1;
+            const float apx = cs * ax + sn * ay, apy = -sn * ax + cs * ay;
+            const float bpx = cs * bx + sn * by, bpy = -sn * bx + cs * by;
+            const float ex = bpx - apx, ey = bpy - apy;
+            const float ee = ex * ex + ey * ey;
+            const float iee = __builtin_amdgcn_rcpf(ee);
+            float uu = ee > 0.0f ? -(apx * ex + apy * ey) * iee : 0.0f;
+            const bool cl = uu <= 0.0f || uu >= 1.0f;
+            uu = fminf(fmaxf(uu, 0.0f), 1.0f);
+            const float qx = apx + uu * ex, qy = apy + uu * ey;
+            const float d = sqrtf(qx * qx + qy * qy);
+            const float sdist = ch.side * d;
+            const float sbar = -sigmoidf(sdist) * gr;
+            const float dbar = ch.side * sbar;
+            float bqx = 0.f, bqy = 0.f;
+            if (d > 0.0f) {
+                const float id = __builtin_amdgcn_rcpf(d);
+                bqx = dbar * qx * id;
+                bqy = dbar * qy * id;
+            }
+            float bapx = bqx, bapy = bqy, bex = uu * bqx, bey = uu * bqy;
+            if (!cl && ee > 0.0f) {
+                const float ubar = bqx * ex + bqy * ey;
+                bapx += ubar * (-ex * iee);
+                bapy += ubar * (-ey * iee);
+                bex += ubar * (-apx * iee - 2.0f * uu * ex * iee);
+                bey += ubar * (-apy * iee - 2.0f * uu * ey * iee);
+            }
+            const float bbpx = bex, bbpy = bey;
+            bapx -= bex;
+            bapy -= bey;
+            const float bax = cs * bapx - sn * bapy, bay = sn * bapx + cs * bapy;
+            const float bbx = cs * bbpx - sn * bbpy, bby = sn * bbpx + cs * bbpy;
+            gx += -(bax + bbx);
+            gy += -(bay + bby);
+            gth += bapx * apy - bapy * apx + bbpx * bpy - bbpy * bpx;
+        }
+        // dynamics s_t -> s_{t+1}: coefficients of the adjoint's recursion
+        //   lth <- lth + m1 lx + m2 ly,  lv <- n1 lx + n2 ly + n3 lth + n4 lv
+        float m1 = 0.f, m2 = 0.f, n1 = 0.f, n2 = 0.f, n3 = 0.f, n4 = 1.f;
+        float c1f = 0.f, c2f = 0.f;
+        if (DELTA) {
+            // d = v dt + a dt^2/2; x += d cos(yaw); y += d sin(yaw); yaw += s d; v += a dt
+            m1 = -o.vb * o.sn0;
+            m2 = o.vb * o.cs0;
+            n1 = o.cs0 * dt;
+            n2 = o.sn0 * dt;
+            n3 = u.y * dt;
+        } else {
+            const float vb_raw = o.v0 + 0.5f * u.x * dt, vn_raw = o.v0 + u.x * dt;
+            c1f = (vb_raw > -vmax && vb_raw < vmax) ? 1.0f : 0.0f;
+            c2f = (vn_raw > -vmax && vn_raw < vmax) ? 1.0f : 0.0f;
+            m1 = -o.vb * o.sp * dt;
+            m2 = o.vb * o.cp * dt;
+            n1 = c1f * (o.cp * dt);
+            n2 = c1f * (o.sp * dt);
+            n3 = c1f * (o.cb * o.ts * iL * dt);
+            n4 = c2f;
+        }
+        if (!on) {
+            gx = gy = gth = gv = 0.f;
+            m1 = m2 = n1 = n2 = n3 = 0.f;
+            n4 = 1.f;
+        }
+        // the recursion, last step first, on all lanes of the row; a lane keeps the adjoint
+        // of the state after its step
+        float kx = 0.f, ky = 0.f, kth = 0.f, kv = 0.f;
+        each_step_down(n, [&](auto kc) {
+            constexpr int k = decltype(kc)::k;
+            lx += row_bcast<k>(gx);
+            ly += row_bcast<k>(gy);
+            lth += row_bcast<k>(gth);
+            if (OBS) lv += row_bcast<k>(gv);
+            const bool me = sub == k;
+            kx = me ? lx : kx;
+            ky = me ? ly : ky;
+            kth = me ? lth : kth;
+            kv = me ? lv : kv;
+            const float v = row_bcast<k>(n4) * lv;
+            lv = row_bcast<k>(n1) * lx + v;
+            lv = row_bcast<k>(n2) * ly + lv;
+            lv = row_bcast<k>(n3) * lth + lv;
+            lth = row_bcast<k>(m1) * lx + lth;
+            lth = row_bcast<k>(m2) * ly + lth;
+        });
+        // gradient of the step's action
+        float2 ga;
+        if (DELTA) {
+            const float bdist = kx * o.cs0 + ky * o.sn0 + kth * u.y;
+            ga = make_float2(kv * dt + bdist * 0.5f * dt * dt, kth * o.vb);
+        } else {
+            const float sec2 = 1.0f + o.ts * o.ts;
+            const float dbeta = 0.5f * sec2 * __builtin_amdgcn_rcpf(1.0f + 0.25f * o.ts * o.ts);
+            const float bvb = kx * o.cp * dt + ky * o.sp * dt + kth * o.cb * o.ts * iL * dt;
+            const float bphi = -kx * o.vb * o.sp * dt + ky * o.vb * o.cp * dt;
+            const float bbeta = bphi - kth * o.vb * o.sb * o.ts * iL * dt;
+            ga = make_float2(bvb * c1f * 0.5f * dt + kv * c2f * dt, kth * o.vb * o.cb * sec2 * iL * dt + bbeta * dbeta);
+        }
+        if (on) grad_a[(size_t)t * A + i] = ga;
     }
     if (OBS && Ts > 0) {
         if (sub == 0) carry[i] = make_float4(lx, ly, lth, lv);
@@ -1002,13 +1011,14 @@ template <bool DELTA>
 static hipError_t launch_bwd(const SimArgs &a, const float2 *actions, const float *ckpt, int T, int C,
                              const float *grad_rewards, const float *grad_obs, const float *states, int max_agents,
                              float2 *grad_actions, float *grad_state0, hipStream_t s) {
+    const int B = roll_block(T, C);
     if (!grad_obs) {
         hipLaunchKernelGGL((k_rollout_bwd<DELTA, false>), dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a, actions,
-                           ckpt, T, C, 0, T, grad_rewards, nullptr, nullptr, grad_actions, grad_state0);
+                           ckpt, T, C, B, 0, T, grad_rewards, nullptr, nullptr, grad_actions, grad_state0);
         return hipGetLastError();
     }
     // the observation's gradient in parts of as many whole blocks as the workspace holds
-    const int B = roll_block(C), part = std::max(1, obs_grad_steps(a.A) / B) * B;
+    const int part = obs_grad_steps(a.A) / B * B;
     int cols = 8;  // columns of a wave: as many as agents, a power of two
     while (cols < kWave && cols < max_agents) cols *= 2;
     const int rows = kWave / cols;
@@ -1023,7 +1033,7 @@ static hipError_t launch_bwd(const SimArgs &a, const float2 *actions, const floa
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((k_rollout_bwd<DELTA, true>), dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a, actions,
-                           ckpt, T, C, Ts, Te, grad_rewards, a.obs_grad, a.carry, grad_actions, grad_state0);
+                           ckpt, T, C, B, Ts, Te, grad_rewards, a.obs_grad, a.carry, grad_actions, grad_state0);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
