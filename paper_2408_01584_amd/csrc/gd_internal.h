@@ -174,10 +174,8 @@ __device__ __forceinline__ void delta_model(float &x, float &y, float &yaw, floa
 // Cell of coordinate v on an axis of n cells (clamped; NaN maps to cell 0).  Monotone
 // non-decreasing in v, which is what makes range queries over cells exact.
 __device__ __forceinline__ int cell_coord(float v, float o, float inv_cs, int n) {
-    float f = floorf((v - o) * inv_cs);
-    if (!(f >= 0.0f)) return 0;
-    if (f >= (float)n) return n - 1;
-    return (int)f;
+    // (fmaxf takes a NaN to 0; the conversion truncates, the floor of what is not negative)
+    return (int)fminf(fmaxf((v - o) * inv_cs, 0.0f), (float)(n - 1));
 }
 
 // Inclusive prefix sum over the 64 lanes with DPP moves: shifts by 1, 2, 4, 8 inside each
