@@ -192,6 +192,9 @@ struct AgentField {
 // Road modes of the step kernel: where phase 5 reads the road, and the index width.
 enum RoadMode { kRoadGlobal32 = 0, kRoadGlobal16 = 1, kRoadLds = 2 };
 
+using u32x4 = __attribute__((ext_vector_type(4))) unsigned;
+constexpr int kBufferFlags = 0x00027000;  // raw 32-bit data
+constexpr int kNoSlot = 0x7ffffff;        // past the end of every descriptor
 constexpr int kMates = 4;  // keys of a bin read together when its points are ranked
 
 template <int NB, int RM>
@@ -829,11 +832,8 @@ __global__ __launch_bounds__(1024) void k_step(SimArgs a, StepCtl c) {
         float kk = -1.0f;  // key of slot K - 1, on the lane that ranks it
         if (lane < kMates - 1) skey[nstaged + lane] = INFINITY;
         wave_sync();
-        for (int p = lane; p < nstaged; p += kWave) {
-            const float k = skey[p];
-            const int q = sq[p];
-            const float2 pt = rxy[q];
-            const float2 x2 = aux[q];
+        // slot of staged point p with key k, whose index (| type << 24) is `bits`
+        auto slot_of = [&](int p, float k, int bits) {
             const int b = bin_of(k, bscale, NB);
             const int lo = hist[b - 1];
             const int hi = hist[b];
@@ -849,24 +849,64 @@ __global__ __launch_bounds__(1024) void k_step(SimArgs a, StepCtl c) {
 #pragma unroll
             for (int m = 0; m < kMates; m++) mate(mk[m]);
             for (int m = lo + kMates; m < hi; m++) mate(skey[m]);
-            const int bits = __float_as_int(x2.y);
             if (tie) {
                 const int my_idx = bits & 0xffffff;
                 for (int m = lo; m < hi; m++)
                     if (m != p && skey[m] == k)
                         rank += (int)((__float_as_int(aux[sq[m]].y) & 0xffffff) < my_idx);
             }
-            const int fin = lo + rank;
-            if (fin < direct_end) {
-                const float dx = pt.x - px, dy = pt.y - py;
-                float dd = x2.x - yaw_w;
-                const float up = dd < -3.14159265358979323846f ? 6.283185307179586f : 0.0f;
-                dd += dd >= 3.14159265358979323846f ? -6.283185307179586f : up;
-                const unsigned at = (unsigned)fin;  // (a 32-bit offset from a scalar base)
-                out[at] = make_float4(csy * dx + sny * dy, -sny * dx + csy * dy, dd, (float)((unsigned)bits >> 24));
-                if (oidx) oidx[at] = bits & 0xffffff;
+            return lo + rank;
+        };
+        auto row_of = [&](float2 pt, float2 x2) {
+            const float dx = pt.x - px, dy = pt.y - py;
+            float dd = x2.x - yaw_w;
+            const float up = dd < -3.14159265358979323846f ? 6.283185307179586f : 0.0f;
+            dd += dd >= 3.14159265358979323846f ? -6.283185307179586f : up;
+            // (the products' rounding spelled out: both loops below give the same bits)
+            return make_float4(__builtin_fmaf(csy, dx, sny * dy), __builtin_fmaf(csy, dy, -(sny * dx)), dd,
+                               (float)(__float_as_uint(x2.y) >> 24));
+        };
+        if (STAGED) {
+            for (int p = lane; p < nstaged; p += kWave) {
+                const float k = skey[p];
+                const int q = sq[p];
+                const float2 pt = rxy[q];
+                const float2 x2 = aux[q];
+                const int fin = slot_of(p, k, __float_as_int(x2.y));
+                if (fin < direct_end) {
+                    const unsigned at = (unsigned)fin;  // (a 32-bit offset from a scalar base)
+                    const int bits = __float_as_int(x2.y);
+                    out[at] = row_of(pt, x2);
+                    if (oidx) oidx[at] = bits & 0xffffff;
+                }
+                kk = fin == K - 1 ? k : kk;
             }
-            kk = fin == K - 1 ? k : kk;
+        } else if (nstaged > 0) {
+            // A read through the caches that follows a wave's stores waits for them to complete, so
+            // each pass's points are read before the stores of the pass before.  The stores go
+            // through buffer descriptors, which drop slots past their end: after stores under a
+            // branch, whose number is not known, a read waits for every one of them (1024 uneven
+            // worlds: 212 us, read ahead 209, with these stores 204; with the road in LDS there
+            // is nothing to wait for, and the branch is 1 % faster).
+            const auto rows = __builtin_amdgcn_make_buffer_rsrc(out, 0, direct_end * 16, kBufferFlags);
+            const auto idxs = __builtin_amdgcn_make_buffer_rsrc(oidx, 0, oidx ? direct_end * 4 : 0, kBufferFlags);
+            int q = sq[min(lane, nstaged - 1)];
+            float2 npt = rxy[q], nx2 = aux[q];
+            for (int p0 = 0; p0 < nstaged; p0 += kWave) {
+                const int p = min(p0 + lane, nstaged - 1);
+                const float k = skey[p];
+                const float2 pt = npt, x2 = nx2;
+                q = sq[min(p + kWave, nstaged - 1)];
+                npt = rxy[q];
+                nx2 = aux[q];
+                const int slot = slot_of(p, k, __float_as_int(x2.y));
+                const int fin = p0 + lane < nstaged ? slot : kNoSlot;
+                const float4 r = row_of(pt, x2);
+                const u32x4 row = {__float_as_uint(r.x), __float_as_uint(r.y), __float_as_uint(r.z), __float_as_uint(r.w)};
+                __builtin_amdgcn_raw_buffer_store_b128(row, rows, fin * 16, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x2.y) & 0xffffffu, idxs, fin * 4, 0, 0);
+                kk = fin == K - 1 ? k : kk;
+            }
         }
         // slots beyond the points in the radius
         for (int s = nsel + lane; s < K; s += kWave) {
