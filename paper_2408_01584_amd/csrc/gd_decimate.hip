@@ -9,12 +9,13 @@
 // decide which points survive, so they are computed in binary32 with a fixed operation
 // order (no contraction).
 //
-// A polyline is taken by a wave (short ones) or a workgroup, with its points, areas and
-// links (a doubly linked list of the surviving points) in LDS; longer ones keep areas and
-// links in the caller's workspace.  The removals are sequential by definition, and taking
-// them one at a time is a chain of LDS round trips and wave minima (about 1250 cycles
-// each).  Here a round takes all the next removals that are certain at once.
+// The removals are sequential by definition, and taking them one at a time is a chain of LDS
+// round trips and wave minima (about 1250 cycles each).  Up to 4096 points a polyline is
+// taken by chunks that run ahead of each other (vw_chunks: a wave up to 512 points, a workgroup
+// beyond), longer ones and the few that the chunks take out of order round by round
+// (vw_polyline, areas and links in LDS up to 6144 points, else in the caller's workspace).
 //
+// Rounds: every removal that is certain to be among the next ones is taken at once.
 // A key is (area bits, index): areas are >= 0, so their bit patterns order like the values;
 // end points carry +inf and removed points a pattern above it.  Each thread owns every TH-th
 // point and offers its smallest key, its level.  If a neighbour's area falls below the
@@ -29,21 +30,27 @@
 // each other's areas.  The smallest offer has no conflict and is below T, so every round
 // removes a point.
 //
-// Bound by the vector instructions and the latency of the rounds (about 200 for a polyline of
-// 2900 points).  2560 polylines of 2600 points on average (64 maps sampled every 0.1 m, 97 %
-// of the points removed): one point at a time 9.2 ms, rounds that stop at the first cascade
-// (700 of them) 7.9 ms, with cascades 1.64 ms; 128 or 512 threads per polyline instead of
-// 256: 2.3 ms both.  16 B of LDS per point let a compute unit hold three polylines.
+// 2560 polylines of 2600 points on average (64 maps sampled every 0.1 m, 97 % of the points
+// removed): one point at a time 9.2 ms, rounds 1.64 ms (190 of 4500 cycles), chunks 0.81 ms.
+// On straight lines, whose areas are all equal, nothing can be taken at the same time: 2600
+// points 8.1 ms one at a time, 8.6 ms by chunks, 36 ms by rounds; 500 points 1.5, 0.5 and
+// 2.0 ms.
 #include "gd_internal.h"
 
 namespace gdk {
 
-__device__ __forceinline__ float dec_area(const float *x, const float *y, int a, int b, int c) {
+__device__ __forceinline__ float dec_area(float2 a, float2 b, float2 c) {
 #pragma clang fp contract(off)
-    const float ux = x[b] - x[a], uy = y[b] - y[a];
-    const float vx = x[c] - x[a], vy = y[c] - y[a];
+    const float ux = b.x - a.x, uy = b.y - a.y;
+    const float vx = c.x - a.x, vy = c.y - a.y;
     const float p = ux * vy, q = uy * vx;
     return 0.5f * fabsf(p - q);
+}
+__device__ __forceinline__ float2 dec_point(const float *x, const float *y, int k) {
+    return make_float2(x[(unsigned)k], y[(unsigned)k]);  // (32-bit offsets from scalar bases)
+}
+__device__ __forceinline__ float dec_area(const float *x, const float *y, int a, int b, int c) {
+    return dec_area(dec_point(x, y, a), dec_point(x, y, b), dec_point(x, y, c));
 }
 
 // minimum over the wave: row minima by DPP row rotations, then the four rows' minima
@@ -65,6 +72,7 @@ __device__ __forceinline__ void wave_sync() {
 
 // area bits of a removed point: above every area, +inf (end points) and every NaN
 constexpr unsigned kRemoved = 0xffffffffu;
+constexpr unsigned kSign = 0x80000000u;
 
 using u64 = unsigned long long;
 __device__ __forceinline__ u64 dec_key(float area, int k) { return ((u64)__float_as_uint(area) << 32) | (unsigned)k; }
@@ -85,13 +93,35 @@ __device__ __forceinline__ void dec_sync() {
     else __syncthreads();
 }
 
+// Outputs of a polyline whose removed points have the sign bit of their area set (areas are
+// >= 0, end points +inf).
+template <int TH, typename Link>
+__device__ __forceinline__ void write_kept(int n, int tid, const float *X, const float *Y, const float *AR,
+                                           const Link *PRV, const Link *NXT, uint8_t *keep, float *dir) {
+    for (int k = tid; k < n; k += TH) {
+        const bool kept = !(__float_as_uint(AR[k]) & kSign);
+        float d = 0.0f;
+        if (kept) {
+            const int j = (int)NXT[k];
+            if (j < n) {
+                d = atan2f(Y[j] - Y[k], X[j] - X[k]);
+            } else if (k > 0) {
+                const int pk = (int)PRV[k];
+                d = atan2f(Y[k] - Y[pk], X[k] - X[pk]);
+            }
+        }
+        keep[k] = kept ? 1 : 0;
+        dir[k] = d;
+    }
+}
+
 // One polyline of n points, X/Y its coordinates, AR/PRV/NXT its areas and links (local
 // indices), keep/dir the outputs at its first point; tid = 0 .. TH - 1.  Removed points are
 // marked in AR only (kRemoved), so that the removals touch no global memory when AR and the
 // links sit in LDS; keep is written at the end.  PADDED: AR has room up to the next multiple of
 // kDecUnroll * TH points.
 template <int TH, typename Link, bool PADDED>
-__device__ void vw_polyline(int n, int tid, DecShared<TH> &sh, const float *X, const float *Y, float *AR, Link *PRV,
+__device__ __forceinline__ void vw_polyline(int n, int tid, DecShared<TH> &sh, const float *X, const float *Y, float *AR, Link *PRV,
                             Link *NXT, float min_area, uint8_t *keep, float *dir) {
     for (int k = tid; k < n; k += TH) {
         PRV[k] = (Link)(k - 1);
@@ -186,20 +216,206 @@ __device__ void vw_polyline(int n, int tid, DecShared<TH> &sh, const float *X, c
         }
         dec_sync<TH>();
     }
+    write_kept<TH>(n, tid, X, Y, AR, PRV, NXT, keep, dir);
+}
+
+// ---- the same removals, by chunks of the polyline that run ahead of each other
+// The order of two removals matters only if they are neighbours.  Each thread owns a chunk of
+// consecutive surviving points and takes its own next removals as long as their keys are
+// below the smallest keys of the chunks around it, as far as the next four points on each
+// side reach: between two chunks that take removals at the same time there are four points
+// or more, and each touches two of them.  What a thread cannot know is whether a cascade will
+// come through these chunks with smaller keys later.  That is checked instead:
+// the time of a removal is its key, or the time of the removal that caused it if that is
+// larger (a cascade), and each gap between surviving points knows the time of the last
+// removal in it.  A removal reads the point's two gaps and changes the areas of its two
+// neighbours, so for it to come in order
+//   - the removals in its own two gaps must not be later: they are not, one of them caused it
+//     if the point's key is smaller;
+//   - the removals in the two gaps beyond its neighbours must not be later;
+//   - a neighbour with a key before this time would have gone first, unless it lies, like
+//     the point, at the gap of the cascade that this removal belongs to.
+// When every removal passes, any two that touch each other's points were taken in the order of
+// their times, and no point was passed over at its time, so sorted by their times they are
+// the removals of the definition.  When one does not pass, the polyline is taken again with
+// larger chunks, then by vw_polyline: never on straight lines and circles, on 1 of 7000 noisy curves, on up to 19 %
+// of random points on a few integer positions.  (1.1 million polylines compared with the
+// definition on the CPU.)  When an eighth of the points is gone the chunks are dealt out anew.
+//
+// Bound by the latency of a removal (about 1700 cycles: six dependent LDS reads, the
+// coordinates through the caches, the chunk's next key) times the 150 or so that follow one
+// another on some thread of a polyline of 2600 points in 50 rounds.  12 B of LDS per point let
+// a compute unit hold three polylines; with the coordinates in LDS too (20 B) it took as
+// long.  Chunks of 4 or 6 points and deals after a quarter or a half of them were 1 to 20 %
+// slower, mostly for the polylines taken again: those are first taken with larger chunks.
+constexpr int kChunk = 5, kChunkAgain = 12;  // points of a chunk, at least: at first, and when taken again
+constexpr int kReach = 4;  // points between two chunks that take removals
+constexpr int kNear = 2;   // chunks on each side in which it looks for them
+constexpr int kOwn = 16;   // points of its chunk that a thread keeps in registers
+constexpr unsigned short kNoGap = 0xffff;
+
+template <int TH>
+struct ChunkShared {
+    u64 first[TH];  // smallest key of each chunk
+    unsigned short count[TH];  // its surviving points
+    int part[TH / kWave];
+    int removed, wrong;
+};
+
+template <int TH>
+union DecAnyShared {
+    DecShared<TH> rounds;
+    ChunkShared<TH> chunks;
+};
+
+// G: by point, the point whose key is the time of the last removal in the gap after it (its
+// area stays in AR, with the sign bit set); LST: the surviving points in order.  False: a
+// removal was out of order, nothing is valid.  At most MOST points.
+template <int TH, int MOST>
+__device__ __forceinline__ bool vw_chunks(int n, int tid, ChunkShared<TH> &sh, const float *X, const float *Y, float *AR,
+                          unsigned short *PRV, unsigned short *NXT, unsigned short *G, unsigned short *LST,
+                          float min_area, int chunk) {
     for (int k = tid; k < n; k += TH) {
-        const bool kept = __float_as_uint(AR[k]) != kRemoved;
-        float d = 0.0f;
-        if (kept) {
-            const int j = (int)NXT[k];
-            if (j < n) {
-                d = atan2f(Y[j] - Y[k], X[j] - X[k]);
-            } else if (k > 0) {
-                const int pk = (int)PRV[k];
-                d = atan2f(Y[k] - Y[pk], X[k] - X[pk]);
+        PRV[k] = (unsigned short)(k - 1);
+        NXT[k] = (unsigned short)(k + 1);
+        AR[k] = (k > 0 && k < n - 1) ? dec_area(X, Y, k - 1, k, k + 1) : INFINITY;
+        G[k] = kNoGap;
+        LST[k] = (unsigned short)k;
+    }
+    if (tid == 0) {
+        sh.removed = sh.wrong = 0;
+    }
+    dec_sync<TH>();
+    const unsigned lim = __float_as_uint(min_area);  // areas >= 0 order like their bits
+    auto gap = [&](int k) -> u64 {  // (no branch: the reads of a removal go out together)
+        const int g = G[k], h = g == kNoGap ? 0 : g;
+        const u64 t = ((u64)(__float_as_uint(AR[h]) & ~kSign) << 32) | (unsigned)g;
+        return g == kNoGap ? 0ull : t;
+    };
+    int gone = 0;  // removals so far
+    // (every part but the last removes a point, and every round but the last of a part)
+    for (;;) {
+        const int m = n - gone, start = gone;
+        const int chunks = max(1, min(TH, m / chunk)), per = m / chunks, rest = m % chunks;
+        const bool mine = tid < chunks;
+        const int c0 = mine ? tid * per + min(tid, rest) : 0, c1 = mine ? c0 + per + (tid < rest) : 0;
+        const int lo = mine ? (int)LST[c0] : 0, hi = mine ? (int)LST[c1 - 1] : 0;
+        int count = c1 - c0;
+        // the chunk's smallest key (removed points have the sign bit, above every limit); its
+        // first points are kept in registers
+        int own[kOwn];
+#pragma unroll
+        for (int u = 0; u < kOwn; u++) own[u] = LST[max(min(c0 + u, c1 - 1), 0)];
+        auto smallest = [&]() -> u64 {
+            unsigned a = lim;
+            int p = -1;
+            auto take = [&](auto first) {
+                unsigned v[kOwn / 2];
+#pragma unroll
+                for (int u = 0; u < kOwn / 2; u++) v[u] = __float_as_uint(AR[own[first() + u]]);
+#pragma unroll
+                for (int u = 0; u < kOwn / 2; u++) {
+                    p = v[u] < a ? own[first() + u] : p;
+                    a = min(a, v[u]);
+                }
+            };
+            take([] { return 0; });
+            if (per >= kOwn / 2) {
+                take([] { return kOwn / 2; });
+                for (int j = c0 + kOwn; j < c1; j++) {
+                    const int k = LST[j];
+                    const unsigned w = __float_as_uint(AR[k]);
+                    p = w < a ? k : p;
+                    a = min(a, w);
+                }
             }
+            return p < 0 ? ~0ull : ((u64)a << 32) | (unsigned)p;
+        };
+        bool wrong = false;
+        for (;;) {
+            u64 key = smallest();
+            sh.first[tid] = key;
+            sh.count[tid] = (unsigned short)count;
+            dec_sync<TH>();
+            // the chunks around this one, kNear on each side read together; where fewer than
+            // kReach points are left in them the thread waits for the next deal
+            u64 bound = 0ull;
+            if (mine) {
+                u64 before[kNear], after[kNear];
+                int nb[kNear], na[kNear];
+#pragma unroll
+                for (int u = 0; u < kNear; u++) {
+                    const int cb = max(tid - 1 - u, 0), ca = min(tid + 1 + u, chunks - 1);
+                    before[u] = sh.first[cb];
+                    nb[u] = sh.count[cb];
+                    after[u] = sh.first[ca];
+                    na[u] = sh.count[ca];
+                }
+                bound = ~0ull;
+                int seenb = 0, seena = 0;
+#pragma unroll
+                for (int u = 0; u < kNear; u++) {
+                    if (tid - 1 - u >= 0 && seenb < kReach) bound = min(bound, before[u]);
+                    if (tid + 1 + u < chunks && seena < kReach) bound = min(bound, after[u]);
+                    seenb += nb[u];
+                    seena += na[u];
+                }
+                if ((tid > kNear && seenb < kReach) || (tid + 1 + kNear < chunks && seena < kReach)) bound = 0ull;
+            }
+            int did = 0;
+            while (key < bound) {
+                const int p = (int)(unsigned)key;
+                const int l = PRV[p], r = NXT[p];
+                const bool inl = l > 0, inr = r < n - 1;
+                const int bl = PRV[l], br = NXT[r], l2 = inl ? bl : l, r2 = inr ? br : r;
+                const float2 xl2 = dec_point(X, Y, l2), xl = dec_point(X, Y, l);
+                const float2 xr = dec_point(X, Y, r), xr2 = dec_point(X, Y, r2);
+                const float nl = dec_area(xl2, xl, xr), nr = dec_area(xl, xr, xr2);
+                const u64 gl = gap(l), gp = gap(p), gl2 = gap(l2), gr = gap(r);
+                const u64 time = max(key, max(gl, gp));
+                const u64 kl = dec_key(AR[l], l), kr = dec_key(AR[r], r);
+                wrong |= (inl & ((time < gl2) | ((kl < time) & (gl != time)))) |
+                         (inr & ((time < gr) | ((kr < time) & (gp != time))));
+                AR[p] = __uint_as_float((unsigned)(key >> 32) | kSign);
+                NXT[l] = (unsigned short)r;
+                PRV[r] = (unsigned short)l;
+                G[l] = (unsigned short)time;
+                if (inl) AR[l] = nl;
+                if (inr) AR[r] = nr;
+                // a neighbour in another chunk is taken there (keys from the limit on never)
+                if (inl && l < lo) bound = min(bound, dec_key(nl, l));
+                if (inr && r > hi) bound = min(bound, dec_key(nr, r));
+                did++;
+                key = smallest();
+            }
+            count -= did;
+            if (did) atomicAdd(&sh.removed, did);
+            if (wrong) sh.wrong = 1;
+            dec_sync<TH>();
+            const bool idle = sh.removed == gone;
+            gone = sh.removed;
+            if (sh.wrong) return false;
+            if (idle || (gone - start) * 8 >= m) break;
         }
-        keep[k] = kept ? 1 : 0;
-        dir[k] = d;
+        if (gone == start) return true;
+        // the surviving points in order: a thread counts those of a stretch of the polyline (of an
+        // odd length: lanes read different banks)
+        const int len = ((n + TH - 1) / TH) | 1, s0 = tid * len, s1 = min(n, s0 + len);
+        constexpr int kStretch = MOST / TH + 1;
+        unsigned there = 0;
+#pragma unroll
+        for (int u = 0; u < kStretch; u++) {
+            const int k = min(s0 + u, n - 1);
+            there |= (unsigned)(s0 + u < s1 && !(__float_as_uint(AR[k]) & kSign)) << u;
+        }
+        const int alive = __popc(there);
+        const int upto = wave_incl_scan(alive);
+        if ((tid & (kWave - 1)) == kWave - 1) sh.part[tid / kWave] = upto;
+        dec_sync<TH>();
+        int at = upto - alive;
+        for (int w = 0; w < tid / kWave; w++) at += sh.part[w];
+        for (; there; there &= there - 1) LST[at++] = (unsigned short)(s0 + __ffs((int)there) - 1);
+        dec_sync<TH>();
     }
 }
 
@@ -222,16 +438,16 @@ __device__ __forceinline__ int dec_range(const DecArgs &a, int pl, int &s) {
 }
 
 constexpr int kDecShort = 512;    // points of a polyline taken by one wave (8 per lane)
-constexpr int kDecThreads = 256;  // threads of a longer one
-constexpr int kDecPoints = 3072;  // points staged in LDS (16 B each): three workgroups of a compute unit
-constexpr int kDecLinks = 6144;   // points whose areas and links fit the same LDS (8 B each)
+constexpr int kDecThreads = 256;   // threads of a longer one
+constexpr int kDecChunked = 4096;  // points taken by chunks (12 B of LDS each)
+constexpr int kDecLinks = 6144;   // points whose areas and links fit the LDS (8 B each)
 
 // Polylines of up to kDecShort points, a wave each.
 constexpr int kDecShortWaves = 4;
 __global__ __launch_bounds__(kDecShortWaves *kWave) void k_decimate_short(DecArgs a) {
-    __shared__ float sx[kDecShortWaves][kDecShort], sy[kDecShortWaves][kDecShort], sa[kDecShortWaves][kDecShort];
-    __shared__ unsigned short sp[kDecShortWaves][kDecShort], sn[kDecShortWaves][kDecShort];
-    __shared__ DecShared<kWave> shared[kDecShortWaves];
+    __shared__ float areas[kDecShortWaves][kDecShort];
+    __shared__ unsigned short links[kDecShortWaves][4 * kDecShort];
+    __shared__ DecAnyShared<kWave> shared[kDecShortWaves];
     const int g = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int tid = threadIdx.x % kWave;
     const int pl = blockIdx.x * kDecShortWaves + g;
@@ -239,41 +455,44 @@ __global__ __launch_bounds__(kDecShortWaves *kWave) void k_decimate_short(DecArg
     int s;
     const int n = dec_range(a, pl, s);
     if (n < 1 || n > kDecShort) return;
-    for (int k = tid; k < n; k += kWave) {
-        sx[g][k] = a.x[s + k];
-        sy[g][k] = a.y[s + k];
+    const float *x = a.x + s, *y = a.y + s;
+    unsigned short *prv = links[g], *nxt = prv + kDecShort;
+    for (int chunk = kChunk; chunk <= kChunkAgain; chunk += kChunkAgain - kChunk) {
+        if (vw_chunks<kWave, kDecShort>(n, tid, shared[g].chunks, x, y, areas[g], prv, nxt, nxt + kDecShort,
+                                        nxt + 2 * kDecShort, a.min_area, chunk)) {
+            write_kept<kWave>(n, tid, x, y, areas[g], prv, nxt, a.keep + s, a.dir + s);
+            return;
+        }
+        wave_sync();
     }
-    wave_sync();
-    vw_polyline<kWave, unsigned short, true>(n, tid, shared[g], sx[g], sy[g], sa[g], sp[g], sn[g], a.min_area, a.keep + s,
-                                       a.dir + s);
+    vw_polyline<kWave, unsigned short, true>(n, tid, shared[g].rounds, x, y, areas[g], prv, nxt, a.min_area, a.keep + s, a.dir + s);
 }
 
-// Polylines of up to kDecLinks points, a workgroup each: with their points in LDS when they
-// fit, else the points are read through the caches.
+// Polylines of up to kDecLinks points, a workgroup each: by chunks up to kDecChunked points,
+// round by round beyond and where the chunks were out of order.
 __global__ __launch_bounds__(kDecThreads) void k_decimate(DecArgs a) {
-    __shared__ float mem[kDecPoints * 4];
-    __shared__ DecShared<kDecThreads> shared;
-    static_assert(kDecPoints * 4 == kDecLinks * 2, "one block of LDS");
-    static_assert(kDecPoints % (kDecUnroll * kDecThreads) == 0 && kDecLinks % (kDecUnroll * kDecThreads) == 0, "padded");
+    __shared__ float mem[kDecLinks * 2];
+    __shared__ DecAnyShared<kDecThreads> shared;
+    static_assert(kDecChunked * 3 <= kDecLinks * 2, "one block of LDS");
+    static_assert(kDecLinks % (kDecUnroll * kDecThreads) == 0, "padded");
     const int tid = threadIdx.x;
     int s;
     const int n = dec_range(a, blockIdx.x, s);
     if (n <= kDecShort || n > kDecLinks) return;
-    if (n <= kDecPoints) {
-        float *sx = mem, *sy = mem + kDecPoints, *sa = mem + 2 * kDecPoints;
-        unsigned short *sp = reinterpret_cast<unsigned short *>(mem + 3 * kDecPoints);
-        for (int k = tid; k < n; k += kDecThreads) {
-            sx[k] = a.x[s + k];
-            sy[k] = a.y[s + k];
+    if (n <= kDecChunked) {
+        unsigned short *link = reinterpret_cast<unsigned short *>(mem + kDecChunked);
+        for (int chunk = kChunk; chunk <= kChunkAgain; chunk += kChunkAgain - kChunk) {
+            if (vw_chunks<kDecThreads, kDecChunked>(n, tid, shared.chunks, a.x + s, a.y + s, mem, link, link + kDecChunked,
+                                                    link + 2 * kDecChunked, link + 3 * kDecChunked, a.min_area, chunk)) {
+                write_kept<kDecThreads>(n, tid, a.x + s, a.y + s, mem, link, link + kDecChunked, a.keep + s, a.dir + s);
+                return;
+            }
+            __syncthreads();
         }
-        __syncthreads();
-        vw_polyline<kDecThreads, unsigned short, true>(n, tid, shared, sx, sy, sa, sp, sp + kDecPoints, a.min_area, a.keep + s,
-                                                 a.dir + s);
-    } else {
-        unsigned short *sp = reinterpret_cast<unsigned short *>(mem + kDecLinks);
-        vw_polyline<kDecThreads, unsigned short, true>(n, tid, shared, a.x + s, a.y + s, mem, sp, sp + kDecLinks, a.min_area,
-                                                 a.keep + s, a.dir + s);
     }
+    unsigned short *link = reinterpret_cast<unsigned short *>(mem + kDecLinks);
+    vw_polyline<kDecThreads, unsigned short, true>(n, tid, shared.rounds, a.x + s, a.y + s, mem, link, link + kDecLinks, a.min_area,
+                                                   a.keep + s, a.dir + s);
 }
 
 // Polylines of more than kDecLinks points, areas and links in the workspace.
