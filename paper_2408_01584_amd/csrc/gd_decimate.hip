@@ -31,7 +31,7 @@
 // removes a point.
 //
 // 2560 polylines of 2600 points on average (64 maps sampled every 0.1 m, 97 % of the points
-// removed): one point at a time 9.2 ms, rounds 1.64 ms (190 of 4500 cycles), chunks 0.81 ms.
+// removed): one point at a time 9.2 ms, rounds 1.64 ms (190 of 4500 cycles), chunks 0.80 to 0.87 ms.
 // On straight lines, whose areas are all equal, nothing can be taken at the same time: 2600
 // points 8.1 ms one at a time, 8.6 ms by chunks, 36 ms by rounds; 500 points 1.5, 0.5 and
 // 2.0 ms.
@@ -247,8 +247,9 @@ __device__ __forceinline__ void vw_polyline(int n, int tid, DecShared<TH> &sh, c
 // another on some thread of a polyline of 2600 points in 50 rounds.  12 B of LDS per point let
 // a compute unit hold three polylines; with the coordinates in LDS too (20 B) it took as
 // long.  Chunks of 4 or 6 points and deals after a quarter or a half of them were 1 to 20 %
-// slower, mostly for the polylines taken again: those are first taken with larger chunks.
-constexpr int kChunk = 5, kChunkAgain = 12;  // points of a chunk, at least: at first, and when taken again
+// slower, mostly for the few polylines taken again (1 to 5 of the 2560, at the end of the
+// launch): those are first taken with chunks of 8, which pass (12 instead: up to 5 % slower).
+constexpr int kChunk = 5, kChunkAgain = 8;  // points of a chunk, at least: at first, and when taken again
 constexpr int kReach = 4;  // points between two chunks that take removals
 constexpr int kNear = 2;   // chunks on each side in which it looks for them
 constexpr int kOwn = 16;   // points of its chunk that a thread keeps in registers
