@@ -35,6 +35,8 @@
 // On straight lines, whose areas are all equal, nothing can be taken at the same time: 2600
 // points 8.1 ms one at a time, 8.6 ms by chunks, 36 ms by rounds; 500 points 1.5, 0.5 and
 // 2.0 ms.
+#include <algorithm>
+
 #include "gd_internal.h"
 
 namespace gdk {
@@ -443,6 +445,10 @@ constexpr int kDecThreads = 256;   // threads of a longer one
 constexpr int kDecChunked = 4096;  // points taken by chunks (12 B of LDS each)
 constexpr int kDecLinks = 6144;   // points whose areas and links fit the LDS (8 B each)
 
+// A workgroup (or wave) takes every kDecMaxBlocks-th group of polylines: grids are limited to
+// 2^32 threads, which n_poly with a workgroup each can exceed.
+constexpr int kDecMaxBlocks = 1 << 20;
+
 // Polylines of up to kDecShort points, a wave each.
 constexpr int kDecShortWaves = 4;
 __global__ __launch_bounds__(kDecShortWaves *kWave) void k_decimate_short(DecArgs a) {
@@ -451,22 +457,26 @@ __global__ __launch_bounds__(kDecShortWaves *kWave) void k_decimate_short(DecArg
     __shared__ DecAnyShared<kWave> shared[kDecShortWaves];
     const int g = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int tid = threadIdx.x % kWave;
-    const int pl = blockIdx.x * kDecShortWaves + g;
-    if (pl >= a.n_poly) return;
-    int s;
-    const int n = dec_range(a, pl, s);
-    if (n < 1 || n > kDecShort) return;
-    const float *x = a.x + s, *y = a.y + s;
-    unsigned short *prv = links[g], *nxt = prv + kDecShort;
-    for (int chunk = kChunk; chunk <= kChunkAgain; chunk += kChunkAgain - kChunk) {
-        if (vw_chunks<kWave, kDecShort>(n, tid, shared[g].chunks, x, y, areas[g], prv, nxt, nxt + kDecShort,
-                                        nxt + 2 * kDecShort, a.min_area, chunk)) {
+    for (long long pl = (long long)blockIdx.x * kDecShortWaves + g; pl < a.n_poly; pl += (long long)gridDim.x * kDecShortWaves) {
+        int s;
+        const int n = dec_range(a, (int)pl, s);
+        if (n < 1 || n > kDecShort) continue;
+        const float *x = a.x + s, *y = a.y + s;
+        unsigned short *prv = links[g], *nxt = prv + kDecShort;
+        bool done = false;
+        for (int chunk = kChunk; chunk <= kChunkAgain && !done; chunk += kChunkAgain - kChunk) {
+            wave_sync();
+            done = vw_chunks<kWave, kDecShort>(n, tid, shared[g].chunks, x, y, areas[g], prv, nxt, nxt + kDecShort,
+                                               nxt + 2 * kDecShort, a.min_area, chunk);
+        }
+        if (done) {
             write_kept<kWave>(n, tid, x, y, areas[g], prv, nxt, a.keep + s, a.dir + s);
-            return;
+            continue;
         }
         wave_sync();
+        vw_polyline<kWave, unsigned short, true>(n, tid, shared[g].rounds, x, y, areas[g], prv, nxt, a.min_area, a.keep + s,
+                                                 a.dir + s);
     }
-    vw_polyline<kWave, unsigned short, true>(n, tid, shared[g].rounds, x, y, areas[g], prv, nxt, a.min_area, a.keep + s, a.dir + s);
 }
 
 // Polylines of up to kDecLinks points, a workgroup each: by chunks up to kDecChunked points,
@@ -477,32 +487,37 @@ __global__ __launch_bounds__(kDecThreads) void k_decimate(DecArgs a) {
     static_assert(kDecChunked * 3 <= kDecLinks * 2, "one block of LDS");
     static_assert(kDecLinks % (kDecUnroll * kDecThreads) == 0, "padded");
     const int tid = threadIdx.x;
-    int s;
-    const int n = dec_range(a, blockIdx.x, s);
-    if (n <= kDecShort || n > kDecLinks) return;
-    if (n <= kDecChunked) {
-        unsigned short *link = reinterpret_cast<unsigned short *>(mem + kDecChunked);
-        for (int chunk = kChunk; chunk <= kChunkAgain; chunk += kChunkAgain - kChunk) {
-            if (vw_chunks<kDecThreads, kDecChunked>(n, tid, shared.chunks, a.x + s, a.y + s, mem, link, link + kDecChunked,
-                                                    link + 2 * kDecChunked, link + 3 * kDecChunked, a.min_area, chunk)) {
-                write_kept<kDecThreads>(n, tid, a.x + s, a.y + s, mem, link, link + kDecChunked, a.keep + s, a.dir + s);
-                return;
+    for (long long pl = blockIdx.x; pl < a.n_poly; pl += gridDim.x) {
+        int s;
+        const int n = dec_range(a, (int)pl, s);
+        if (n <= kDecShort || n > kDecLinks) continue;
+        bool done = false;
+        if (n <= kDecChunked) {
+            unsigned short *link = reinterpret_cast<unsigned short *>(mem + kDecChunked);
+            for (int chunk = kChunk; chunk <= kChunkAgain && !done; chunk += kChunkAgain - kChunk) {
+                __syncthreads();
+                done = vw_chunks<kDecThreads, kDecChunked>(n, tid, shared.chunks, a.x + s, a.y + s, mem, link, link + kDecChunked,
+                                                           link + 2 * kDecChunked, link + 3 * kDecChunked, a.min_area, chunk);
             }
-            __syncthreads();
+            if (done) {
+                write_kept<kDecThreads>(n, tid, a.x + s, a.y + s, mem, link, link + kDecChunked, a.keep + s, a.dir + s);
+                continue;
+            }
         }
+        __syncthreads();
+        unsigned short *link = reinterpret_cast<unsigned short *>(mem + kDecLinks);
+        vw_polyline<kDecThreads, unsigned short, true>(n, tid, shared.rounds, a.x + s, a.y + s, mem, link, link + kDecLinks,
+                                                       a.min_area, a.keep + s, a.dir + s);
     }
-    unsigned short *link = reinterpret_cast<unsigned short *>(mem + kDecLinks);
-    vw_polyline<kDecThreads, unsigned short, true>(n, tid, shared.rounds, a.x + s, a.y + s, mem, link, link + kDecLinks, a.min_area,
-                                                   a.keep + s, a.dir + s);
 }
 
 // Polylines of more than kDecLinks points, areas and links in the workspace.
 constexpr int kDecLong = 1024;
 __global__ __launch_bounds__(kDecLong) void k_decimate_long(DecArgs a) {
     __shared__ DecShared<kDecLong> shared;
-    for (int pl = blockIdx.x; pl < a.n_poly; pl += gridDim.x) {
+    for (long long pl = blockIdx.x; pl < a.n_poly; pl += gridDim.x) {
         int s;
-        const int n = dec_range(a, pl, s);
+        const int n = dec_range(a, (int)pl, s);
         if (n <= kDecLinks) continue;
         __syncthreads();
         vw_polyline<kDecLong, int, false>(n, threadIdx.x, shared, a.x + s, a.y + s, a.area + s, a.prv + s, a.nxt + s, a.min_area,
@@ -519,9 +534,9 @@ hipError_t launch_decimate_impl(const int *poly_off, int n_poly, int n_points, c
     // (-0 is 0: its bits would order above every area)
     const DecArgs a{poly_off, n_poly, n_points, x, y, min_area == 0.0f ? 0.0f : min_area, keep, dir, (float *)w,
                     (int *)(w + decimate_ws_offset(n_points, 1)), (int *)(w + decimate_ws_offset(n_points, 2))};
-    const unsigned short_blocks = (unsigned)(((long long)n_poly + kDecShortWaves - 1) / kDecShortWaves);
-    hipLaunchKernelGGL(k_decimate_short, dim3(short_blocks), dim3(kDecShortWaves * kWave), 0, s, a);
-    if (n_points > kDecShort) hipLaunchKernelGGL(k_decimate, dim3(n_poly), dim3(kDecThreads), 0, s, a);
+    auto blocks = [&](int per) { return dim3((unsigned)std::min(((long long)n_poly + per - 1) / per, (long long)kDecMaxBlocks)); };
+    hipLaunchKernelGGL(k_decimate_short, blocks(kDecShortWaves), dim3(kDecShortWaves * kWave), 0, s, a);
+    if (n_points > kDecShort) hipLaunchKernelGGL(k_decimate, blocks(1), dim3(kDecThreads), 0, s, a);
     if (n_points > kDecLinks)
         hipLaunchKernelGGL(k_decimate_long, dim3(n_poly < 65536 ? n_poly : 65536), dim3(kDecLong), 0, s, a);
     return hipGetLastError();
