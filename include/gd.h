@@ -276,16 +276,31 @@ gd_status gd_rollout_obs_features(const gd_sim *sim, int32_t *features);
 /* Differentiable rollout (backward): vector-Jacobian product of gd_rollout_fwd.  Given
  * grad_rewards [T,A] = dJ/d rewards and, if non-NULL, grad_obs [T,A,F] = dJ/d obs,
  * writes grad_actions [T,A,2] = dJ/d actions and, if non-NULL, grad_state0 [4,A] =
- * dJ/d (x, y, yaw, speed) at t = 0.  Recomputes each segment of ckpt_every steps from
- * `ckpt` (the output of gd_rollout_fwd with the same actions, T and ckpt_every).  With
+ * dJ/d (x, y, yaw, speed) at t = 0.  Recomputes the states, blocks of up to 16 steps from
+ * the checkpoint before them, from `ckpt` (the output of gd_rollout_fwd with the same
+ * actions, T and ckpt_every).  With
  * grad_obs, `states` must be the state log of that forward (the observation couples the
  * agents of a world: an agent's adjoint gathers the terms of every observation it
- * appears in, read against the other agents' logged states).  The nearest-segment
- * choice, the side, the clip activity, the partner masks and the heading wraps are held
+ * appears in, read against the other agents' logged states).  The call writes its
+ * outputs only.  The nearest-segment choice, the side, the clip activity, the partner masks and the heading wraps are held
  * constant (they are piecewise constant); collision flags are not differentiated. */
 gd_status gd_rollout_bwd(gd_sim *sim, const float *actions, const float *ckpt, int32_t T,
                          int32_t ckpt_every, const float *grad_rewards, const float *grad_obs,
                          const float *states, float *grad_actions, float *grad_state0, void *stream);
+
+/* gd_rollout_bwd with a workspace of the call's own, in which a kernel forms the gradient of
+ * the observation terms world by world before the backward reads it: several times faster with
+ * grad_obs, the same without.  The gradients of both differ by the rounding of sums taken in
+ * another order.  workspace: device, 256-byte aligned, at least
+ * gd_rollout_bwd_workspace_size(T) bytes (16 B per agent and step, of up to 128 steps at a
+ * time; at most 64 MB, or 512 B per agent if that is more, and 16 B per agent); not read or
+ * written without grad_obs, when it may be NULL.  Calls that run at the same time need one
+ * each. */
+gd_status gd_rollout_bwd_workspace_size(const gd_sim *sim, int32_t T, size_t *bytes);
+gd_status gd_rollout_bwd_ws(gd_sim *sim, const float *actions, const float *ckpt, int32_t T,
+                            int32_t ckpt_every, const float *grad_rewards, const float *grad_obs,
+                            const float *states, float *grad_actions, float *grad_state0,
+                            void *workspace, size_t workspace_bytes, void *stream);
 
 /* Expert-action inversion for the simplified model (Sec. 3.2 "Agent dynamics": the model is
  * invertible for unbounded actions, which makes logged trajectories usable as

@@ -23,8 +23,8 @@ hipError_t launch_rollout_obs_impl(const SimArgs &a, const float *states, int T,
                                    hipStream_t s);
 hipError_t launch_rollout_bwd_impl(const SimArgs &a, const float2 *actions, const float *ckpt,
                                    int T, int C, const float *grad_rewards, const float *grad_obs,
-                                   const float *states, int max_agents, float2 *grad_actions,
-                                   float *grad_state0, hipStream_t s);
+                                   const float *states, int max_agents, void *scratch,
+                                   float2 *grad_actions, float *grad_state0, hipStream_t s);
 hipError_t launch_invert_actions_impl(const float *states, int T, int A, float dt, float *actions,
                                       hipStream_t s);
 constexpr int kMaxInvertSteps = 65535 * 16;  // launch chunks of 16 steps on grid axis y
@@ -36,7 +36,7 @@ bool lidar_kernel_node(const SimArgs *a, const LidarCtl *lc, hipKernelNodeParams
 
 static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
-Layout make_layout(int W, long long A, long long R, int partners) {
+Layout make_layout(int W, long long A, long long R) {
     Layout L{};
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -56,8 +56,6 @@ Layout make_layout(int W, long long A, long long R, int partners) {
     L.pbase = take(sizeof(long long) * (size_t)W);
     L.err = take(256);
     L.order = take(sizeof(int) * (size_t)W);
-    L.obs_grad = take(partners >= 0 ? sizeof(float4) * (size_t)A * obs_grad_steps(A) : 0);
-    L.carry = take(partners >= 0 ? sizeof(float4) * (size_t)A : 0);
     L.total = off;
     return L;
 }
@@ -388,7 +386,7 @@ gd_status gd_workspace_size(const gd_config *cfg, const int32_t *h_agent_off,
     if (st != GD_OK) return st;
     if (!bytes) return fail(GD_E_ARG, "bytes is NULL");
     const int W = cfg->num_worlds;
-    *bytes = make_layout(W, h_agent_off[W], h_road_off[W], cfg->partners).total;
+    *bytes = make_layout(W, h_agent_off[W], h_road_off[W]).total;
     return GD_OK;
 }
 
@@ -417,7 +415,7 @@ gd_status gd_create(const gd_config *cfg, const int32_t *h_agent_off, const int3
     if (cfg->lidar_rays > 0 && A > 0 && (!b->lidar || !b->lidar_hit))
         return fail(GD_E_ARG, "lidar buffers are NULL");
     if (((uintptr_t)b->workspace) & 255) return fail(GD_E_ARG, "workspace must be 256-byte aligned");
-    Layout L = make_layout(W, A, R, cfg->partners);
+    Layout L = make_layout(W, A, R);
     if (b->workspace_bytes < L.total)
         return fail(GD_E_SIZE, "workspace too small: %zu bytes, need %zu", b->workspace_bytes, L.total);
     int max_road = 0, max_agents = 0;
@@ -516,8 +514,6 @@ gd_status gd_create(const gd_config *cfg, const int32_t *h_agent_off, const int3
     a.kth = (float *)(ws + L.kth);
     a.pbase = (long long *)(ws + L.pbase);
     a.err = (unsigned *)(ws + L.err);
-    a.obs_grad = (float4 *)(ws + L.obs_grad);
-    a.carry = (float4 *)(ws + L.carry);
     sim->ctl.order = (const int *)(ws + L.order);
     // a multiple of 4 agents keeps the LDS regions after the agent records 16-byte aligned
     sim->ctl.agent_cap = (std::max(max_agents, 1) + 3) / 4 * 4;
@@ -677,9 +673,10 @@ gd_status gd_rollout_fwd(gd_sim *sim, const float *actions, int32_t T, int32_t c
     return GD_OK;
 }
 
-gd_status gd_rollout_bwd(gd_sim *sim, const float *actions, const float *ckpt, int32_t T,
-                         int32_t ckpt_every, const float *grad_rewards, const float *grad_obs,
-                         const float *states, float *grad_actions, float *grad_state0, void *stream) {
+static gd_status rollout_bwd(gd_sim *sim, const float *actions, const float *ckpt, int32_t T,
+                             int32_t ckpt_every, const float *grad_rewards, const float *grad_obs,
+                             const float *states, float *grad_actions, float *grad_state0, bool with_ws,
+                             void *ws, size_t ws_bytes, void *stream) {
     if (!sim) return fail(GD_E_ARG, "sim is NULL");
     if (T < 0) return fail(GD_E_ARG, "T must be >= 0");
     if (ckpt_every < 1 || ckpt_every > 32) return fail(GD_E_ARG, "ckpt_every must be in [1, 32]");
@@ -688,13 +685,41 @@ gd_status gd_rollout_bwd(gd_sim *sim, const float *actions, const float *ckpt, i
         return fail(GD_E_UNSUPPORTED, "the rollout observation needs a fixed number of partner slots");
     if (T == 0 || sim->args.A == 0) return GD_OK;
     if (!actions || !ckpt || !grad_rewards || !grad_actions) return fail(GD_E_ARG, "NULL buffer");
+    if (with_ws && grad_obs) {
+        const size_t need = obs_grad_scratch(sim->args.A, T).total;
+        if (!ws) return fail(GD_E_ARG, "workspace is NULL");
+        if (ws_bytes < need) return fail(GD_E_SIZE, "workspace of %zu bytes, %zu needed", ws_bytes, need);
+        if (((uintptr_t)ws) & 255) return fail(GD_E_ARG, "workspace must be 256-byte aligned");
+    }
     hipStream_t s = (hipStream_t)stream;
     TIMED(sim, s, GD_PHASE_ROLLOUT_BWD,
           launch_rollout_bwd_impl(sim->args, (const float2 *)actions, ckpt, T, ckpt_every, grad_rewards,
-                                  grad_obs, grad_obs ? states : nullptr, sim->max_agents, (float2 *)grad_actions,
-                                  grad_state0, s),
+                                  grad_obs, grad_obs ? states : nullptr, sim->max_agents, with_ws ? ws : nullptr,
+                                  (float2 *)grad_actions, grad_state0, s),
           "rollout backward launch");
     return GD_OK;
+}
+
+gd_status gd_rollout_bwd(gd_sim *sim, const float *actions, const float *ckpt, int32_t T,
+                         int32_t ckpt_every, const float *grad_rewards, const float *grad_obs,
+                         const float *states, float *grad_actions, float *grad_state0, void *stream) {
+    return rollout_bwd(sim, actions, ckpt, T, ckpt_every, grad_rewards, grad_obs, states, grad_actions, grad_state0,
+                       false, nullptr, 0, stream);
+}
+
+gd_status gd_rollout_bwd_workspace_size(const gd_sim *sim, int32_t T, size_t *bytes) {
+    if (!sim || !bytes) return fail(GD_E_ARG, "NULL argument");
+    if (T < 0) return fail(GD_E_ARG, "T must be >= 0");
+    *bytes = T == 0 ? 0 : obs_grad_scratch(sim->args.A, T).total;
+    return GD_OK;
+}
+
+gd_status gd_rollout_bwd_ws(gd_sim *sim, const float *actions, const float *ckpt, int32_t T,
+                            int32_t ckpt_every, const float *grad_rewards, const float *grad_obs,
+                            const float *states, float *grad_actions, float *grad_state0, void *workspace,
+                            size_t workspace_bytes, void *stream) {
+    return rollout_bwd(sim, actions, ckpt, T, ckpt_every, grad_rewards, grad_obs, states, grad_actions, grad_state0,
+                       true, workspace, workspace_bytes, stream);
 }
 
 gd_status gd_invert_actions(gd_sim *sim, const float *states, int32_t T, float *actions, void *stream) {

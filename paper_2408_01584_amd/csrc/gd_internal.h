@@ -68,8 +68,6 @@ struct SimArgs {
                        // observation, R^2 when it had fewer than K in the radius
     long long *pbase;  // [W] first partner slot of each world
     unsigned *err;     // device error word
-    float4 *obs_grad;  // [obs_grad_steps(A), A] rollout backward: the observation's gradient
-    float4 *carry;     // [A] rollout backward: adjoint between parts
 };
 
 enum StepMode { kModeStep = 0, kModeObs = 1, kModeReset = 2 };
@@ -106,17 +104,26 @@ size_t lidar_lds_bytes(int N, const LidarCtl &lc);
 
 // Workspace layout (byte offsets, each 256-aligned).
 struct Layout {
-    size_t grid, cell_start, pt_xy, pt_aux, ecell_start, eseg, eseg_id, snap, kth, pbase, err, order,
-        obs_grad, carry, total;
+    size_t grid, cell_start, pt_xy, pt_aux, ecell_start, eseg, eseg_id, snap, kth, pbase, err, order, total;
 };
-// partners: the configured slots (a rollout's observation needs a fixed number)
-Layout make_layout(int W, long long A, long long R, int partners);
+Layout make_layout(int W, long long A, long long R);
 
-// Steps of a rollout whose observation gradient (16 B per agent and step) the workspace holds:
-// 64 MB of it, at least 32 steps (the longest backward block) and at most 128.
-__host__ __device__ inline int obs_grad_steps(long long A) {
-    const long long s = A > 0 ? ((64ll << 20) / 16) / A : 128;
-    return s < 32 ? 32 : s > 128 ? 128 : (int)s;
+// Scratch of one rollout backward with an observation gradient: obs_grad [steps, A], the
+// gradient of `steps` of the T steps at a time, and carry [A], the adjoint between them.
+// 64 MB of obs_grad, at least 32 steps (two blocks of the backward: a part is two kernels) and
+// at most 128 or T, in whole blocks of 16 steps.
+struct ObsGradScratch {
+    int steps;
+    size_t carry, total;  // byte offsets, 256-aligned
+};
+inline ObsGradScratch obs_grad_scratch(long long A, int T) {
+    const long long fit = A > 0 ? (64ll << 20) / 16 / A : 128, all = ((long long)T + 15) / 16 * 16;
+    const long long most = fit < 32 ? 32 : fit > 128 ? 128 : fit / 16 * 16;
+    ObsGradScratch L{};
+    L.steps = (int)(all < most ? all : most);
+    L.carry = ((size_t)L.steps * (size_t)A * 16 + 255) / 256 * 256;
+    L.total = L.carry + ((size_t)A * 16 + 255) / 256 * 256;
+    return L;
 }
 
 // Workspace of the polyline decimation: areas (f32), then predecessor and successor links

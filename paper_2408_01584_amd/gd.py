@@ -23,6 +23,7 @@ GD_AUTO_RESET, GD_TERMINATE_ON_COLLISION, GD_CHECK_FINITE, GD_USE_GRAPH = 1, 2, 
 
 ENTRY_POINTS = ("gd_partner_slots", "gd_workspace_size", "gd_create", "gd_reset", "gd_step",
                 "gd_obs", "gd_rollout_fwd", "gd_rollout_obs_features", "gd_rollout_bwd",
+                "gd_rollout_bwd_workspace_size", "gd_rollout_bwd_ws",
                 "gd_invert_actions",
                 "gd_decimate_workspace_size", "gd_decimate", "gd_decimate_noalloc",
                 "gd_set_obs_buffers", "gd_set_timing",
@@ -84,6 +85,8 @@ def lib():
             "gd_rollout_fwd": [vp, vp, i32, i32, vp, vp, vp, vp, vp],
             "gd_rollout_obs_features": [vp, C.POINTER(C.c_int32)],
             "gd_rollout_bwd": [vp, vp, vp, i32, i32, vp, vp, vp, vp, vp, vp],
+            "gd_rollout_bwd_workspace_size": [vp, i32, szp],
+            "gd_rollout_bwd_ws": [vp, vp, vp, i32, i32, vp, vp, vp, vp, vp, vp, C.c_size_t, vp],
             "gd_invert_actions": [vp, vp, i32, vp, vp],
             "gd_decimate_workspace_size": [i32, szp],
             "gd_decimate": [vp, i32, i32, vp, vp, C.c_float, vp, vp, vp, C.c_size_t, vp],
@@ -167,6 +170,23 @@ def gd_rollout_bwd(sim, actions_ptr: int, ckpt_ptr: int, T: int, ckpt_every: int
                                 C.c_void_p(grad_rewards_ptr), C.c_void_p(grad_obs_ptr or 0),
                                 C.c_void_p(states_ptr or 0), C.c_void_p(grad_actions_ptr),
                                 C.c_void_p(grad_state0_ptr or 0), C.c_void_p(stream)))
+
+
+def gd_rollout_bwd_workspace_size(sim, T: int) -> int:
+    out = C.c_size_t(0)
+    _check(lib().gd_rollout_bwd_workspace_size(sim, T, C.byref(out)))
+    return out.value
+
+
+def gd_rollout_bwd_ws(sim, actions_ptr: int, ckpt_ptr: int, T: int, ckpt_every: int,
+                      grad_rewards_ptr: int, grad_obs_ptr: int | None, states_ptr: int | None,
+                      grad_actions_ptr: int, grad_state0_ptr: int | None, ws_ptr: int | None,
+                      ws_bytes: int, stream: int):
+    _check(lib().gd_rollout_bwd_ws(sim, C.c_void_p(actions_ptr), C.c_void_p(ckpt_ptr), T, ckpt_every,
+                                   C.c_void_p(grad_rewards_ptr), C.c_void_p(grad_obs_ptr or 0),
+                                   C.c_void_p(states_ptr or 0), C.c_void_p(grad_actions_ptr),
+                                   C.c_void_p(grad_state0_ptr or 0), C.c_void_p(ws_ptr or 0), ws_bytes,
+                                   C.c_void_p(stream)))
 
 
 def gd_invert_actions(sim, states_ptr: int, T: int, actions_ptr: int, stream: int):

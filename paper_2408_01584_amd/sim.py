@@ -212,14 +212,19 @@ class Sim:
         T = actions.shape[0]
         ga = torch.empty((T, self.A, 2), dtype=torch.float32, device=self.device)
         g0 = torch.empty((4, self.A), dtype=torch.float32, device=self.device) if want_state0 else None
-        if grad_obs is not None:
-            assert states is not None and states.shape == (T, 4, self.A)
-            grad_obs = grad_obs.contiguous()
-        G.gd_rollout_bwd(self.handle, actions.data_ptr(), ckpt.data_ptr(), T, ckpt_every,
-                         grad_rewards.contiguous().data_ptr(),
-                         None if grad_obs is None else grad_obs.data_ptr(),
-                         None if grad_obs is None else states.data_ptr(), ga.data_ptr(),
-                         None if g0 is None else g0.data_ptr(), _stream())
+        grad_rewards = grad_rewards.contiguous()
+        p0 = None if g0 is None else g0.data_ptr()
+        if grad_obs is None:
+            G.gd_rollout_bwd(self.handle, actions.data_ptr(), ckpt.data_ptr(), T, ckpt_every,
+                             grad_rewards.data_ptr(), None, None, ga.data_ptr(), p0, _stream())
+            return ga, g0
+        assert states is not None and states.shape == (T, 4, self.A)
+        grad_obs = grad_obs.contiguous()
+        wsb = G.gd_rollout_bwd_workspace_size(self.handle, T)
+        ws = torch.empty(wsb + 256, dtype=torch.uint8, device=self.device)  # of this call and its stream
+        G.gd_rollout_bwd_ws(self.handle, actions.data_ptr(), ckpt.data_ptr(), T, ckpt_every,
+                            grad_rewards.data_ptr(), grad_obs.data_ptr(), states.data_ptr(), ga.data_ptr(), p0,
+                            ws.data_ptr() + (-ws.data_ptr()) % 256, wsb, _stream())
         return ga, g0
 
 
