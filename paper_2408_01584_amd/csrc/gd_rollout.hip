@@ -523,12 +523,16 @@ constexpr int kObsThreads = 256;
 // states are staged in LDS with their sines and cosines; then `lpr` lanes (a power of two)
 // per agent, a partner slot per lane, 16 bytes stored at a time.  A wave per agent-step with a
 // lane per feature looked up the world and took a sine and cosine for each agent-step:
-// 512 x 32 agents, T = 20 (166 MB): 192 us against 30 us now (5.6 TB/s).
+// 512 x 32 agents, T = 20 (166 MB): 192 us against 30 us now (5.6 TB/s).  Where worlds and
+// steps leave the chip idle, `share` agents of the world per workgroup instead of all.
 __global__ __launch_bounds__(kObsThreads) void k_rollout_obs(SimArgs a, const float *__restrict__ slog, int tb,
-                                                             int T, int steps, int lpr, float *__restrict__ obs) {
+                                                             int T, int steps, int share, int lpr,
+                                                             float *__restrict__ obs) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int w = blockIdx.x;
     const int a0 = a.agent_off[w], n = a.agent_off[w + 1] - a0;
+    const int i0 = (int)blockIdx.z * share, i1 = min(n, i0 + share);
+    if (i0 >= n) return;
     const int t0 = tb + (int)blockIdx.y * steps, m = min(steps, T - t0);
     float4 *pose = reinterpret_cast<float4 *>(smem);  // x, y, yaw, speed of the steps' agents
     const size_t A = (size_t)a.A;
@@ -544,6 +548,7 @@ __global__ __launch_bounds__(kObsThreads) void k_rollout_obs(SimArgs a, const fl
         sincosf(yaw, &sn, &cs);
         pose[k] = make_float4(x, y, yaw, v);
         turn[k] = make_float2(sn, cs);
+        if (i < i0 || i >= i1) continue;
         const float dxg = gx - x, dyg = gy - y;
         float *o = obs + ((size_t)(t0 + tl) * A + a0 + i) * F;
         o[0] = v;
@@ -553,7 +558,7 @@ __global__ __launch_bounds__(kObsThreads) void k_rollout_obs(SimArgs a, const fl
     __syncthreads();
     const int sub = threadIdx.x & (lpr - 1), per = kObsThreads / lpr;
     for (int tl = 0; tl < m; tl++) {
-        for (int i = threadIdx.x / lpr; i < n; i += per) {
+        for (int i = i0 + threadIdx.x / lpr; i < i1; i += per) {
             const float4 p = pose[tl * n + i];
             const float sn = turn[tl * n + i].x, cs = turn[tl * n + i].y;
             Slot4 *o = reinterpret_cast<Slot4 *>(obs + ((size_t)(t0 + tl) * A + a0 + i) * F + 3);
@@ -577,13 +582,15 @@ __global__ __launch_bounds__(kObsThreads) void k_rollout_obs(SimArgs a, const fl
 // wave takes an observer (a few of them in small worlds) with a lane per agent j, so that
 // grad_obs is read in rows, only where the partner is within the radius; the terms of j stay
 // in its lane over all observers, those of m are summed over the row's lanes; both in a
-// fixed order.  Bound by the latency of those reads.  Gathered by each agent's lanes inside
+// fixed order.  Where worlds and steps leave the chip idle, `share` agents of the world per
+// workgroup: it takes their columns over all observers, then their rows over all agents (each
+// pair twice, but nothing to add up between workgroups).  Bound by the latency of those reads.  Gathered by each agent's lanes inside
 // the backward kernel instead, row and column read per agent and step, the backward took
 // 390 us against 40 + 37 us now (512 x 32 agents, T = 20).
 struct ObsGradLds {
     float4 *pose;  // x, y, sine, cosine of each agent
-    float4 *mine;  // terms of each agent from its own row (x, y, yaw)
-    float4 *part;  // per wave: terms of each agent from the others' rows
+    float4 *mine;  // terms of each of the workgroup's agents from its own row (x, y, yaw)
+    float4 *part;  // per wave: terms of each of them from the others' rows
 };
 
 // sum over groups of `cols` lanes (a power of two, at least 8), on all of their lanes
@@ -598,14 +605,16 @@ __device__ __forceinline__ float group_sum(float v, int cols) {
 }
 
 __global__ __launch_bounds__(kObsThreads) void k_rollout_obs_grad(SimArgs a, const float *__restrict__ slog, int t0,
-                                                                  int cols, const float *__restrict__ grad_obs,
+                                                                  int share, const float *__restrict__ grad_obs,
                                                                   float4 *__restrict__ og) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int w = blockIdx.x, t = t0 + blockIdx.y;
     const int a0 = a.agent_off[w], n = a.agent_off[w + 1] - a0;
+    const int i0 = (int)blockIdx.z * share, i1 = min(n, i0 + share), ni = i1 - i0;
+    if (i0 >= n) return;
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave, waves = blockDim.x / kWave;
     const ObsGradLds s{reinterpret_cast<float4 *>(smem), reinterpret_cast<float4 *>(smem) + n,
-                       reinterpret_cast<float4 *>(smem) + 2 * n};
+                       reinterpret_cast<float4 *>(smem) + n + ni};
     const size_t A = (size_t)a.A;
     const int P = a.P;
     const size_t F = 3 + 4 * (size_t)P;
@@ -615,82 +624,98 @@ __global__ __launch_bounds__(kObsThreads) void k_rollout_obs_grad(SimArgs a, con
         float sn, cs;
         sincosf(S[2 * A + i], &sn, &cs);
         s.pose[i] = make_float4(S[i], S[A + i], sn, cs);
-        s.mine[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (i < ni) s.mine[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     __syncthreads();
-    const int rows = kWave / cols;  // observers of a wave at a time
-    const int col = lane & (cols - 1), row = lane / cols;
-    for (int j0 = 0; j0 < n; j0 += cols) {
-        const int j = j0 + col;
-        const float4 pj = s.pose[min(j, n - 1)];
-        float cx = 0.f, cy = 0.f, ch = 0.f, cv = 0.f;
-        // four observers' rows in flight together
-        constexpr int U = 4;
-        for (int m0 = wid * rows; m0 < n; m0 += U * waves * rows) {
-            Slot4 g[U];
-            float4 pm[U];
-            bool in[U];
+    // observers [ma, mb) with agents [ja, jb) in their slots: terms of the agents (COLS), of
+    // the observers (ROWS)
+    auto pairs = [&](int ma, int mb, int ja, int jb, auto cols_too, auto rows_too) {
+        constexpr bool COLS = decltype(cols_too)::k, ROWS = decltype(rows_too)::k;
+        // lanes of an observer: as many as agents, a power of two from 8 on; observers of a wave
+        const int log = jb - ja <= 8 ? 3 : jb - ja > kWave / 2 ? 6 : 32 - __builtin_clz(jb - ja - 1);
+        const int cols = 1 << log, rows = kWave >> log;
+        const int col = lane & (cols - 1), row = lane >> log;
+        for (int j0 = ja; j0 < jb; j0 += cols) {
+            const int j = j0 + col;
+            const float4 pj = s.pose[min(j, n - 1)];
+            float cx = 0.f, cy = 0.f, ch = 0.f, cv = 0.f;
+            // four observers' rows in flight together
+            constexpr int U = 4;
+            for (int m0 = ma + wid * rows; m0 < mb; m0 += U * waves * rows) {
+                Slot4 g[U];
+                float4 pm[U];
+                bool in[U];
 #pragma unroll
-            for (int u = 0; u < U; u++) {
-                const int m = m0 + u * waves * rows + row;
-                pm[u] = s.pose[min(m, n - 1)];
-                const int sl = j < m ? j : j - 1;
-                in[u] = j < n && m < n && j != m && sl < P && key32(pm[u].x, pm[u].y, pj.x, pj.y) <= a.R2_obs;
-                g[u] = Slot4{0.f, 0.f, 0.f, 0.f};
-                if (in[u]) g[u] = *reinterpret_cast<const Slot4 *>(G + (size_t)m * F + 3 + 4 * (size_t)sl);
-            }
+                for (int u = 0; u < U; u++) {
+                    const int m = m0 + u * waves * rows + row;
+                    pm[u] = s.pose[min(m, n - 1)];
+                    const int sl = j < m ? j : j - 1;
+                    in[u] = j < jb && m < mb && j != m && sl < P && key32(pm[u].x, pm[u].y, pj.x, pj.y) <= a.R2_obs;
+                    g[u] = Slot4{0.f, 0.f, 0.f, 0.f};
+                    if (in[u]) g[u] = *reinterpret_cast<const Slot4 *>(G + (size_t)m * F + 3 + 4 * (size_t)sl);
+                }
 #pragma unroll
-            for (int u = 0; u < U; u++) {
-                const int m = m0 + u * waves * rows + row;
-                if (__ballot(in[u]) == 0ull) continue;
-                float rx = 0.f, ry = 0.f, rh = 0.f;
-                if (in[u]) {
-                    const float sn = pm[u].z, cs = pm[u].w;
-                    const float dx = pj.x - pm[u].x, dy = pj.y - pm[u].y;
-                    const float fx = cs * dx + sn * dy, fy = -sn * dx + cs * dy;
-                    const float wx = cs * g[u].x - sn * g[u].y, wy = sn * g[u].x + cs * g[u].y;
-                    cx += wx;
-                    cy += wy;
-                    ch += g[u].z;
-                    cv += g[u].w;
-                    rx = -wx;
-                    ry = -wy;
-                    rh = g[u].x * fy - g[u].y * fx - g[u].z;
-                }
-                rx = group_sum(rx, cols);
-                ry = group_sum(ry, cols);
-                rh = group_sum(rh, cols);
-                if (col == 0 && m < n) {
-                    float4 q = s.mine[m];  // (observer m is always taken by this wave)
-                    q.x += rx;
-                    q.y += ry;
-                    q.z += rh;
-                    s.mine[m] = q;
+                for (int u = 0; u < U; u++) {
+                    const int m = m0 + u * waves * rows + row;
+                    if (__ballot(in[u]) == 0ull) continue;
+                    float rx = 0.f, ry = 0.f, rh = 0.f;
+                    if (in[u]) {
+                        const float sn = pm[u].z, cs = pm[u].w;
+                        const float dx = pj.x - pm[u].x, dy = pj.y - pm[u].y;
+                        const float fx = cs * dx + sn * dy, fy = -sn * dx + cs * dy;
+                        const float wx = cs * g[u].x - sn * g[u].y, wy = sn * g[u].x + cs * g[u].y;
+                        cx += wx;
+                        cy += wy;
+                        ch += g[u].z;
+                        cv += g[u].w;
+                        rx = -wx;
+                        ry = -wy;
+                        rh = g[u].x * fy - g[u].y * fx - g[u].z;
+                    }
+                    if (!ROWS) continue;
+                    rx = group_sum(rx, cols);
+                    ry = group_sum(ry, cols);
+                    rh = group_sum(rh, cols);
+                    if (col == 0 && m < mb) {
+                        float4 q = s.mine[m - i0];  // (observer m is always taken by this wave)
+                        q.x += rx;
+                        q.y += ry;
+                        q.z += rh;
+                        s.mine[m - i0] = q;
+                    }
                 }
             }
+            if (!COLS) continue;
+            for (int d = cols; d < kWave; d <<= 1) {
+                cx += __shfl_xor(cx, d, kWave);
+                cy += __shfl_xor(cy, d, kWave);
+                ch += __shfl_xor(ch, d, kWave);
+                cv += __shfl_xor(cv, d, kWave);
+            }
+            if (row == 0 && j < jb) s.part[wid * ni + j - i0] = make_float4(cx, cy, ch, cv);
         }
-        for (int d = cols; d < kWave; d <<= 1) {
-            cx += __shfl_xor(cx, d, kWave);
-            cy += __shfl_xor(cy, d, kWave);
-            ch += __shfl_xor(ch, d, kWave);
-            cv += __shfl_xor(cv, d, kWave);
-        }
-        if (row == 0 && j < n) s.part[wid * n + j] = make_float4(cx, cy, ch, cv);
+    };
+    if (ni == n) {
+        pairs(0, n, 0, n, StepIndex<1>{}, StepIndex<1>{});
+    } else {
+        pairs(0, n, i0, i1, StepIndex<1>{}, StepIndex<0>{});
+        pairs(i0, i1, 0, n, StepIndex<0>{}, StepIndex<1>{});
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    for (int k = threadIdx.x; k < ni; k += blockDim.x) {
+        const int i = i0 + k;
         const float *go = G + (size_t)i * F;
         const float4 p = s.pose[i];
         const float dxg = a.gx[a0 + i] - p.x, dyg = a.gy[a0 + i] - p.y;
         const float gpx = p.w * dxg + p.z * dyg, gpy = -p.z * dxg + p.w * dyg;
         // own speed, goal in the own frame g' = R(-yaw)(g - p), own slots
-        float4 q = s.mine[i];
+        float4 q = s.mine[k];
         q.x += -p.w * go[1] + p.z * go[2];
         q.y += -p.z * go[1] - p.w * go[2];
         q.z += gpy * go[1] - gpx * go[2];
         q.w = go[0];
-        for (int k = 0; k < waves; k++) {
-            const float4 c = s.part[k * n + i];
+        for (int v = 0; v < waves; v++) {
+            const float4 c = s.part[v * ni + k];
             q.x += c.x;
             q.y += c.y;
             q.z += c.z;
@@ -1044,17 +1069,28 @@ static int obs_lanes(int P) {
     return best;
 }
 
+// Agents per workgroup of the observation kernels: all of a world's, unless the `groups` workgroups
+// that gives are fewer than 1024 (four per compute unit); then a share, at most `most` of them.
+// Below that a world's kernels take as long as its agents squared: 4 x 1000 agents, T = 5: forward
+// 443 -> 86 us, backward 3641 -> 86; 1 x 128, T = 10: 26 -> 19 and 60 -> 24.
+static int agents_per_group(int max_agents, long long groups, int most) {
+    const int shares = groups >= 1024 ? 1 : (int)std::min(2048 / groups, (long long)most);
+    return std::max(1, (max_agents + std::max(shares, 1) - 1) / std::max(shares, 1));
+}
+
 hipError_t launch_rollout_obs_impl(const SimArgs &a, const float *states, int T, int max_agents, float *obs,
                                    hipStream_t s) {
     // about 4096 slots per workgroup, 16 per thread; at least one step, states within 48 KB
     const long long slots = (long long)std::max(max_agents, 1) * std::max(a.P, 1);
     const int steps = (int)std::max(1ll, std::min({4096 / slots, (long long)T, 2048ll / std::max(max_agents, 1)}));
+    const int share = agents_per_group(max_agents, (long long)a.W * ((T + steps - 1) / steps),
+                                       (int)std::min((long long)max_agents, (slots + 4095) / 4096));
     const size_t lds = (size_t)steps * max_agents * (sizeof(float4) + sizeof(float2));
     const long long most = 65535ll * steps;  // (grid axis y)
     for (long long t0 = 0; t0 < T; t0 += most) {
         const int m = (int)std::min((long long)T - t0, most);
-        hipLaunchKernelGGL(k_rollout_obs, dim3(a.W, (m + steps - 1) / steps), dim3(kObsThreads), lds, s, a, states,
-                           (int)t0, T, steps, obs_lanes(a.P), obs);
+        hipLaunchKernelGGL(k_rollout_obs, dim3(a.W, (m + steps - 1) / steps, (max_agents + share - 1) / share),
+                           dim3(kObsThreads), lds, s, a, states, (int)t0, T, steps, share, obs_lanes(a.P), obs);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1076,17 +1112,18 @@ static hipError_t launch_bwd(const SimArgs &a, const float2 *actions, const floa
     const ObsGradScratch L = obs_grad_scratch(a.A, T);
     float4 *og = (float4 *)scratch, *carry = (float4 *)((char *)scratch + L.carry);
     const int part = L.steps / B * B;
-    int cols = 8;  // columns of a wave: as many as agents, a power of two
+    const int share = agents_per_group(max_agents, (long long)a.W * std::min(T, part), (max_agents + 15) / 16);
+    int cols = 8;  // lanes of an observer: as many as agents, a power of two
     while (cols < kWave && cols < max_agents) cols *= 2;
     const int rows = kWave / cols;
     // four observers per wave and pass, up to four waves, within 64 KB of LDS
-    const int fit = std::max(1, 64 * 1024 / (int)sizeof(float4) / std::max(max_agents, 1) - 2);
+    const int fit = std::max(1, (64 * 1024 / (int)sizeof(float4) - max_agents) / share - 1);
     const int waves = std::min({kObsThreads / kWave, fit, std::max(1, (max_agents + 4 * rows - 1) / (4 * rows))});
-    const size_t lds = (size_t)max_agents * sizeof(float4) * (2 + waves);
+    const size_t lds = ((size_t)max_agents + (size_t)share * (1 + waves)) * sizeof(float4);
     for (int Ts = (T - 1) / part * part; Ts >= 0; Ts -= part) {
         const int Te = std::min(T, Ts + part);
-        hipLaunchKernelGGL(k_rollout_obs_grad, dim3(a.W, Te - Ts), dim3(waves * kWave), lds, s, a, states, Ts, cols,
-                           grad_obs, og);
+        hipLaunchKernelGGL(k_rollout_obs_grad, dim3(a.W, Te - Ts, (max_agents + share - 1) / share), dim3(waves * kWave),
+                           lds, s, a, states, Ts, share, grad_obs, og);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((k_rollout_bwd<DELTA, kObsScratch>), dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a,
