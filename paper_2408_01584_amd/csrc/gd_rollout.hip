@@ -140,7 +140,7 @@ struct StepState {   // this lane's step: the state before (0) and after (1) it
 // step-by-step evaluation.  Bicycle model (App. B): slip angle beta = atan(tan(steer) / 2)
 // through cos beta = 1 / sqrt(1 + z^2), sin beta = z cos beta (z = tan(steer) / 2), the
 // direction of motion by angle addition.
-template <bool DELTA>
+template <bool DELTA, bool ONE>
 __device__ __forceinline__ void run_block(const AgentState &c, float2 u, int n, int sub, float L, float dt,
                                           float vmax, StepState &o) {
 #pragma clang fp contract(off)
@@ -148,7 +148,7 @@ __device__ __forceinline__ void run_block(const AgentState &c, float2 u, int n, 
     float ix, iy, iw;  // increments of the lane's step
     // speed before the step
     float v = c.v;
-    each_step(n, [&](auto kc) {
+    if (!ONE) each_step(n, [&](auto kc) {
         constexpr int k = decltype(kc)::k;
         float w = __builtin_fmaf(row_bcast<k>(acc), dt, v);
         if (!DELTA) w = fminf(fmaxf(w, -vmax), vmax);
@@ -170,7 +170,7 @@ __device__ __forceinline__ void run_block(const AgentState &c, float2 u, int n, 
     }
     // heading before the step
     float yaw = c.yaw;
-    each_step(n, [&](auto kc) {
+    if (!ONE) each_step(n, [&](auto kc) {
         constexpr int k = decltype(kc)::k;
         const float w = yaw + row_bcast<k>(iw);
         yaw = sub > k ? w : yaw;
@@ -178,8 +178,8 @@ __device__ __forceinline__ void run_block(const AgentState &c, float2 u, int n, 
     o.yaw0 = yaw;
     o.yaw1 = yaw + iw;
     sincosf(o.yaw1, &o.sn1, &o.cs1);
-    o.sn0 = row_before(o.sn1, c.sn);  // the step before ends with this step's heading
-    o.cs0 = row_before(o.cs1, c.cs);
+    o.sn0 = ONE ? c.sn : row_before(o.sn1, c.sn);  // the step before ends with this step's heading
+    o.cs0 = ONE ? c.cs : row_before(o.cs1, c.cs);
     if (DELTA) {
         ix = o.vb * o.cs0;
         iy = o.vb * o.sn0;
@@ -191,7 +191,7 @@ __device__ __forceinline__ void run_block(const AgentState &c, float2 u, int n, 
     }
     // position before the step
     float x = c.x, y = c.y;
-    each_step(n, [&](auto kc) {
+    if (!ONE) each_step(n, [&](auto kc) {
         constexpr int k = decltype(kc)::k;
         const float wx = x + row_bcast<k>(ix), wy = y + row_bcast<k>(iy);
         x = sub > k ? wx : x;
@@ -283,6 +283,10 @@ struct EdgeList {
 //   4. every lane takes its minimum over what is left, read by all lanes at once.
 // A full list is taken in parts.  Bound by vector instructions: step 4 over the whole list
 // of step 2 took about 65 instead of 20 segments per block and half of the kernel's time.
+// ONE: a rollout of one step has one point per row, c itself, whose nearest segment the widening
+// squares find without a list (4096 x 64 agents, T = 1: forward 178 -> 88 us, backward 189 ->
+// 118; 114 and 127 with 8 lanes per agent).
+template <bool ONE>
 __device__ __forceinline__ EdgeChoice nearest_edges(const EdgeGrid &e, const EdgeList &ls, float px, float py,
                                                     bool valid, float R, int sub, EdgeBound &bd,
                                                     bool last_lane) {
@@ -306,103 +310,124 @@ __device__ __forceinline__ EdgeChoice nearest_edges(const EdgeGrid &e, const Edg
             const float d2 = seg_d2(s.x, s.y, ex, ey, seg_inv(ex, ey), cx, cy);
             return ok ? d2 : INFINITY;
         };
-        float D;
-        if (bd.q >= 0) {
-            const int q = bd.q - kRow / 2 + sub;
-            const float d = __builtin_amdgcn_sqrtf(row_min(centre_d2(q, q >= 0 && q < g.n_edge)));
-            const float hx = cx - bd.x, hy = cy - bd.y;
-            D = fminf(d, bd.d + __builtin_amdgcn_sqrtf(hx * hx + hy * hy)) + marg;
-        } else {
+        auto nearer = [&](float d2, int q) {
+            bool less = d2 < best;
+            // (exact ties are rare: the indices are read for them only)
+            if (d2 == best && bq >= 0) less = e.eid[q] < e.eid[bq];
+            best = less ? d2 : best;
+            bq = less ? q : bq;
+        };
+        if (ONE) {
             for (float r = 0.5f * g.cs;; r *= 3.0f) {
                 r = fminf(r, far);
-                float d2 = INFINITY;
-                scan_edges(e, cx, cy, r, sub, [&](int q, bool ok) { d2 = fminf(d2, centre_d2(q, ok)); });
-                D = __builtin_amdgcn_sqrtf(row_min(d2)) + marg;
-                if (D <= r || !(r < far)) break;
+                best = INFINITY;
+                bq = -1;
+                scan_edges(e, cx, cy, r, sub, [&](int q, bool ok) { nearer(centre_d2(q, ok), q); });
+                const float d2 = row_min(best);
+                unsigned who = row_ballot(bq >= 0 && best == d2);
+                if (who & (who - 1)) {  // equal ones: the lowest index
+                    const float id = bq >= 0 && best == d2 ? (float)e.eid[bq] : INFINITY;
+                    who = row_ballot(id == row_min(id));
+                }
+                best = d2;
+                bq = who ? __shfl(bq, __ffs(who) - 1, kRow) : -1;
+                if (__builtin_amdgcn_sqrtf(best) + marg <= r || !(r < far)) break;
             }
-        }
-        const float rf = fminf(D + 2.0f * rho, far) + marg;
-        const float pcx = px - cx, pcy = py - cy;
-        const float pc = __builtin_amdgcn_sqrtf(pcx * pcx + pcy * pcy);
-        int cnt = 0;
-        auto sync = [] {
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-        };
-        auto distance2 = [&](int k, int &q) {
-            const float4 s = ls.seg[k];
-            const float2 t = ls.inv[k];
-            q = __float_as_int(t.y);
-            return seg_d2(s.x, s.y, s.z, s.w, t.x, px, py);
-        };
-        // the segments of the list pad to a multiple of four with some that are never nearer
-        auto pad = [&](int m) {
-            const int padded = (m + 3) & ~3;
-            if (m + sub < padded) {
-                ls.seg[m + sub] = make_float4(NAN, NAN, 0.f, 0.f);
-                ls.inv[m + sub] = make_float2(0.f, 0.f);
+        } else {
+            float D;
+            if (bd.q >= 0) {
+                const int q = bd.q - kRow / 2 + sub;
+                const float d = __builtin_amdgcn_sqrtf(row_min(centre_d2(q, q >= 0 && q < g.n_edge)));
+                const float hx = cx - bd.x, hy = cy - bd.y;
+                D = fminf(d, bd.d + __builtin_amdgcn_sqrtf(hx * hx + hy * hy)) + marg;
+            } else {
+                for (float r = 0.5f * g.cs;; r *= 3.0f) {
+                    r = fminf(r, far);
+                    float d2 = INFINITY;
+                    scan_edges(e, cx, cy, r, sub, [&](int q, bool ok) { d2 = fminf(d2, centre_d2(q, ok)); });
+                    D = __builtin_amdgcn_sqrtf(row_min(d2)) + marg;
+                    if (D <= r || !(r < far)) break;
+                }
             }
-            sync();
-            return padded;
-        };
-        auto take = [&]() {
-            sync();
-            float b2 = best;
-            for (int k = 0; k < cnt; k += 4) {
-                int q;
-                b2 = fminf(b2, distance2(k, q));
-            }
-            const float reach = valid ? __builtin_amdgcn_sqrtf(b2) + pc : 0.0f;
-            const float keep = -row_min(-reach) + marg;
-            int m = 0;
-            for (int k0 = 0; k0 < cnt; k0 += kRow) {
-                const int k = min(k0 + sub, cnt - 1);
+            const float rf = fminf(D + 2.0f * rho, far) + marg;
+            const float pcx = px - cx, pcy = py - cy;
+            const float pc = __builtin_amdgcn_sqrtf(pcx * pcx + pcy * pcy);
+            int cnt = 0;
+            auto sync = [] {
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            };
+            auto distance2 = [&](int k, int &q) {
                 const float4 s = ls.seg[k];
                 const float2 t = ls.inv[k];
-                const bool in = k0 + sub < cnt && ls.dc[k] <= keep;
-                const unsigned bits = row_ballot(in);
-                sync();
-                if (in) {
-                    const int pos = m + __popc(bits & ((1u << sub) - 1u));
-                    ls.seg[pos] = s;
-                    ls.inv[pos] = t;
+                q = __float_as_int(t.y);
+                return seg_d2(s.x, s.y, s.z, s.w, t.x, px, py);
+            };
+            // the segments of the list pad to a multiple of four with some that are never nearer
+            auto pad = [&](int m) {
+                const int padded = (m + 3) & ~3;
+                if (m + sub < padded) {
+                    ls.seg[m + sub] = make_float4(NAN, NAN, 0.f, 0.f);
+                    ls.inv[m + sub] = make_float2(0.f, 0.f);
                 }
-                m += __popc(bits);
                 sync();
-            }
-            const int padded = pad(m);
-            for (int k0 = 0; k0 < padded; k0 += 2) {
-#pragma unroll
-                for (int k = k0; k < k0 + 2; k++) {
+                return padded;
+            };
+            auto take = [&]() {
+                sync();
+                float b2 = best;
+                for (int k = 0; k < cnt; k += 4) {
                     int q;
-                    const float d2 = distance2(k, q);
-                    bool less = d2 < best;
-                    // (exact ties are rare: the indices are read for them only)
-                    if (d2 == best && bq >= 0) less = e.eid[q] < e.eid[bq];
-                    best = less ? d2 : best;
-                    bq = less ? q : bq;
+                    b2 = fminf(b2, distance2(k, q));
                 }
-            }
-            sync();
-            cnt = 0;
-        };
-        scan_edges(e, cx, cy, rf, sub, [&](int q, bool ok) {
-            const float4 s = e.es[ok ? q : 0];
-            const float ex = s.z - s.x, ey = s.w - s.y;
-            const float ir = seg_inv(ex, ey);
-            const float d = __builtin_amdgcn_sqrtf(seg_d2(s.x, s.y, ex, ey, ir, cx, cy));
-            const bool in = ok && d <= rf;
-            const unsigned bits = row_ballot(in);
-            if (cnt + kRow > kEdgeList) take();
-            if (in) {
-                const int pos = cnt + __popc(bits & ((1u << sub) - 1u));
-                ls.seg[pos] = make_float4(s.x, s.y, ex, ey);
-                ls.inv[pos] = make_float2(ir, __int_as_float(q));
-                ls.dc[pos] = d;
-            }
-            cnt += __popc(bits);
-        });
-        take();
+                const float reach = valid ? __builtin_amdgcn_sqrtf(b2) + pc : 0.0f;
+                const float keep = -row_min(-reach) + marg;
+                int m = 0;
+                for (int k0 = 0; k0 < cnt; k0 += kRow) {
+                    const int k = min(k0 + sub, cnt - 1);
+                    const float4 s = ls.seg[k];
+                    const float2 t = ls.inv[k];
+                    const bool in = k0 + sub < cnt && ls.dc[k] <= keep;
+                    const unsigned bits = row_ballot(in);
+                    sync();
+                    if (in) {
+                        const int pos = m + __popc(bits & ((1u << sub) - 1u));
+                        ls.seg[pos] = s;
+                        ls.inv[pos] = t;
+                    }
+                    m += __popc(bits);
+                    sync();
+                }
+                const int padded = pad(m);
+                for (int k0 = 0; k0 < padded; k0 += 2) {
+#pragma unroll
+                    for (int k = k0; k < k0 + 2; k++) {
+                        int q;
+                        const float d2 = distance2(k, q);
+                        nearer(d2, q);
+                    }
+                }
+                sync();
+                cnt = 0;
+            };
+            scan_edges(e, cx, cy, rf, sub, [&](int q, bool ok) {
+                const float4 s = e.es[ok ? q : 0];
+                const float ex = s.z - s.x, ey = s.w - s.y;
+                const float ir = seg_inv(ex, ey);
+                const float d = __builtin_amdgcn_sqrtf(seg_d2(s.x, s.y, ex, ey, ir, cx, cy));
+                const bool in = ok && d <= rf;
+                const unsigned bits = row_ballot(in);
+                if (cnt + kRow > kEdgeList) take();
+                if (in) {
+                    const int pos = cnt + __popc(bits & ((1u << sub) - 1u));
+                    ls.seg[pos] = make_float4(s.x, s.y, ex, ey);
+                    ls.inv[pos] = make_float2(ir, __int_as_float(q));
+                    ls.dc[pos] = d;
+                }
+                cnt += __popc(bits);
+            });
+            take();
+        }
     }
     // the bound for the next block: this block's point next to it
     const float d = sqrtf(best);
@@ -456,14 +481,15 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
 }
 
 // (four waves per SIMD: 128 registers; one more register costs a quarter of the waves)
-template <bool DELTA>
+template <bool DELTA, bool ONE>
 __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_fwd(SimArgs a, const float2 *__restrict__ act,
                                                               int T, int C, float *__restrict__ rewards,
                                                               float *__restrict__ ckpt,
                                                               float *__restrict__ slog) {
-    __shared__ float4 s_seg[kRollAgents * kEdgeStride];
-    __shared__ float2 s_inv[kRollAgents * kEdgeStride];
-    __shared__ float s_dc[kRollAgents * kEdgeStride];
+    constexpr int kList = ONE ? 1 : kRollAgents * kEdgeStride;
+    __shared__ float4 s_seg[kList];
+    __shared__ float2 s_inv[kList];
+    __shared__ float s_dc[kList];
     const int row = threadIdx.x / kRow, sub = threadIdx.x % kRow;
     const int i = xcd_tile(blockIdx.x, gridDim.x) * kRollAgents + row;
     if (i >= a.A) return;
@@ -478,13 +504,13 @@ __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_fwd(SimArgs a, cons
     const EdgeGrid e{a.grid[w], a.ecell_start + (size_t)w * kCellStride, a.eseg + r0, a.eseg_id + r0};
     sincosf(c.yaw, &c.sn, &c.cs);
     EdgeBound bd{0.f, 0.f, 0.f, -1};
-    for (int t0 = 0; t0 < T; t0 += kRow) {
-        const int n = min(kRow, T - t0), t = t0 + sub;
+    for (int t0 = 0; t0 < (ONE ? 1 : T); t0 += kRow) {
+        const int n = ONE ? 1 : min(kRow, T - t0), t = t0 + sub;
         const bool on = sub < n;
         const float2 u = next;
         next = t + kRow < T ? act[(size_t)(t + kRow) * A + i] : none;
         StepState o;
-        run_block<DELTA>(c, u, n, sub, L, a.dt, a.vmax, o);
+        run_block<DELTA, ONE>(c, u, n, sub, L, a.dt, a.vmax, o);
         if (n == kRow) c = after_block(o, kRow);
         if (on && t % C == 0) {
             float *ck = ckpt + (size_t)(t / C) * 4 * A;
@@ -493,7 +519,7 @@ __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_fwd(SimArgs a, cons
             ck[2 * A + i] = o.yaw0;
             ck[3 * A + i] = o.v0;
         }
-        const EdgeChoice ch = nearest_edges(e, ls, o.x1, o.y1, on, a.R_obs, sub, bd, true);
+        const EdgeChoice ch = nearest_edges<ONE>(e, ls, o.x1, o.y1, on, a.R_obs, sub, bd, true);
         const float rw = smooth_reward(o.x1, o.y1, o.sn1, o.cs1, gx, gy, e.es, ch, a.R_obs);
         if (on) {
             rewards[(size_t)t * A + i] = rw;
@@ -785,7 +811,7 @@ enum ObsGrad { kObsNone = 0, kObsScratch = 1, kObsGather = 2 };
 // Steps [Ts, Te) of the backward: all of them, unless the observation's gradient og, of these
 // steps, comes in parts (kObsScratch): then the adjoint of the state before the part is kept in
 // `carry`.  kObsGather reads slog and grad_obs instead.
-template <bool DELTA, int OBS>
+template <bool DELTA, int OBS, bool ONE>
 __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, const float2 *__restrict__ act,
                                                               const float *__restrict__ ckpt, int T, int C,
                                                               int B, int Ts, int Te,
@@ -796,9 +822,10 @@ __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, cons
                                                               const float *__restrict__ grad_obs,
                                                               float2 *__restrict__ grad_a,
                                                               float *__restrict__ grad_s0) {
-    __shared__ float4 s_seg[kRollAgents * kEdgeStride];
-    __shared__ float2 s_inv[kRollAgents * kEdgeStride];
-    __shared__ float s_dc[kRollAgents * kEdgeStride];
+    constexpr int kList = ONE ? 1 : kRollAgents * kEdgeStride;
+    __shared__ float4 s_seg[kList];
+    __shared__ float2 s_inv[kList];
+    __shared__ float s_dc[kList];
     const int row = threadIdx.x / kRow, sub = threadIdx.x % kRow;
     const int i = xcd_tile(blockIdx.x, gridDim.x) * kRollAgents + row;
     if (i >= a.A) return;
@@ -820,8 +847,8 @@ __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, cons
     }
     EdgeBound bd{0.f, 0.f, 0.f, -1};
     // blocks of B steps, last one first
-    for (int t0 = (Te - 1) / B * B; t0 >= Ts; t0 -= B) {
-        const int n = min(B, Te - t0), t = t0 + sub;
+    for (int t0 = ONE ? 0 : (Te - 1) / B * B; t0 >= Ts; t0 -= B) {
+        const int n = ONE ? 1 : min(B, Te - t0), t = t0 + sub;
         const bool on = sub < n;
         const float gr = on ? grad_r[(size_t)t * A + i] : 0.0f;
         float4 og_t = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -837,15 +864,15 @@ __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, cons
         StepState o;
         float2 u;
         for (int tb = t0 / C * C;;) {
-            const bool own = tb == t0;
+            const bool own = ONE || tb == t0;
             const int m = own ? n : min(kRow, t0 - tb);
             u = sub < m ? act[(size_t)(tb + sub) * A + i] : make_float2(0.f, 0.f);
-            run_block<DELTA>(c, u, m, sub, L, dt, vmax, o);
+            run_block<DELTA, ONE>(c, u, m, sub, L, dt, vmax, o);
             if (own) break;
             c = after_block(o, m);
             tb += m;
         }
-        const EdgeChoice ch = nearest_edges(e, ls, o.x1, o.y1, on, a.R_obs, sub, bd, false);
+        const EdgeChoice ch = nearest_edges<ONE>(e, ls, o.x1, o.y1, on, a.R_obs, sub, bd, false);
         // gradient of the step's reward (and observation) with respect to the state after
         // the step
         float gx = og_t.x, gy = og_t.y, gth = og_t.z, gv = og_t.w;
@@ -933,7 +960,7 @@ __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, cons
         // the recursion, last step first, on all lanes of the row; a lane keeps the adjoint
         // of the state after its step
         float kx = 0.f, ky = 0.f, kth = 0.f, kv = 0.f;
-        each_step_down(n, [&](auto kc) {
+        auto back = [&](auto kc) {
             constexpr int k = decltype(kc)::k;
             lx += row_bcast<k>(gx);
             ly += row_bcast<k>(gy);
@@ -950,7 +977,9 @@ __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, cons
             lv = row_bcast<k>(n3) * lth + lv;
             lth = row_bcast<k>(m1) * lx + lth;
             lth = row_bcast<k>(m2) * ly + lth;
-        });
+        };
+        if (ONE) back(StepIndex<0>{});
+        else each_step_down(n, back);
         // gradient of the step's action
         float2 ga;
         if (DELTA) {
@@ -1056,7 +1085,8 @@ static unsigned roll_blocks(int A) { return (unsigned)(((long long)A + kRollAgen
 hipError_t launch_rollout_fwd_impl(const SimArgs &a, const float2 *actions, int T, int C,
                                    float *rewards, float *ckpt, float *states, hipStream_t s) {
     if (C < 1 || C > kMaxCkpt) return hipErrorInvalidValue;
-    auto k = a.dyn == GD_DYN_DELTA ? k_rollout_fwd<true> : k_rollout_fwd<false>;
+    auto k = a.dyn == GD_DYN_DELTA ? (T == 1 ? k_rollout_fwd<true, true> : k_rollout_fwd<true, false>)
+                                   : (T == 1 ? k_rollout_fwd<false, true> : k_rollout_fwd<false, false>);
     hipLaunchKernelGGL(k, dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a, actions, T, C, rewards, ckpt, states);
     return hipGetLastError();
 }
@@ -1097,13 +1127,13 @@ hipError_t launch_rollout_obs_impl(const SimArgs &a, const float *states, int T,
     return hipSuccess;
 }
 
-template <bool DELTA>
+template <bool DELTA, bool ONE>
 static hipError_t launch_bwd(const SimArgs &a, const float2 *actions, const float *ckpt, int T, int C,
                              const float *grad_rewards, const float *grad_obs, const float *states, int max_agents,
                              void *scratch, float2 *grad_actions, float *grad_state0, hipStream_t s) {
     const int B = roll_block(T, C);
     if (!grad_obs || !scratch) {
-        auto k = grad_obs ? k_rollout_bwd<DELTA, kObsGather> : k_rollout_bwd<DELTA, kObsNone>;
+        auto k = grad_obs ? k_rollout_bwd<DELTA, kObsGather, ONE> : k_rollout_bwd<DELTA, kObsNone, ONE>;
         hipLaunchKernelGGL(k, dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a, actions, ckpt, T, C, B, 0, T,
                            grad_rewards, nullptr, nullptr, states, grad_obs, grad_actions, grad_state0);
         return hipGetLastError();
@@ -1126,7 +1156,7 @@ static hipError_t launch_bwd(const SimArgs &a, const float2 *actions, const floa
                            lds, s, a, states, Ts, share, grad_obs, og);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_rollout_bwd<DELTA, kObsScratch>), dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a,
+        hipLaunchKernelGGL((k_rollout_bwd<DELTA, kObsScratch, ONE>), dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a,
                            actions, ckpt, T, C, B, Ts, Te, grad_rewards, og, carry, nullptr, nullptr, grad_actions,
                            grad_state0);
         if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1139,7 +1169,8 @@ hipError_t launch_rollout_bwd_impl(const SimArgs &a, const float2 *actions, cons
                                    const float *states, int max_agents, void *scratch, float2 *grad_actions,
                                    float *grad_state0, hipStream_t s) {
     if (C < 1 || C > kMaxCkpt) return hipErrorInvalidValue;
-    auto f = a.dyn == GD_DYN_DELTA ? launch_bwd<true> : launch_bwd<false>;
+    auto f = a.dyn == GD_DYN_DELTA ? (T == 1 ? launch_bwd<true, true> : launch_bwd<true, false>)
+                                   : (T == 1 ? launch_bwd<false, true> : launch_bwd<false, false>);
     return f(a, actions, ckpt, T, C, grad_rewards, grad_obs, states, max_agents, scratch, grad_actions, grad_state0, s);
 }
 
