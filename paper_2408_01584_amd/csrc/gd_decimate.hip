@@ -9,11 +9,11 @@
 // decide which points survive, so they are computed in binary32 with a fixed operation
 // order (no contraction).
 //
-// The removals are sequential by definition, and taking them one at a time is a chain of LDS
-// round trips and wave minima (about 1250 cycles each).  Up to 4096 points a polyline is
-// taken by chunks that run ahead of each other (vw_chunks: a wave up to 512 points, a workgroup
-// beyond), longer ones and the few that the chunks take out of order round by round
-// (vw_polyline, areas and links in LDS up to 6144 points, else in the caller's workspace).
+// The removals are sequential by definition, and taking them one at a time (vw_single) is a chain
+// of LDS round trips and wave minima.  Up to 4096 points a polyline is taken by chunks that run
+// ahead of each other (vw_chunks: a wave up to 512 points, a workgroup beyond) unless it is short
+// or mostly ties, or the chunks took it out of order; longer ones round by round (vw_polyline,
+// areas and links in LDS up to 6144 points, else in the caller's workspace).
 //
 // Rounds: every removal that is certain to be among the next ones is taken at once.
 // A key is (area bits, index): areas are >= 0, so their bit patterns order like the values;
@@ -32,9 +32,8 @@
 //
 // 2560 polylines of 2600 points on average (64 maps sampled every 0.1 m, 97 % of the points
 // removed): one point at a time 9.2 ms, rounds 1.64 ms (190 of 4500 cycles), chunks 0.80 to 0.87 ms.
-// On straight lines, whose areas are all equal, nothing can be taken at the same time: 2600
-// points 8.1 ms one at a time, 8.6 ms by chunks, 36 ms by rounds; 500 points 1.5, 0.5 and
-// 2.0 ms.
+// On straight lines, whose areas are all equal, nothing can be taken at the same time: 512 lines
+// of 2600 points 1.19 ms one at a time, 2.2 ms by chunks; one of 7000 points 51 ms by rounds.
 #include <algorithm>
 
 #include "gd_internal.h"
@@ -221,6 +220,72 @@ __device__ __forceinline__ void vw_polyline(int n, int tid, DecShared<TH> &sh, c
     write_kept<TH>(n, tid, X, Y, AR, PRV, NXT, keep, dir);
 }
 
+// ---- the same removals, one at a time, by one wave
+// Lane c keeps the smallest key of the 64 points from 64 c on.  A removal takes its own chunk's
+// smallest key, so that chunk is searched again; in a neighbour's chunk only if the neighbour
+// was its smallest and grew.  Bound by one chain of latencies per removal, about 900 cycles: two
+// wave minima, two dependent reads of links, the coordinates, and stores.  AR, PRV and NXT are set; removed points are marked in AR (kRemoved); point(k) gives the coordinates.
+constexpr int kDecSingle = kWave * kWave;  // points, at most
+
+template <typename P>
+__device__ __forceinline__ void vw_single(int n, int lane, P &&point, float *AR, unsigned short *PRV, unsigned short *NXT,
+                                          float min_area) {
+    const unsigned lim = __float_as_uint(min_area);  // areas >= 0 order like their bits
+    unsigned bb = kRemoved;  // smallest area of this lane's chunk, and its first point
+    int bk = 0;
+    // searches chunk c, whose point 64 c + lane has area bits v on this lane
+    auto search = [&](int c, unsigned v) {
+        const unsigned m = wave_min_u32(v);
+        const int first = __ffsll((long long)__builtin_amdgcn_ballot_w64(v == m)) - 1;
+        bb = lane == c ? m : bb;
+        bk = lane == c ? c * kWave + first : bk;
+    };
+    auto area_bits = [&](int c) {
+        const int k = c * kWave + lane;
+        const unsigned v = __float_as_uint(AR[min(k, n - 1)]);
+        return k < n ? v : kRemoved;
+    };
+    for (int c = 0; c * kWave < n; c++) search(c, area_bits(c));
+    for (;;) {
+        const unsigned m = wave_min_u32(bb);
+        if (!(m < lim)) break;  // (also when only end points remain)
+        // (chunks are in order: the first that holds the minimum has its lowest index)
+        const int q = __builtin_amdgcn_readlane(bk, __ffsll((long long)__builtin_amdgcn_ballot_w64(bb == m)) - 1);
+        const int cq = q >> 6;
+        const unsigned vq = area_bits(cq);
+        const int l = PRV[q], r = NXT[q];
+        const int bl = PRV[l], br = NXT[r], l2 = l > 0 ? bl : l, r2 = r < n - 1 ? br : r;
+        const float2 xl2 = point(l2), xl = point(l), xr = point(r), xr2 = point(r2);
+        const float al = dec_area(xl2, xl, xr), ar = dec_area(xl, xr, xr2);
+        const unsigned nl = __float_as_uint(l > 0 ? al : INFINITY), nr = __float_as_uint(r < n - 1 ? ar : INFINITY);
+        if (lane == 0) {
+            NXT[l] = (unsigned short)r;
+            PRV[r] = (unsigned short)l;
+            AR[q] = __uint_as_float(kRemoved);
+            AR[l] = __uint_as_float(nl);
+            AR[r] = __uint_as_float(nr);
+        }
+        wave_sync();
+        const int k = cq * kWave + lane;
+        search(cq, k == q ? kRemoved : k == l ? nl : k == r ? nr : vq);
+        // the neighbours' chunks, where they are others (end points keep their area)
+        auto neighbour = [&](int p, unsigned v) {
+            const int c = p >> 6;
+            if (c == cq) return;
+            const bool me = lane == c, less = v < bb || (v == bb && p < bk);
+            if (__builtin_amdgcn_ballot_w64(me && bk == p && !less) != 0ull) {
+                search(c, area_bits(c));
+            } else {
+                bb = me && less ? v : bb;
+                bk = me && less ? p : bk;
+            }
+        };
+        const int sl = __builtin_amdgcn_readfirstlane(l), sr = __builtin_amdgcn_readfirstlane(r);
+        if (sl > 0) neighbour(sl, nl);
+        if (sr < n - 1) neighbour(sr, nr);
+    }
+}
+
 // ---- the same removals, by chunks of the polyline that run ahead of each other
 // The order of two removals matters only if they are neighbours.  Each thread owns a chunk of
 // consecutive surviving points and takes its own next removals as long as their keys are
@@ -240,7 +305,7 @@ __device__ __forceinline__ void vw_polyline(int n, int tid, DecShared<TH> &sh, c
 // When every removal passes, any two that touch each other's points were taken in the order of
 // their times, and no point was passed over at its time, so sorted by their times they are
 // the removals of the definition.  When one does not pass, the polyline is taken again with
-// larger chunks, then by vw_polyline: never on straight lines and circles, on 1 of 7000 noisy curves, on up to 19 %
+// larger chunks, then by vw_single: never on straight lines and circles, on 1 of 7000 noisy curves, on up to 19 %
 // of random points on a few integer positions.  (1.1 million polylines compared with the
 // definition on the CPU.)  When an eighth of the points is gone the chunks are dealt out anew.
 //
@@ -263,6 +328,7 @@ struct ChunkShared {
     unsigned short count[TH];  // its surviving points
     int part[TH / kWave];
     int removed, wrong;
+    int below, ties;  // areas below the limit, and how many of them equal their neighbour's
 };
 
 template <int TH>
@@ -271,6 +337,38 @@ union DecAnyShared {
     ChunkShared<TH> chunks;
 };
 
+// Areas, links and the rest that vw_chunks starts from.  Ties are counted among the 16 lanes of a
+// row, in 15 of 16 places.
+template <int TH>
+__device__ __forceinline__ void dec_begin(int n, int tid, ChunkShared<TH> &sh, const float *X, const float *Y, float *AR,
+                                          unsigned short *PRV, unsigned short *NXT, unsigned short *G,
+                                          unsigned short *LST, float min_area) {
+    if (tid == 0) sh.removed = sh.wrong = sh.below = sh.ties = 0;
+    dec_sync<TH>();  // (also the polyline or the attempt before)
+    int below = 0, ties = 0;  // of the wave
+    for (int k0 = 0; k0 < n; k0 += TH) {
+        const int k = k0 + tid;
+        float area = INFINITY;
+        if (k < n) {
+            if (k > 0 && k < n - 1) area = dec_area(X, Y, k - 1, k, k + 1);
+            PRV[k] = (unsigned short)(k - 1);
+            NXT[k] = (unsigned short)(k + 1);
+            AR[k] = area;
+            G[k] = kNoGap;
+            LST[k] = (unsigned short)k;
+        }
+        const int v = __float_as_int(area), before = __builtin_amdgcn_update_dpp(~v, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+        const bool in = area < min_area;
+        below += __popcll(__builtin_amdgcn_ballot_w64(in));
+        ties += __popcll(__builtin_amdgcn_ballot_w64(in && v == before));
+    }
+    if ((tid & (kWave - 1)) == 0) {
+        atomicAdd(&sh.below, below);
+        atomicAdd(&sh.ties, ties);
+    }
+    dec_sync<TH>();
+}
+
 // G: by point, the point whose key is the time of the last removal in the gap after it (its
 // area stays in AR, with the sign bit set); LST: the surviving points in order.  False: a
 // removal was out of order, nothing is valid.  At most MOST points.
@@ -278,17 +376,6 @@ template <int TH, int MOST>
 __device__ __forceinline__ bool vw_chunks(int n, int tid, ChunkShared<TH> &sh, const float *X, const float *Y, float *AR,
                           unsigned short *PRV, unsigned short *NXT, unsigned short *G, unsigned short *LST,
                           float min_area, int chunk) {
-    for (int k = tid; k < n; k += TH) {
-        PRV[k] = (unsigned short)(k - 1);
-        NXT[k] = (unsigned short)(k + 1);
-        AR[k] = (k > 0 && k < n - 1) ? dec_area(X, Y, k - 1, k, k + 1) : INFINITY;
-        G[k] = kNoGap;
-        LST[k] = (unsigned short)k;
-    }
-    if (tid == 0) {
-        sh.removed = sh.wrong = 0;
-    }
-    dec_sync<TH>();
     const unsigned lim = __float_as_uint(min_area);  // areas >= 0 order like their bits
     auto gap = [&](int k) -> u64 {  // (no branch: the reads of a removal go out together)
         const int g = G[k], h = g == kNoGap ? 0 : g;
@@ -422,6 +509,48 @@ __device__ __forceinline__ bool vw_chunks(int n, int tid, ChunkShared<TH> &sh, c
     }
 }
 
+constexpr int kDecShort = 512;    // points of a polyline taken by one wave (8 per lane)
+constexpr int kDecChunked = 4096;  // points taken by chunks (12 B of LDS each)
+
+// The removals of a polyline of up to MOST points, by chunks or one at a time.  The chunks need
+// points that can be removed at the same time, and equal areas leave few: with index order
+// among them a run of ties is a chain.  So polylines with ties in more than 3 of 7 places
+// (straight lines along an axis, lines on a raster, walks on one) are taken one at a time; with a
+// workgroup up to 2048 points more than 5 of 9, as the larger ones mostly come out of order.  And
+// short ones: up to 128 points, or 160 where more than a quarter ties (straight lines whose areas
+// are rounding).  One at a time and by chunks, us: straight 2600 points 1122 and 2018 (1559 before
+// there were chunks), 1/4 m raster 981 and 1241 (1210); walk on integers 300 points 74 and 137
+// (88), 1000 points 210 and 126 (257), 4096 points 815 and 1165 (984); oblique line of 150 points
+// 71 and 93 (84), of 300 139 and 137; noisy curve of 100 points 47 and 56 (55), of 200 92 and 68.
+// mem: areas and links of `stride` points (8 B each), then what the chunks need (4 B) or the
+// coordinates of `room` points (8 B).
+template <int TH, int MOST>
+__device__ __forceinline__ void vw_any(int n, int tid, ChunkShared<TH> &sh, const float *X, const float *Y, float *mem,
+                                       int stride, int room, float min_area) {
+    static_assert(MOST <= kDecSingle, "one chunk per lane of a wave");
+    float *AR = mem;
+    unsigned short *PRV = reinterpret_cast<unsigned short *>(mem + stride), *NXT = PRV + stride, *G = NXT + stride;
+    dec_begin<TH>(n, tid, sh, X, Y, AR, PRV, NXT, G, G + stride, min_area);
+    const int below = sh.below, ties = sh.ties;
+    const bool some = ties * 4 > below, half = ties * 7 > below * 3, most = ties * 9 > below * 5;
+    if (n > (some ? 160 : 128) && !(n > kDecShort && n <= kDecChunked / 2 ? most : half)) {
+        for (int chunk = kChunk; chunk <= kChunkAgain; chunk += kChunkAgain - kChunk) {
+            if (vw_chunks<TH, MOST>(n, tid, sh, X, Y, AR, PRV, NXT, G, G + stride, min_area, chunk)) return;
+            dec_begin<TH>(n, tid, sh, X, Y, AR, PRV, NXT, G, G + stride, min_area);
+            if (some) break;  // (larger chunks would hardly pass)
+        }
+    }
+    if (n <= room) {
+        float2 *xy = reinterpret_cast<float2 *>(G);
+        for (int k = tid; k < n; k += TH) xy[k] = dec_point(X, Y, k);
+        dec_sync<TH>();
+        if (tid < kWave) vw_single(n, tid, [&](int k) { return xy[k]; }, AR, PRV, NXT, min_area);
+    } else if (tid < kWave) {
+        vw_single(n, tid, [&](int k) { return dec_point(X, Y, k); }, AR, PRV, NXT, min_area);
+    }
+    dec_sync<TH>();
+}
+
 struct DecArgs {
     const int *off;
     int n_poly, n_points;
@@ -440,9 +569,9 @@ __device__ __forceinline__ int dec_range(const DecArgs &a, int pl, int &s) {
     return min(max(a.off[pl + 1], s), a.n_points) - s;
 }
 
-constexpr int kDecShort = 512;    // points of a polyline taken by one wave (8 per lane)
 constexpr int kDecThreads = 256;   // threads of a longer one
-constexpr int kDecChunked = 4096;  // points taken by chunks (12 B of LDS each)
+// points taken one at a time with their coordinates in LDS (16 B each) where chunks take 12 B
+constexpr int kDecShortStaged = kDecShort * 3 / 4, kDecStaged = 3072;
 constexpr int kDecLinks = 6144;   // points whose areas and links fit the LDS (8 B each)
 
 // A workgroup (or wave) takes every kDecMaxBlocks-th group of polylines: grids are limited to
@@ -452,9 +581,9 @@ constexpr int kDecMaxBlocks = 1 << 20;
 // Polylines of up to kDecShort points, a wave each.
 constexpr int kDecShortWaves = 4;
 __global__ __launch_bounds__(kDecShortWaves *kWave) void k_decimate_short(DecArgs a) {
-    __shared__ float areas[kDecShortWaves][kDecShort];
-    __shared__ unsigned short links[kDecShortWaves][4 * kDecShort];
-    __shared__ DecAnyShared<kWave> shared[kDecShortWaves];
+    __shared__ __align__(16) float mem[kDecShortWaves][3 * kDecShort];
+    static_assert(kDecShortStaged * 4 <= kDecShort * 3, "one block of LDS");
+    __shared__ ChunkShared<kWave> shared[kDecShortWaves];
     const int g = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int tid = threadIdx.x % kWave;
     for (long long pl = (long long)blockIdx.x * kDecShortWaves + g; pl < a.n_poly; pl += (long long)gridDim.x * kDecShortWaves) {
@@ -462,47 +591,30 @@ __global__ __launch_bounds__(kDecShortWaves *kWave) void k_decimate_short(DecArg
         const int n = dec_range(a, (int)pl, s);
         if (n < 1 || n > kDecShort) continue;
         const float *x = a.x + s, *y = a.y + s;
-        unsigned short *prv = links[g], *nxt = prv + kDecShort;
-        bool done = false;
-        for (int chunk = kChunk; chunk <= kChunkAgain && !done; chunk += kChunkAgain - kChunk) {
-            wave_sync();
-            done = vw_chunks<kWave, kDecShort>(n, tid, shared[g].chunks, x, y, areas[g], prv, nxt, nxt + kDecShort,
-                                               nxt + 2 * kDecShort, a.min_area, chunk);
-        }
-        if (done) {
-            write_kept<kWave>(n, tid, x, y, areas[g], prv, nxt, a.keep + s, a.dir + s);
-            continue;
-        }
-        wave_sync();
-        vw_polyline<kWave, unsigned short, true>(n, tid, shared[g].rounds, x, y, areas[g], prv, nxt, a.min_area, a.keep + s,
-                                                 a.dir + s);
+        const int stride = n <= kDecShortStaged ? kDecShortStaged : kDecShort;
+        vw_any<kWave, kDecShort>(n, tid, shared[g], x, y, mem[g], stride, kDecShortStaged, a.min_area);
+        const unsigned short *prv = reinterpret_cast<unsigned short *>(mem[g] + stride);
+        write_kept<kWave>(n, tid, x, y, mem[g], prv, prv + stride, a.keep + s, a.dir + s);
     }
 }
 
-// Polylines of up to kDecLinks points, a workgroup each: by chunks up to kDecChunked points,
-// round by round beyond and where the chunks were out of order.
+// Polylines of up to kDecLinks points, a workgroup each: round by round from kDecChunked points on.
 __global__ __launch_bounds__(kDecThreads) void k_decimate(DecArgs a) {
-    __shared__ float mem[kDecLinks * 2];
+    __shared__ __align__(16) float mem[kDecLinks * 2];
     __shared__ DecAnyShared<kDecThreads> shared;
-    static_assert(kDecChunked * 3 <= kDecLinks * 2, "one block of LDS");
+    static_assert(kDecChunked * 3 <= kDecLinks * 2 && kDecStaged * 4 <= kDecLinks * 2, "one block of LDS");
     static_assert(kDecLinks % (kDecUnroll * kDecThreads) == 0, "padded");
     const int tid = threadIdx.x;
     for (long long pl = blockIdx.x; pl < a.n_poly; pl += gridDim.x) {
         int s;
         const int n = dec_range(a, (int)pl, s);
         if (n <= kDecShort || n > kDecLinks) continue;
-        bool done = false;
         if (n <= kDecChunked) {
-            unsigned short *link = reinterpret_cast<unsigned short *>(mem + kDecChunked);
-            for (int chunk = kChunk; chunk <= kChunkAgain && !done; chunk += kChunkAgain - kChunk) {
-                __syncthreads();
-                done = vw_chunks<kDecThreads, kDecChunked>(n, tid, shared.chunks, a.x + s, a.y + s, mem, link, link + kDecChunked,
-                                                           link + 2 * kDecChunked, link + 3 * kDecChunked, a.min_area, chunk);
-            }
-            if (done) {
-                write_kept<kDecThreads>(n, tid, a.x + s, a.y + s, mem, link, link + kDecChunked, a.keep + s, a.dir + s);
-                continue;
-            }
+            const int stride = n <= kDecStaged ? kDecStaged : kDecChunked;
+            vw_any<kDecThreads, kDecChunked>(n, tid, shared.chunks, a.x + s, a.y + s, mem, stride, kDecStaged, a.min_area);
+            const unsigned short *prv = reinterpret_cast<unsigned short *>(mem + stride);
+            write_kept<kDecThreads>(n, tid, a.x + s, a.y + s, mem, prv, prv + stride, a.keep + s, a.dir + s);
+            continue;
         }
         __syncthreads();
         unsigned short *link = reinterpret_cast<unsigned short *>(mem + kDecLinks);
