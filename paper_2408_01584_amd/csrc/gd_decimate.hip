@@ -623,17 +623,28 @@ __global__ __launch_bounds__(kDecThreads) void k_decimate(DecArgs a) {
     }
 }
 
-// Polylines of more than kDecLinks points, areas and links in the workspace.
-constexpr int kDecLong = 1024;
+// Polylines of more than kDecLinks points, areas and links in the workspace.  A workgroup looks
+// through every gridDim.x-th polyline, a thread each: few workgroups, as there is usually nothing
+// to do for them (10 000 polylines of 2 points: 24.0 us a call with a workgroup each, 19.6 so).
+constexpr int kDecLong = 1024, kDecLongBlocks = 512;
 __global__ __launch_bounds__(kDecLong) void k_decimate_long(DecArgs a) {
     __shared__ DecShared<kDecLong> shared;
-    for (long long pl = blockIdx.x; pl < a.n_poly; pl += gridDim.x) {
-        int s;
-        const int n = dec_range(a, (int)pl, s);
-        if (n <= kDecLinks) continue;
+    __shared__ int found[kDecLong], count;
+    for (long long p0 = blockIdx.x; p0 < a.n_poly; p0 += (long long)gridDim.x * kDecLong) {
         __syncthreads();
-        vw_polyline<kDecLong, int, false>(n, threadIdx.x, shared, a.x + s, a.y + s, a.area + s, a.prv + s, a.nxt + s, a.min_area,
-                             a.keep + s, a.dir + s);
+        if (threadIdx.x == 0) count = 0;
+        __syncthreads();
+        const long long pl = p0 + (long long)gridDim.x * threadIdx.x;
+        int s = 0;
+        if (pl < a.n_poly && dec_range(a, (int)pl, s) > kDecLinks) found[atomicAdd(&count, 1)] = (int)pl;
+        __syncthreads();
+        const int m = count;
+        for (int k = 0; k < m; k++) {
+            const int n = dec_range(a, found[k], s);
+            __syncthreads();
+            vw_polyline<kDecLong, int, false>(n, threadIdx.x, shared, a.x + s, a.y + s, a.area + s, a.prv + s, a.nxt + s,
+                                              a.min_area, a.keep + s, a.dir + s);
+        }
     }
 }
 
@@ -650,7 +661,7 @@ hipError_t launch_decimate_impl(const int *poly_off, int n_poly, int n_points, c
     hipLaunchKernelGGL(k_decimate_short, blocks(kDecShortWaves), dim3(kDecShortWaves * kWave), 0, s, a);
     if (n_points > kDecShort) hipLaunchKernelGGL(k_decimate, blocks(1), dim3(kDecThreads), 0, s, a);
     if (n_points > kDecLinks)
-        hipLaunchKernelGGL(k_decimate_long, dim3(n_poly < 65536 ? n_poly : 65536), dim3(kDecLong), 0, s, a);
+        hipLaunchKernelGGL(k_decimate_long, dim3(std::min(n_poly, kDecLongBlocks)), dim3(kDecLong), 0, s, a);
     return hipGetLastError();
 }
 

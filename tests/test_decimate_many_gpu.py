@@ -22,3 +22,15 @@ def test_more_polylines_than_workgroups_fit(gpu, oracle_mod):
     y = (0.3 * np.sin(s / 6) + rng.normal(0, 0.01, len(s))).astype(np.float32)
     kept = _compare(oracle_mod, off, x, y, 0.05)
     assert 0 < kept < len(s)
+
+
+def test_long_polylines_of_one_workgroup(gpu, oracle_mod):
+    """Polylines beyond the LDS sizes at a distance of 512, which one workgroup takes in turn."""
+    lens = np.full(1100, 3)
+    lens[[3, 515, 1027, 1028]] = [6200, 6145, 6400, 6144]
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rng = np.random.default_rng(9)
+    s = np.arange(off[-1]) * 0.1
+    x = (s + rng.normal(0, 0.01, len(s))).astype(np.float32)
+    y = (0.3 * np.sin(s / 6) + rng.normal(0, 0.01, len(s))).astype(np.float32)
+    _compare(oracle_mod, off, x, y, 0.05)
