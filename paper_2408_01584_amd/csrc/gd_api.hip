@@ -175,109 +175,6 @@ static long long partner_slots_of(const gd_config *c, const int32_t *h_agent_off
     return s;
 }
 
-// Launch shape of the step kernel: waves per workgroup, distance bins, candidate-list
-// entries per wave, and whether the road is staged in LDS.  Fields the config fixes are
-// kept; of the shapes that fit, the one with the lowest predicted step time is taken.
-//
-// The prediction (microseconds) was fitted to measured steps of 47 batches (1 to 4096
-// worlds, 2 to 128 agents each, even and uneven, 500 to 10 000 road points, K 32 to 960;
-// 12 to 24 shapes each): the shape it picks is 0.8 % slower on average than the fastest one
-// measured, 6.6 % at most.  A rule that took the most resident waves per compute unit, then
-// 512 bins, was 17 % slower on average (512 x 32 agents: 41 against 28.7 us, 1024 x 64 with
-// 6000 points: 241 against 175).  Its terms:
-//   - a workgroup takes a fixed time for its world phases, more with the square of the agents
-//     over its waves (pairs) and with the points it stages, then its share of the agents
-//     one after the other, at a time per agent that grows with K;
-//   - that time is a latency at few waves per compute unit and grows with their number where
-//     the vector units are shared; reading the road through the caches costs more, the more
-//     so when the roads of the worlds in flight outgrow an XCD's 4 MB of L2;
-//   - the batch takes as many rounds of workgroups as the compute units hold at once.  An
-//     uneven batch is dispatched longest world first, so its last round is filled.
-// 128 and 256 bins measured alike (512 and more up to 7 % slower: their prefix scan), and the
-// length of the candidate list does not matter as long as it holds the points in the radius.
-struct Batch {  // what the prediction needs to know of the worlds
-    int worlds = 0, max_agents = 0, max_road = 0, max_edges = 0, cell_cap4 = 0, agent_cap = 0;
-    bool idx16 = true, uneven = false;
-    double agents = 0.0, road = 0.0;  // means
-};
-
-struct Shape {
-    double us = INFINITY;
-    int waves = 0, bins = 0, cand_cap = 0, edge_cap = 0, road_cap = 0;
-};
-
-constexpr int kComputeUnits = 256;
-
-static double predict_step(const Batch &b, int K, bool staged, int waves, int per_cu) {
-    const int per_unit = (b.worlds + kComputeUnits - 1) / kComputeUnits;  // workgroups of a compute unit
-    const int in_flight = std::min(per_cu, per_unit);
-    double fixed = 6.0 + 0.0038 * b.agents * b.agents / waves + (staged ? 0.0144 * b.road / waves : 0.0);
-    if (per_unit == 1) fixed *= 1.0 + 0.23 * (16 - waves) / 16;  // (nothing else to overlap it)
-    fixed *= 1.0 + 0.02 * in_flight * std::sqrt((double)waves);
-    double latency = staged ? 5.8 : 7.2, share = staged ? 0.33 : 0.43;
-    if (!staged) {
-        const double mb = 32.0 * in_flight * b.road * 16e-6;  // roads in flight per XCD
-        const double x = std::max(0.0, std::min(1.0, (mb - 1.9) / 4.1));
-        latency *= 1.0 + 0.05 * x;
-        share *= 1.0 + 0.45 * x + 0.05 * std::max(0.0, std::log2(std::max(mb, 1e-3) / 6.6));
-    }
-    share *= in_flight * waves;
-    const double agent = std::cbrt(latency * latency * latency + share * share * share) * (0.375 + 0.0025 * K);
-    const double slots = (double)kComputeUnits * per_cu;
-    const double n = b.uneven && b.worlds <= slots ? b.max_agents : b.agents;
-    const double each = fixed + std::max(1.0, n / waves + (n > waves ? 0.45 : 0.0)) * agent;
-    double rounds = b.uneven ? std::max(1.0, b.worlds / slots + 0.4) : (double)per_unit / per_cu;
-    if (!b.uneven && (rounds <= 1.0 || per_cu == 1)) rounds = std::max(1.0, rounds);
-    else if (!b.uneven && per_unit % per_cu != 0) rounds += 0.15;
-    return each * rounds * (b.agents > 20.0 * waves ? 1.3 : 1.0);
-}
-
-static Shape best_shape(const gd_config *c, const Batch &b, bool staged) {
-    const int K = c->top_k;
-    Shape best;
-    // a multiple of 4 points keeps the LDS regions after the road 16-byte aligned
-    const int rc = staged ? (std::max(b.max_road, 1) + 3) / 4 * 4 : 0;
-    for (int ec : {b.max_edges, 0}) {
-        for (int wv : {16, 12, 8, 4, 2, 1}) {
-            if (c->obs_waves && wv != c->obs_waves) continue;
-            for (int nb : {256, 128, 512, 64, 1024}) {
-                if (c->obs_bins ? nb != c->obs_bins : nb == 1024) continue;
-                const int per_cu_regs = step_waves_per_cu(nb, staged, b.idx16) / wv;
-                for (int cc : {128, 256, 384, 512, 768, 1024}) {
-                    if (c->obs_cands && cc != c->obs_cands) continue;
-                    const size_t lds = step_lds_bytes(wv, nb, K, K ? cc : 0, rc, b.cell_cap4, ec, b.agent_cap, b.idx16);
-                    if (lds > (size_t)kLdsBytes) continue;
-                    const int per_cu = std::min((int)((size_t)kLdsBytes / lds), per_cu_regs);
-                    if (per_cu < 1) continue;
-                    double us = predict_step(b, K, staged, wv, per_cu);
-                    us *= nb == 256 ? 1.0 : nb == 128 ? 1.02 : 1.06;
-                    if (K && cc < 1.2 * K && cc < 1024) us *= 1.3;  // the grid scanned again
-                    us *= 1.0 + 1e-5 * cc / 128;                    // (the shortest list that does)
-                    if (!ec && b.max_edges) us *= 1.01;             // edge segments through the caches
-                    if (us < best.us) best = Shape{us, wv, nb, K ? cc : 0, ec, rc};
-                }
-            }
-        }
-    }
-    return best;
-}
-
-static bool launch_shape(const gd_config *c, const Batch &b, int &waves, int &bins, int &road_cap, int &edge_cap,
-                         int &cand_cap) {
-    const bool can_stage = c->top_k > 0 && b.idx16 && b.max_road <= 60000;
-    Shape glob, lds;
-    if (c->obs_road != GD_ROAD_LDS) glob = best_shape(c, b, false);
-    if (c->obs_road != GD_ROAD_GLOBAL && can_stage) lds = best_shape(c, b, true);
-    const Shape &pick = lds.us <= glob.us ? lds : glob;
-    if (!pick.waves) return false;
-    waves = pick.waves;
-    bins = pick.bins;
-    cand_cap = pick.cand_cap;
-    edge_cap = pick.edge_cap;
-    road_cap = pick.road_cap;
-    return true;
-}
-
 // workgroup order: costliest worlds first, so that the in-order dispatch of workgroups
 // acts as a longest-processing-time-first schedule over the compute units.  The cost model
 // n (r + 1000) + 3 n^2 (n agents, r road points) was fitted to measured per-workgroup
@@ -571,20 +468,24 @@ gd_status gd_create(const gd_config *cfg, const int32_t *h_agent_off, const int3
         batch.idx16 = max_road < 65536;
         batch.agents = (double)A / W;
         batch.road = (double)R / W;
+        for (int w = 0; w < W; w++) {
+            const double area = (double)grids[w].nx * grids[w].ny * grids[w].cs * grids[w].cs, r = cfg->obs_radius;
+            batch.within += (h_road_off[w + 1] - h_road_off[w]) * std::min(1.0, M_PI * r * r / area) / W;
+        }
         for (int w = 0; w < W; w++) batch.uneven = batch.uneven || h_agent_off[w + 1] - h_agent_off[w] != max_agents;
-        int waves = 0, bins = 0, road_cap = 0, edge_cap = 0, cand_cap = 0;
-        if (!launch_shape(cfg, batch, waves, bins, road_cap, edge_cap, cand_cap)) {
+        Shape shape;
+        if (!launch_shape(*cfg, batch, step_waves_per_cu, shape)) {
             delete sim;
             return fail(GD_E_SIZE, "no launch shape fits the LDS (top_k %d, %d agents per world)",
                         cfg->top_k, max_agents);
         }
-        sim->waves = waves;
-        sim->bins = bins;
-        sim->ctl.road_cap = road_cap;
+        sim->waves = shape.waves;
+        sim->bins = shape.bins;
+        sim->ctl.road_cap = shape.road_cap;
         sim->ctl.idx16 = batch.idx16 ? 1 : 0;
         sim->ctl.cell_cap4 = batch.cell_cap4;
-        sim->ctl.edge_cap = edge_cap;
-        sim->ctl.cand_cap = cand_cap;
+        sim->ctl.edge_cap = shape.edge_cap;
+        sim->ctl.cand_cap = shape.cand_cap;
         // LIDAR: the world's agents staged in LDS, and its edge segments too when that
         // keeps as many workgroups resident per compute unit as reading them through the
         // caches (on 4096 worlds of 6000 points, staging left one workgroup per CU and

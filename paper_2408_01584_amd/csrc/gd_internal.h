@@ -6,10 +6,10 @@
 #include <stdint.h>
 
 #include "gd.h"
+#include "gd_shape.h"
 
 namespace gdk {
 
-constexpr int kWave = 64;
 constexpr int kGridAxis = GD_GRID_MAX_CELLS_PER_AXIS;        // cells per axis, at most
 constexpr int kGridCells = kGridAxis * kGridAxis;            // cells per world, at most
 constexpr int kCellStride = kGridCells + 1;                  // CSR row length per world
@@ -71,8 +71,6 @@ struct SimArgs {
 };
 
 enum StepMode { kModeStep = 0, kModeObs = 1, kModeReset = 2 };
-
-constexpr int kLdsBytes = 160 * 1024 - 1024;  // LDS of one gfx950 CU, less room for static LDS
 
 // Per-launch control block of the fused step kernel.
 struct StepCtl {
@@ -136,8 +134,6 @@ inline size_t decimate_ws_offset(long long n_points, int part) {
 // launchers (return hipError_t of the launch)
 hipError_t launch_build_grid(const SimArgs &a, float cell_size, hipStream_t s);
 hipError_t launch_step(const SimArgs &a, const StepCtl &c, int waves, int bins, hipStream_t s);
-size_t step_lds_bytes(int waves, int NB, int K, int ccap, int road_cap, int cell_cap4,
-                      int edge_cap, int agent_cap, bool idx16);
 int step_waves_per_cu(int bins, bool staged, bool idx16);
 
 // ---------------------------------------------------------------- device helpers

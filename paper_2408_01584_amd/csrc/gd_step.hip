@@ -151,8 +151,6 @@ __device__ __forceinline__ float wave_uniform(float v) {
 }
 __device__ __forceinline__ int wave_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-__host__ __device__ inline int stage_cap(int K) { return (K + 60 + 3) / 4 * 4; }
-
 // Point indices and packed (bin, point) candidates: 16-bit / 32-bit when every world has
 // fewer than 65536 road points, 32-bit / 64-bit otherwise.
 template <bool IDX16>
@@ -167,20 +165,6 @@ struct PointIndex<true> {
     using cand_t = unsigned;
     static constexpr int kShift = 16;
 };
-
-// per-wave LDS of phase 5:
-//   hist  NB ints        histogram of bin(d2), then the first (later: end) slot of each bin;
-//                        a 0 before it, the start of bin 0 (16 B)
-//   cand  ccap entries   (bin, point) of every point within the radius
-//   skey  scap floats    keys of the staged points (bins up to the cut bin)
-//   sq    scap indices   their points
-__host__ __device__ inline size_t wave_lds_bytes(int NB, int K, int ccap, bool idx16) {
-    const size_t ib = idx16 ? 2 : 4, cb = idx16 ? 4 : 8;
-    const size_t b = 16 + (size_t)NB * 4 + (size_t)ccap * cb + (size_t)stage_cap(K) * (4 + ib);
-    return (b + 15) / 16 * 16;
-}
-
-constexpr int kAgentArrays = 13;  // x y yaw v L W cos sin goal_x goal_y flags coll bound
 
 // one field of the agents' records in LDS (record of kAgentArrays words per agent)
 template <typename T>
@@ -951,15 +935,6 @@ __global__ __launch_bounds__(1024) void k_step(SimArgs a, StepCtl c) {
         if (lane == 0) a.kth[ai] = kth_key;
         wave_sync();
     }
-}
-
-size_t step_lds_bytes(int waves, int NB, int K, int ccap, int road_cap, int cell_cap4,
-                      int edge_cap, int agent_cap, bool idx16) {
-    const bool staged = road_cap > 0;
-    const size_t road = staged ? (size_t)road_cap * 16 + (size_t)cell_cap4 * 4 : 0;
-    const size_t edges = edge_cap > 0 ? (size_t)edge_cap * 16 + (size_t)cell_cap4 * 4 : 0;
-    const size_t per_wave = (size_t)waves * wave_lds_bytes(NB, K, ccap, idx16 || staged);
-    return road + (size_t)agent_cap * 4 * kAgentArrays + (edges > per_wave ? edges : per_wave);
 }
 
 // raise the kernel's dynamic-LDS limit to what this launch needs (once per size increase)
