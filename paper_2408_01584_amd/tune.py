@@ -5,12 +5,16 @@ that every shape gives the same bits): waves per workgroup, number of distance b
 the top-K selection, candidate-list entries per wave, the cell size of the per-world road
 grid, and whether the road is staged in LDS or read through the caches.  Which shape is fastest depends on the batch (agents and road points per
 world, K) and on the device, so it is measured: every candidate shape steps the given
-scene a few times and the one with the lowest mean step time wins.
+scene a few times and the one with the lowest mean step time wins.  The length of the
+candidate list is left to the library: a list that is long enough at the speeds of the
+timed steps can be too short later.
 
-Results are cached in a JSON file keyed by the workload signature and the device name.
+Results are cached in a JSON file keyed by the workload signature and the device name; a
+record lapses when the library changes.
 """
 from __future__ import annotations
 
+import functools
 import hashlib
 import json
 import os
@@ -21,10 +25,9 @@ CACHE = os.environ.get("GD_TUNE_CACHE", os.path.join(os.path.dirname(os.path.abs
                                                      "tuned_shapes.json"))
 
 DEFAULT_SPACE = [
-    dict(obs_waves=w, obs_bins=b, obs_cands=c, cell_size=cs, obs_road=rd)
+    dict(obs_waves=w, obs_bins=b, cell_size=cs, obs_road=rd)
     for rd in (1, 2)  # GD_ROAD_LDS, GD_ROAD_GLOBAL
     for w in (16, 12, 8, 4)
-    for c in (256, 512)
     for b in (128, 256, 512)
     for cs in (10.0, 15.0)
 ]
@@ -48,11 +51,21 @@ def _device_name() -> str:
     return "%s:%d" % (getattr(p, "gcnArchName", ""), p.multi_processor_count)
 
 
+@functools.lru_cache(maxsize=None)
+def _library() -> str:
+    """Digest of libgd.so."""
+    from . import gd
+    with open(gd.LIB_PATH, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:20]
+
+
 def _load():
     try:
-        return json.load(open(CACHE))
+        with open(CACHE) as f:
+            cache = json.load(f)
     except (OSError, ValueError):
         return {}
+    return {k: r for k, r in cache.items() if "library" not in r or r["library"] == _library()}
 
 
 def time_shape(scene, params, shape, actions, steps=20, warmup=5, graph=False) -> float:
@@ -118,7 +131,7 @@ def autotune(scene, params=None, space=None, steps=20, warmup=5, graph=False, us
     ms, best = min(results, key=lambda r: r[0])
     if use_cache:
         cache = _load()
-        cache[key] = {"shape": best, "ms_per_step": ms, "candidates": len(results)}
+        cache[key] = {"shape": best, "ms_per_step": ms, "candidates": len(results), "library": _library()}
         tmp = CACHE + ".tmp"
         with open(tmp, "w") as f:
             json.dump(cache, f, indent=1, sort_keys=True)
