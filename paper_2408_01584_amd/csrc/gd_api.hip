@@ -321,6 +321,9 @@ gd_status gd_create(const gd_config *cfg, const int32_t *h_agent_off, const int3
         max_agents = std::max(max_agents, h_agent_off[w + 1] - h_agent_off[w]);
     }
     const std::vector<int> order = world_order(W, h_agent_off, h_road_off);
+    int device = 0, compute_units = 0;
+    HIP_TRY(hipGetDevice(&device), "hipGetDevice");
+    HIP_TRY(hipDeviceGetAttribute(&compute_units, hipDeviceAttributeMultiprocessorCount, device), "compute units");
     hipStream_t s = (hipStream_t)stream;
     // device offsets must hold the host values
     {
@@ -355,6 +358,7 @@ gd_status gd_create(const gd_config *cfg, const int32_t *h_agent_off, const int3
     a.T_ep = cfg->episode_len;
     a.flags = cfg->flags;
     a.dyn = cfg->dynamics;
+    a.compute_units = std::max(compute_units, 1);
     a.dt = cfg->dt;
     a.R_obs = cfg->obs_radius;
     {
@@ -459,6 +463,7 @@ gd_status gd_create(const gd_config *cfg, const int32_t *h_agent_off, const int3
             max_edges = std::max(max_edges, g.n_edge);
         }
         Batch batch;
+        batch.compute_units = a.compute_units;
         batch.worlds = W;
         batch.max_agents = max_agents;
         batch.max_road = max_road;
@@ -496,7 +501,7 @@ gd_status gd_create(const gd_config *cfg, const int32_t *h_agent_off, const int3
         sim->lctl.edge_cap = 0;
         // few worlds: several workgroups each, until there are three per compute unit or a
         // wave has one agent
-        sim->lctl.parts = std::max(1, std::min(3 * kComputeUnits / W, (max_agents + kLidarMaxWaves - 1) / kLidarMaxWaves));
+        sim->lctl.parts = std::max(1, std::min(3 * a.compute_units / W, (max_agents + kLidarMaxWaves - 1) / kLidarMaxWaves));
         if (cfg->lidar_rays > 0) {
             const size_t glob = lidar_lds_bytes(cfg->lidar_rays, sim->lctl);
             LidarCtl staged = sim->lctl;

@@ -65,6 +65,7 @@ inline size_t step_lds_bytes(int waves, int NB, int K, int ccap, int road_cap, i
 // 64 agents, 20 000 points, K = 200: 55.4 us at 15 m/s and 61.8 at 30, with 512 entries 47.8 and
 // 50.3; at 5 m/s both take 46.
 struct Batch {  // what the prediction needs to know of the worlds
+    int compute_units = 256;  // of the device
     int worlds = 0, max_agents = 0, max_road = 0, max_edges = 0, cell_cap4 = 0, agent_cap = 0;
     bool idx16 = true, uneven = false;
     double agents = 0.0, road = 0.0;  // means
@@ -76,10 +77,8 @@ struct Shape {
     int waves = 0, bins = 0, cand_cap = 0, edge_cap = 0, road_cap = 0;
 };
 
-constexpr int kComputeUnits = 256;
-
 inline double predict_step(const Batch &b, int K, bool staged, int waves, int per_cu) {
-    const int per_unit = (b.worlds + kComputeUnits - 1) / kComputeUnits;  // workgroups of a compute unit
+    const int per_unit = (b.worlds + b.compute_units - 1) / b.compute_units;  // workgroups of a compute unit
     const int in_flight = std::min(per_cu, per_unit);
     double fixed = 6.0 + 0.0038 * b.agents * b.agents / waves + (staged ? 0.0144 * b.road / waves : 0.0);
     if (per_unit == 1) fixed *= 1.0 + 0.23 * (16 - waves) / 16;  // (nothing else to overlap it)
@@ -93,7 +92,7 @@ inline double predict_step(const Batch &b, int K, bool staged, int waves, int pe
     }
     share *= in_flight * waves;
     const double agent = std::cbrt(latency * latency * latency + share * share * share) * (0.375 + 0.0025 * K);
-    const double slots = (double)kComputeUnits * per_cu;
+    const double slots = (double)b.compute_units * per_cu;
     const double n = b.uneven && b.worlds <= slots ? b.max_agents : b.agents;
     const double each = fixed + std::max(1.0, n / waves + (n > waves ? 0.45 : 0.0)) * agent;
     double rounds = b.uneven ? std::max(1.0, b.worlds / slots + 0.4) : (double)per_unit / per_cu;

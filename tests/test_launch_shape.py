@@ -15,13 +15,13 @@ using namespace gdk;
 // waves that the registers allow per compute unit
 static int regs(int, bool staged, bool) { return staged ? 20 : 28; }
 int main() {
-    int W, n, road, K, uneven, waves, bins, cands, mode;
-    while (scanf("%d %d %d %d %d %d %d %d %d", &W, &n, &road, &K, &uneven, &waves, &bins, &cands, &mode) == 9) {
+    int cus, W, n, road, K, uneven, waves, bins, cands, mode;
+    while (scanf("%d %d %d %d %d %d %d %d %d %d", &cus, &W, &n, &road, &K, &uneven, &waves, &bins, &cands, &mode) == 10) {
         gd_config c{};
         c.num_worlds = W; c.top_k = K; c.obs_radius = 50.f;
         c.obs_waves = waves; c.obs_bins = bins; c.obs_cands = cands; c.obs_road = mode;
         Batch b;
-        b.worlds = W; b.max_agents = n; b.max_road = road; b.max_edges = road / 3; b.cell_cap4 = 488;
+        b.compute_units = cus; b.worlds = W; b.max_agents = n; b.max_road = road; b.max_edges = road / 3; b.cell_cap4 = 488;
         b.agent_cap = (n + 3) / 4 * 4; b.uneven = uneven; b.idx16 = road < 65536;
         b.agents = uneven ? n / 2.0 : n; b.road = road; b.within = road * 0.07;
         Shape s;
@@ -46,8 +46,8 @@ def choose(tmp_path_factory):
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I",
                            os.path.join(ROOT, "paper_2408_01584_amd", "csrc"), "-o", str(d / "s"), str(d / "s.cpp")])
 
-    def run(batches):
-        text = "\n".join(" ".join(map(str, b)) for b in batches)
+    def run(batches, compute_units=256):
+        text = "\n".join(" ".join(map(str, (compute_units, *b))) for b in batches)
         out = subprocess.check_output([str(d / "s")], input=text, text=True).splitlines()
         return [[int(v) for v in line.split()] for line in out]
     return run
@@ -84,3 +84,11 @@ def test_no_road_needs_no_list(choose):
 def test_what_does_not_fit_is_refused(choose):
     (ok, *_), = choose([(64, 64, 20000, 960, 0, 0, 0, 0, 1)])  # 320 KB of road in LDS
     assert not ok
+
+
+def test_compute_units_of_the_device(choose):
+    """An eighth of the worlds on an eighth of the compute units: the same shape."""
+    whole = [b for b in BATCHES if b[0] >= 256 and b[0] % 8 == 0]
+    part = [(b[0] // 8, *b[1:]) for b in whole]
+    assert choose(whole) == choose(part, 32)
+    assert choose(part) != choose(part, 32)
