@@ -161,20 +161,6 @@ __device__ __forceinline__ float wrap_pi(float a) {
     return r;
 }
 
-// Simplified bicycle model (Sec. 3.2 "Agent dynamics"): a double integrator along the heading
-// held during the step, the yaw turning by the command s (1/m) times the distance covered.
-// No clip, no dependence on the vehicle length.
-__device__ __forceinline__ void delta_model(float &x, float &y, float &yaw, float &v, float acc,
-                                            float s, float dt) {
-    const float d = v * dt + 0.5f * acc * dt * dt;
-    float sn, cs;
-    sincosf(yaw, &sn, &cs);
-    x = x + d * cs;
-    y = y + d * sn;
-    yaw = yaw + s * d;
-    v = v + acc * dt;
-}
-
 // Cell of coordinate v on an axis of n cells (clamped; NaN maps to cell 0).  Monotone
 // non-decreasing in v, which is what makes range queries over cells exact.
 __device__ __forceinline__ int cell_coord(float v, float o, float inv_cs, int n) {
