@@ -305,9 +305,9 @@ __device__ __forceinline__ void vw_single(int n, int lane, P &&point, float *AR,
 // When every removal passes, any two that touch each other's points were taken in the order of
 // their times, and no point was passed over at its time, so sorted by their times they are
 // the removals of the definition.  When one does not pass, the polyline is taken again with
-// larger chunks, then by vw_single: never on straight lines and circles, on 1 of 7000 noisy curves, on up to 19 %
-// of random points on a few integer positions.  (1.1 million polylines compared with the
-// definition on the CPU.)  When an eighth of the points is gone the chunks are dealt out anew.
+// larger chunks, then by vw_single: never on straight lines and circles, on 1 of 7000 noisy
+// curves, on up to 19 % of random points on a few integer positions.  (5.6 million polylines
+// compared with the definition by a host model that interleaves the chunks at random.)  When an eighth of the points is gone the chunks are dealt out anew.
 //
 // Bound by the latency of a removal (about 1700 cycles: six dependent LDS reads, the
 // coordinates through the caches, the chunk's next key) times the 150 or so that follow one
