@@ -482,7 +482,7 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
 
 // (four waves per SIMD: 128 registers; one more register costs a quarter of the waves)
 template <bool DELTA, bool ONE>
-__global__ __launch_bounds__(kRollThreads, 4) void k_rollout_fwd(SimArgs a, const float2 *__restrict__ act,
+__global__ __launch_bounds__(kRollThreads, 4) void k_rollout_fwd(SimArgs a, int tile0, const float2 *__restrict__ act,
                                                               int T, int C, float *__restrict__ rewards,
                                                               float *__restrict__ ckpt,
                                                               float *__restrict__ slog) {
@@ -491,8 +491,9 @@ __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_fwd(SimArgs a, cons
     __shared__ float2 s_inv[kList];
     __shared__ float s_dc[kList];
     const int row = threadIdx.x / kRow, sub = threadIdx.x % kRow;
-    const int i = xcd_tile(blockIdx.x, gridDim.x) * kRollAgents + row;
-    if (i >= a.A) return;
+    const unsigned at = (unsigned)(tile0 + xcd_tile(blockIdx.x, gridDim.x)) * kRollAgents + row;
+    if (at >= (unsigned)a.A) return;
+    const int i = (int)at;
     const EdgeList ls{s_seg + row * kEdgeStride, s_inv + row * kEdgeStride, s_dc + row * kEdgeStride};
     const size_t A = (size_t)a.A;
     const float2 none = make_float2(0.f, 0.f);
@@ -812,7 +813,7 @@ enum ObsGrad { kObsNone = 0, kObsScratch = 1, kObsGather = 2 };
 // steps, comes in parts (kObsScratch): then the adjoint of the state before the part is kept in
 // `carry`.  kObsGather reads slog and grad_obs instead.
 template <bool DELTA, int OBS, bool ONE>
-__global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, const float2 *__restrict__ act,
+__global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, int tile0, const float2 *__restrict__ act,
                                                               const float *__restrict__ ckpt, int T, int C,
                                                               int B, int Ts, int Te,
                                                               const float *__restrict__ grad_r,
@@ -827,8 +828,9 @@ __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, cons
     __shared__ float2 s_inv[kList];
     __shared__ float s_dc[kList];
     const int row = threadIdx.x / kRow, sub = threadIdx.x % kRow;
-    const int i = xcd_tile(blockIdx.x, gridDim.x) * kRollAgents + row;
-    if (i >= a.A) return;
+    const unsigned at = (unsigned)(tile0 + xcd_tile(blockIdx.x, gridDim.x)) * kRollAgents + row;
+    if (at >= (unsigned)a.A) return;
+    const int i = (int)at;
     const EdgeList ls{s_seg + row * kEdgeStride, s_inv + row * kEdgeStride, s_dc + row * kEdgeStride};
     const size_t A = (size_t)a.A;
     const float L = a.len[i], gxa = a.gx[i], gya = a.gy[i];
@@ -1079,16 +1081,24 @@ hipError_t launch_invert_actions_impl(const float *states, int T, int A, float d
     return hipGetLastError();
 }
 
-// workgroups of the rollout kernels: 16 agents each
-static unsigned roll_blocks(int A) { return (unsigned)(((long long)A + kRollAgents - 1) / kRollAgents); }
+// launches of a rollout kernel k (16 agents per workgroup)
+template <typename K, typename... Args>
+static hipError_t launch_rows(K k, const SimArgs &a, hipStream_t s, Args... args) {
+    hipError_t e = hipSuccess;
+    in_launches(((long long)a.A + kRollAgents - 1) / kRollAgents, kRollThreads, [&](long long first, long long count) {
+        if (e != hipSuccess) return;
+        hipLaunchKernelGGL(k, dim3((unsigned)count), dim3(kRollThreads), 0, s, a, (int)first, args...);
+        e = hipGetLastError();
+    });
+    return e;
+}
 
 hipError_t launch_rollout_fwd_impl(const SimArgs &a, const float2 *actions, int T, int C,
                                    float *rewards, float *ckpt, float *states, hipStream_t s) {
     if (C < 1 || C > kMaxCkpt) return hipErrorInvalidValue;
     auto k = a.dyn == GD_DYN_DELTA ? (T == 1 ? k_rollout_fwd<true, true> : k_rollout_fwd<true, false>)
                                    : (T == 1 ? k_rollout_fwd<false, true> : k_rollout_fwd<false, false>);
-    hipLaunchKernelGGL(k, dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a, actions, T, C, rewards, ckpt, states);
-    return hipGetLastError();
+    return launch_rows(k, a, s, actions, T, C, rewards, ckpt, states);
 }
 
 // lanes per agent of k_rollout_obs: the power of two that leaves the fewest lanes without a slot
@@ -1134,9 +1144,8 @@ static hipError_t launch_bwd(const SimArgs &a, const float2 *actions, const floa
     const int B = roll_block(T, C);
     if (!grad_obs || !scratch) {
         auto k = grad_obs ? k_rollout_bwd<DELTA, kObsGather, ONE> : k_rollout_bwd<DELTA, kObsNone, ONE>;
-        hipLaunchKernelGGL(k, dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a, actions, ckpt, T, C, B, 0, T,
-                           grad_rewards, nullptr, nullptr, states, grad_obs, grad_actions, grad_state0);
-        return hipGetLastError();
+        return launch_rows(k, a, s, actions, ckpt, T, C, B, 0, T, grad_rewards, nullptr, nullptr, states, grad_obs,
+                           grad_actions, grad_state0);
     }
     // the observation's gradient in parts of as many whole blocks as the scratch holds
     const ObsGradScratch L = obs_grad_scratch(a.A, T);
@@ -1156,10 +1165,9 @@ static hipError_t launch_bwd(const SimArgs &a, const float2 *actions, const floa
                            lds, s, a, states, Ts, share, grad_obs, og);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_rollout_bwd<DELTA, kObsScratch, ONE>), dim3(roll_blocks(a.A)), dim3(kRollThreads), 0, s, a,
-                           actions, ckpt, T, C, B, Ts, Te, grad_rewards, og, carry, nullptr, nullptr, grad_actions,
-                           grad_state0);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = launch_rows(k_rollout_bwd<DELTA, kObsScratch, ONE>, a, s, actions, ckpt, T, C, B, Ts, Te, grad_rewards, og,
+                             carry, nullptr, nullptr, grad_actions, grad_state0)) != hipSuccess)
+            return e;
     }
     return hipSuccess;
 }

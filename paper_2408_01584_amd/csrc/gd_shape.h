@@ -38,6 +38,14 @@ inline size_t step_lds_bytes(int waves, int NB, int K, int ccap, int road_cap, i
     return road + (size_t)agent_cap * 4 * kAgentArrays + (edges > per_wave ? edges : per_wave);
 }
 
+// Calls f(first, count) for the launches that take workgroups [0, groups) of `threads` threads: a
+// grid holds fewer than 2^32 threads, and one beyond is cut without an error.
+template <typename F>
+void in_launches(long long groups, int threads, F &&f) {
+    const long long most = (1ll << 31) / threads;
+    for (long long first = 0; first < groups; first += most) f(first, std::min(most, groups - first));
+}
+
 // Launch shape of the step kernel: waves per workgroup, distance bins, candidate-list
 // entries per wave, and whether the road is staged in LDS.  Fields the config fixes are
 // kept; of the shapes that fit, the one with the lowest predicted step time is taken.

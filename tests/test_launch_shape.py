@@ -92,3 +92,25 @@ def test_compute_units_of_the_device(choose):
     part = [(b[0] // 8, *b[1:]) for b in whole]
     assert choose(whole) == choose(part, 32)
     assert choose(part) != choose(part, 32)
+
+
+def test_grids_stay_below_2_to_32_threads(tmp_path):
+    """Every workgroup is in one launch, in order, and no launch reaches 2^32 threads."""
+    (tmp_path / "g.cpp").write_text(r'''
+#include <cstdio>
+#include "gd_shape.h"
+int main() {
+    for (long long groups : {0ll, 1ll, (1ll << 23) - 1, 1ll << 23, (1ll << 23) + 1, 1ll << 24, (1ll << 27) - 3}) {
+        long long next = 0;
+        bool ok = true;
+        gdk::in_launches(groups, 256, [&](long long first, long long count) {
+            ok = ok && first == next && count > 0 && count * 256 < (1ll << 32) && first < (1ll << 31);
+            next = first + count;
+        });
+        if (!ok || next != groups) printf("wrong %lld\n", groups);
+    }
+}
+''')
+    subprocess.check_call(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I",
+                           os.path.join(ROOT, "paper_2408_01584_amd", "csrc"), "-o", str(tmp_path / "g"), str(tmp_path / "g.cpp")])
+    assert subprocess.check_output([str(tmp_path / "g")], text=True) == ""
