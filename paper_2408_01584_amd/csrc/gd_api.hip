@@ -19,9 +19,10 @@ namespace gdk {
 hipError_t launch_lidar_impl(const SimArgs &a, const LidarCtl &lc, hipStream_t s);
 hipError_t launch_rollout_fwd_impl(const SimArgs &a, const float2 *actions, int T, int C,
                                    float *rewards, float *ckpt, float *states, hipStream_t s);
-hipError_t launch_rollout_obs_impl(const SimArgs &a, const float *states, int T, int max_agents, float *obs,
+// (units: compute units of the device)
+hipError_t launch_rollout_obs_impl(const SimArgs &a, const float *states, int T, int max_agents, int units, float *obs,
                                    hipStream_t s);
-hipError_t launch_rollout_bwd_impl(const SimArgs &a, const float2 *actions, const float *ckpt,
+hipError_t launch_rollout_bwd_impl(const SimArgs &a, int units, const float2 *actions, const float *ckpt,
                                    int T, int C, const float *grad_rewards, const float *grad_obs,
                                    const float *states, int max_agents, void *scratch,
                                    float2 *grad_actions, float *grad_state0, hipStream_t s);
@@ -78,7 +79,7 @@ struct gd_sim {
     StepCtl ctl{};  // launch shape of the fused step (mode and pointers set per call)
     LidarCtl lctl{};  // launch shape of the LIDAR kernel
     int waves = 16, bins = 256;
-    int max_road = 0, max_agents = 0;
+    int max_road = 0, max_agents = 0, compute_units = 0;
     long long slots = 0;
     // kernel timing
     bool timing = false;
@@ -358,7 +359,7 @@ gd_status gd_create(const gd_config *cfg, const int32_t *h_agent_off, const int3
     a.T_ep = cfg->episode_len;
     a.flags = cfg->flags;
     a.dyn = cfg->dynamics;
-    a.compute_units = std::max(compute_units, 1);
+    sim->compute_units = std::max(compute_units, 1);
     a.dt = cfg->dt;
     a.R_obs = cfg->obs_radius;
     {
@@ -463,7 +464,7 @@ gd_status gd_create(const gd_config *cfg, const int32_t *h_agent_off, const int3
             max_edges = std::max(max_edges, g.n_edge);
         }
         Batch batch;
-        batch.compute_units = a.compute_units;
+        batch.compute_units = sim->compute_units;
         batch.worlds = W;
         batch.max_agents = max_agents;
         batch.max_road = max_road;
@@ -501,7 +502,7 @@ gd_status gd_create(const gd_config *cfg, const int32_t *h_agent_off, const int3
         sim->lctl.edge_cap = 0;
         // few worlds: several workgroups each, until there are three per compute unit or a
         // wave has one agent
-        sim->lctl.parts = std::max(1, std::min(3 * a.compute_units / W, (max_agents + kLidarMaxWaves - 1) / kLidarMaxWaves));
+        sim->lctl.parts = std::max(1, std::min(3 * sim->compute_units / W, (max_agents + kLidarMaxWaves - 1) / kLidarMaxWaves));
         if (cfg->lidar_rays > 0) {
             const size_t glob = lidar_lds_bytes(cfg->lidar_rays, sim->lctl);
             LidarCtl staged = sim->lctl;
@@ -575,7 +576,7 @@ gd_status gd_rollout_fwd(gd_sim *sim, const float *actions, int32_t T, int32_t c
     TIMED(sim, s, GD_PHASE_ROLLOUT_FWD,
           launch_rollout_fwd_impl(sim->args, (const float2 *)actions, T, ckpt_every, rewards, ckpt, states, s),
           "rollout forward launch");
-    if (obs) HIP_TRY(launch_rollout_obs_impl(sim->args, states, T, sim->max_agents, obs, s), "rollout observation launch");
+    if (obs) HIP_TRY(launch_rollout_obs_impl(sim->args, states, T, sim->max_agents, sim->compute_units, obs, s), "rollout observation launch");
     return GD_OK;
 }
 
@@ -599,7 +600,7 @@ static gd_status rollout_bwd(gd_sim *sim, const float *actions, const float *ckp
     }
     hipStream_t s = (hipStream_t)stream;
     TIMED(sim, s, GD_PHASE_ROLLOUT_BWD,
-          launch_rollout_bwd_impl(sim->args, (const float2 *)actions, ckpt, T, ckpt_every, grad_rewards,
+          launch_rollout_bwd_impl(sim->args, sim->compute_units, (const float2 *)actions, ckpt, T, ckpt_every, grad_rewards,
                                   grad_obs, grad_obs ? states : nullptr, sim->max_agents, with_ws ? ws : nullptr,
                                   (float2 *)grad_actions, grad_state0, s),
           "rollout backward launch");

@@ -31,7 +31,6 @@ struct SimArgs {
     int K, P, N, T_ep;
     uint32_t flags;
     int dyn;  // GD_DYN_BICYCLE or GD_DYN_DELTA
-    int compute_units;  // of the device (launch rules)
     float dt, R_obs, R2_obs, goal_r2, vmax, lidar_range, penalty;
     float lidar_fov;  // 0: full ring; > 0: view-cone width (rad)
 

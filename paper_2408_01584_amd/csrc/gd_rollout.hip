@@ -1113,17 +1113,17 @@ static int obs_lanes(int P) {
 // that gives are fewer than four per compute unit; then a share, at most `most` of them.
 // Below that a world's kernels take as long as its agents squared: 4 x 1000 agents, T = 5: forward
 // 443 -> 86 us, backward 3641 -> 86; 1 x 128, T = 10: 26 -> 19 and 60 -> 24.
-static int agents_per_group(const SimArgs &a, int max_agents, long long groups, int most) {
-    const int shares = groups >= 4 * a.compute_units ? 1 : (int)std::min(8 * a.compute_units / groups, (long long)most);
+static int agents_per_group(int units, int max_agents, long long groups, int most) {
+    const int shares = groups >= 4 * units ? 1 : (int)std::min(8 * units / groups, (long long)most);
     return std::max(1, (max_agents + std::max(shares, 1) - 1) / std::max(shares, 1));
 }
 
-hipError_t launch_rollout_obs_impl(const SimArgs &a, const float *states, int T, int max_agents, float *obs,
+hipError_t launch_rollout_obs_impl(const SimArgs &a, const float *states, int T, int max_agents, int units, float *obs,
                                    hipStream_t s) {
     // about 4096 slots per workgroup, 16 per thread; at least one step, states within 48 KB
     const long long slots = (long long)std::max(max_agents, 1) * std::max(a.P, 1);
     const int steps = (int)std::max(1ll, std::min({4096 / slots, (long long)T, 2048ll / std::max(max_agents, 1)}));
-    const int share = agents_per_group(a, max_agents, (long long)a.W * ((T + steps - 1) / steps),
+    const int share = agents_per_group(units, max_agents, (long long)a.W * ((T + steps - 1) / steps),
                                        (int)std::min((long long)max_agents, (slots + 4095) / 4096));
     const size_t lds = (size_t)steps * max_agents * (sizeof(float4) + sizeof(float2));
     const long long most = 65535ll * steps;  // (grid axis y)
@@ -1138,7 +1138,7 @@ hipError_t launch_rollout_obs_impl(const SimArgs &a, const float *states, int T,
 }
 
 template <bool DELTA, bool ONE>
-static hipError_t launch_bwd(const SimArgs &a, const float2 *actions, const float *ckpt, int T, int C,
+static hipError_t launch_bwd(const SimArgs &a, int units, const float2 *actions, const float *ckpt, int T, int C,
                              const float *grad_rewards, const float *grad_obs, const float *states, int max_agents,
                              void *scratch, float2 *grad_actions, float *grad_state0, hipStream_t s) {
     const int B = roll_block(T, C);
@@ -1151,7 +1151,7 @@ static hipError_t launch_bwd(const SimArgs &a, const float2 *actions, const floa
     const ObsGradScratch L = obs_grad_scratch(a.A, T);
     float4 *og = (float4 *)scratch, *carry = (float4 *)((char *)scratch + L.carry);
     const int part = L.steps / B * B;
-    const int share = agents_per_group(a, max_agents, (long long)a.W * std::min(T, part), (max_agents + 15) / 16);
+    const int share = agents_per_group(units, max_agents, (long long)a.W * std::min(T, part), (max_agents + 15) / 16);
     int cols = 8;  // lanes of an observer: as many as agents, a power of two
     while (cols < kWave && cols < max_agents) cols *= 2;
     const int rows = kWave / cols;
@@ -1172,14 +1172,14 @@ static hipError_t launch_bwd(const SimArgs &a, const float2 *actions, const floa
     return hipSuccess;
 }
 
-hipError_t launch_rollout_bwd_impl(const SimArgs &a, const float2 *actions, const float *ckpt, int T,
+hipError_t launch_rollout_bwd_impl(const SimArgs &a, int units, const float2 *actions, const float *ckpt, int T,
                                    int C, const float *grad_rewards, const float *grad_obs,
                                    const float *states, int max_agents, void *scratch, float2 *grad_actions,
                                    float *grad_state0, hipStream_t s) {
     if (C < 1 || C > kMaxCkpt) return hipErrorInvalidValue;
     auto f = a.dyn == GD_DYN_DELTA ? (T == 1 ? launch_bwd<true, true> : launch_bwd<true, false>)
                                    : (T == 1 ? launch_bwd<false, true> : launch_bwd<false, false>);
-    return f(a, actions, ckpt, T, C, grad_rewards, grad_obs, states, max_agents, scratch, grad_actions, grad_state0, s);
+    return f(a, units, actions, ckpt, T, C, grad_rewards, grad_obs, states, max_agents, scratch, grad_actions, grad_state0, s);
 }
 
 }  // namespace gdk
