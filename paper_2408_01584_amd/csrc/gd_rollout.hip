@@ -482,7 +482,7 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
 
 // (four waves per SIMD: 128 registers; one more register costs a quarter of the waves)
 template <bool DELTA, bool ONE>
-__global__ __launch_bounds__(kRollThreads, 4) void k_rollout_fwd(SimArgs a, int tile0, const float2 *__restrict__ act,
+__global__ __launch_bounds__(kRollThreads, 4) void k_rollout_fwd(SimArgs a, const float2 *__restrict__ act,
                                                               int T, int C, float *__restrict__ rewards,
                                                               float *__restrict__ ckpt,
                                                               float *__restrict__ slog) {
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_fwd(SimArgs a, int 
     __shared__ float2 s_inv[kList];
     __shared__ float s_dc[kList];
     const int row = threadIdx.x / kRow, sub = threadIdx.x % kRow;
-    const unsigned at = (unsigned)(tile0 + xcd_tile(blockIdx.x, gridDim.x)) * kRollAgents + row;
+    const unsigned at = (blockIdx.y * gridDim.x + (unsigned)xcd_tile(blockIdx.x, gridDim.x)) * kRollAgents + row;
     if (at >= (unsigned)a.A) return;
     const int i = (int)at;
     const EdgeList ls{s_seg + row * kEdgeStride, s_inv + row * kEdgeStride, s_dc + row * kEdgeStride};
@@ -813,7 +813,7 @@ enum ObsGrad { kObsNone = 0, kObsScratch = 1, kObsGather = 2 };
 // steps, comes in parts (kObsScratch): then the adjoint of the state before the part is kept in
 // `carry`.  kObsGather reads slog and grad_obs instead.
 template <bool DELTA, int OBS, bool ONE>
-__global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, int tile0, const float2 *__restrict__ act,
+__global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, const float2 *__restrict__ act,
                                                               const float *__restrict__ ckpt, int T, int C,
                                                               int B, int Ts, int Te,
                                                               const float *__restrict__ grad_r,
@@ -828,7 +828,7 @@ __global__ __launch_bounds__(kRollThreads, 4) void k_rollout_bwd(SimArgs a, int 
     __shared__ float2 s_inv[kList];
     __shared__ float s_dc[kList];
     const int row = threadIdx.x / kRow, sub = threadIdx.x % kRow;
-    const unsigned at = (unsigned)(tile0 + xcd_tile(blockIdx.x, gridDim.x)) * kRollAgents + row;
+    const unsigned at = (blockIdx.y * gridDim.x + (unsigned)xcd_tile(blockIdx.x, gridDim.x)) * kRollAgents + row;
     if (at >= (unsigned)a.A) return;
     const int i = (int)at;
     const EdgeList ls{s_seg + row * kEdgeStride, s_inv + row * kEdgeStride, s_dc + row * kEdgeStride};
@@ -1081,16 +1081,12 @@ hipError_t launch_invert_actions_impl(const float *states, int T, int A, float d
     return hipGetLastError();
 }
 
-// launches of a rollout kernel k (16 agents per workgroup)
+// launches a rollout kernel k, 16 agents per workgroup
 template <typename K, typename... Args>
 static hipError_t launch_rows(K k, const SimArgs &a, hipStream_t s, Args... args) {
-    hipError_t e = hipSuccess;
-    in_launches(((long long)a.A + kRollAgents - 1) / kRollAgents, kRollThreads, [&](long long first, long long count) {
-        if (e != hipSuccess) return;
-        hipLaunchKernelGGL(k, dim3((unsigned)count), dim3(kRollThreads), 0, s, a, (int)first, args...);
-        e = hipGetLastError();
-    });
-    return e;
+    const Grid2 g = grid_of(((long long)a.A + kRollAgents - 1) / kRollAgents, kRollThreads);
+    hipLaunchKernelGGL(k, dim3(g.x, g.y), dim3(kRollThreads), 0, s, a, args...);
+    return hipGetLastError();
 }
 
 hipError_t launch_rollout_fwd_impl(const SimArgs &a, const float2 *actions, int T, int C,

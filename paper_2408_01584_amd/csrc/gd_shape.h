@@ -38,12 +38,14 @@ inline size_t step_lds_bytes(int waves, int NB, int K, int ccap, int road_cap, i
     return road + (size_t)agent_cap * 4 * kAgentArrays + (edges > per_wave ? edges : per_wave);
 }
 
-// Calls f(first, count) for the launches that take workgroups [0, groups) of `threads` threads: a
-// grid holds fewer than 2^32 threads, and one beyond is cut without an error.
-template <typename F>
-void in_launches(long long groups, int threads, F &&f) {
-    const long long most = (1ll << 31) / threads;
-    for (long long first = 0; first < groups; first += most) f(first, std::min(most, groups - first));
+// Grid of at least `groups` (> 0) workgroups of `threads` threads, x fastest: an axis holds fewer
+// than 2^32 threads, and one beyond is cut without an error.
+struct Grid2 {
+    unsigned x, y;
+};
+inline Grid2 grid_of(long long groups, int threads) {
+    const long long x = std::min(groups, (1ll << 31) / threads);
+    return {(unsigned)x, (unsigned)((groups + x - 1) / x)};
 }
 
 // Launch shape of the step kernel: waves per workgroup, distance bins, candidate-list
