@@ -269,10 +269,12 @@ __global__ __launch_bounds__(kLidarMaxWaves * kWave) void k_lidar(SimArgs a, Lid
             nl = 0;
         };
         auto push = [&](bool ok, float ax, float ay, float bx, float by, unsigned type, float near2) {
-            const float a2 = fmaxf(ax * ax + ay * ay, 1e-30f), b2 = fmaxf(bx * bx + by * by, 1e-30f);
+            const float a2 = ax * ax + ay * ay, b2 = bx * bx + by * by, m2 = fminf(a2, b2);
             int k0, cnt = arc_rays<CONE>(ax, ay, __builtin_amdgcn_rsqf(a2), bx, by, __builtin_amdgcn_rsqf(b2), N,
                                          inv_step, half, k0);
-            const bool keep = ok && cnt > 0 && fminf(a2, b2) <= near2;
+            // (a segment that begins at the agent's centre meets every ray there, at distance 0, and
+            // nowhere else: no hit)
+            const bool keep = ok && cnt > 0 && m2 > 0.0f && m2 <= near2;
             const unsigned long long bal = __ballot(keep);
             const int add = __popcll(bal);
             if (nl + add > kLidarList) flush();
